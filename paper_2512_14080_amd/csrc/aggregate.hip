@@ -256,22 +256,37 @@ __global__ __launch_bounds__(256) void bias_split_kernel(const float* __restrict
   B2s[(size_t)k * 2 * E + E + e] = f2bf(v - bf2f(hi));
 }
 
-// One workgroup per (expert, 512-column chunk).  Wave w sums the expert's
-// rows w, w + 4, w + 8, ... (four rows' loads in flight per step), lane l owns
-// columns 8l .. 8l + 7 of the chunk; the four wave sums are added in wave
-// order through LDS, so the result does not depend on timing.
-constexpr int kColsumWaves = 4;
-__global__ __launch_bounds__(64 * kColsumWaves) void expert_colsum_kernel(
-    const uint16_t* __restrict__ src, int64_t ld, int cols, const int32_t* __restrict__ offsets,
-    const int32_t* __restrict__ row_token, const float* __restrict__ row_w, float* __restrict__ out) {
+// The expert-bias gradients db1 (columns of dH) and db2 (columns of s * dO) in
+// two launches.  They are bound by the latency of the row loads: a single
+// workgroup that walks an expert's rows has one batch of loads in flight at a
+// time (T = 5003, d = 896, n = 192, E = 40, K = 3, one workgroup of four waves
+// per expert and 512 columns: 117 and 90 us for 17 MB).  So the rows are cut
+// along the backward's m-tile list: one workgroup per m-tile and 512 columns,
+// eight waves with eight rows each in flight, wave w on rows w, w + 8, ...;
+// the waves' sums are added in wave order through LDS.  The second kernel adds
+// an expert's tiles in row order, so nothing depends on timing.
+constexpr int kColsumWaves = 8;
+struct ColsumSrc {
+  const uint16_t* src;
+  int cols;               // columns summed, and the leading dimension of src; 0: not asked for
+  const int32_t* token;   // gathered rows, or null
+  const float* w;         // row weights, or null
+};
+__global__ __launch_bounds__(64 * kColsumWaves) void tile_colsum_kernel(const int32_t* __restrict__ mtiles, ColsumSrc s1,
+                                                                       ColsumSrc s2, int ny1,
+                                                                       float* __restrict__ part) {
   __shared__ float red[kColsumWaves][512];
-  const int e = blockIdx.x;
+  const int tile = blockIdx.x;
+  if (tile >= mtiles[0]) return;
+  const bool second = (int)blockIdx.y >= ny1;
+  const ColsumSrc s = second ? s2 : s1;
+  const int chunk = second ? blockIdx.y - ny1 : blockIdx.y;
+  const int nrows = mtiles[4 + 4 * tile + 2], r0 = mtiles[4 + 4 * tile + 3], r1 = r0 + nrows;
   const int wave = threadIdx.x >> 6, lane = lane_id();
-  const int c = blockIdx.y * 512 + lane * 8;
-  const bool live = c < cols;
-  const int r0 = offsets[e], r1 = offsets[e + 1];
+  const int c = chunk * 512 + lane * 8;
+  const bool live = c < s.cols;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  constexpr int kU = 4;
+  constexpr int kU = 8;
   for (int rb = r0 + wave; rb < r1; rb += kColsumWaves * kU) {
     u32x4 v[kU];
     float w[kU];
@@ -279,9 +294,9 @@ __global__ __launch_bounds__(64 * kColsumWaves) void expert_colsum_kernel(
     for (int u = 0; u < kU; ++u) {
       const int r = rb + u * kColsumWaves;
       const bool ok = r < r1 && live;
-      const int g = ok ? (row_token ? row_token[r] : r) : 0;
-      w[u] = ok ? (row_w ? row_w[r] : 1.f) : 0.f;
-      v[u] = ok ? *(const u32x4*)(src + (size_t)g * ld + c) : u32x4{0u, 0u, 0u, 0u};
+      const int g = ok ? (s.token ? s.token[r] : r) : 0;
+      w[u] = ok ? (s.w ? s.w[r] : 1.f) : 0.f;
+      v[u] = ok ? *(const u32x4*)(s.src + (size_t)g * s.cols + c) : u32x4{0u, 0u, 0u, 0u};
     }
 #pragma unroll
     for (int u = 0; u < kU; ++u)
@@ -294,14 +309,51 @@ __global__ __launch_bounds__(64 * kColsumWaves) void expert_colsum_kernel(
 #pragma unroll
   for (int q = 0; q < 8; ++q) red[wave][lane * 8 + q] = acc[q];
   __syncthreads();
-  for (int i = threadIdx.x; i < 512; i += 64 * kColsumWaves) {
-    const int cc = blockIdx.y * 512 + i;
-    if (cc >= cols) continue;
-    float t = 0.f;
+  const int cc = chunk * 512 + threadIdx.x;  // one column per thread
+  if (cc >= s.cols) return;
+  float t = 0.f;
 #pragma unroll
-    for (int w2 = 0; w2 < kColsumWaves; ++w2) t += red[w2][i];
-    out[(size_t)e * cols + cc] = t;
+  for (int w2 = 0; w2 < kColsumWaves; ++w2) t += red[w2][threadIdx.x];
+  part[(size_t)tile * (s1.cols + s2.cols) + (second ? s1.cols : 0) + cc] = t;
+}
+
+// out[e][c] = the sum of expert e's tiles: its full tiles, contiguous in the
+// list, then its partial one (after every expert's full tiles).  Experts
+// without rows get zeros.
+__global__ __launch_bounds__(256) void colsum_reduce_kernel(const int32_t* __restrict__ mtiles,
+                                                            const int32_t* __restrict__ offsets,
+                                                            const float* __restrict__ part, int mtile, int cols1,
+                                                            int cols2, float* __restrict__ out1,
+                                                            float* __restrict__ out2) {
+  __shared__ int red[2][4];
+  const int e = blockIdx.x;
+  int nf = 0, np = 0;  // tiles of the experts before e
+  for (int i = threadIdx.x; i < e; i += 256) {
+    const int cnt = offsets[i + 1] - offsets[i];
+    nf += cnt / mtile;
+    np += cnt % mtile != 0;
   }
+  nf = wave_sum_i(nf);
+  np = wave_sum_i(np);
+  if (lane_id() == 0) {
+    red[0][threadIdx.x >> 6] = nf;
+    red[1][threadIdx.x >> 6] = np;
+  }
+  __syncthreads();
+  const int first = red[0][0] + red[0][1] + red[0][2] + red[0][3];
+  const int last = mtiles[0] - mtiles[1] + red[1][0] + red[1][1] + red[1][2] + red[1][3];
+  const int c = blockIdx.y * 256 + threadIdx.x, cols = cols1 + cols2;
+  if (c >= cols) return;
+  const int cnt = offsets[e + 1] - offsets[e];
+  const float* p = part + (size_t)first * cols + c;
+  float t = 0.f;
+#pragma unroll 8
+  for (int i = 0; i < cnt / mtile; ++i) t += p[(size_t)i * cols];
+  if (cnt % mtile) t += part[(size_t)last * cols + c];
+  if (c < cols1)
+    out1[(size_t)e * cols1 + c] = t;
+  else
+    out2[(size_t)e * cols2 + c - cols1] = t;
 }
 
 hipError_t launch_bias_split(const float* b2, int E, int d, uint16_t* B2s, hipStream_t s) {
@@ -309,11 +361,16 @@ hipError_t launch_bias_split(const float* b2, int E, int d, uint16_t* B2s, hipSt
   return hipGetLastError();
 }
 
-hipError_t launch_expert_colsum(const uint16_t* src, int64_t ld, int cols, const int32_t* offsets,
-                                const int32_t* row_token, const float* row_w, int E, float* out, hipStream_t s) {
-  if (cols % 8) return hipErrorInvalidValue;  // 16-byte column groups
-  expert_colsum_kernel<<<dim3(E, (cols + 511) / 512), dim3(64 * kColsumWaves), 0, s>>>(src, ld, cols, offsets,
-                                                                                        row_token, row_w, out);
+hipError_t launch_expert_colsum(const ExpertColsumArgs& a, hipStream_t s) {
+  const int c1 = a.db1 ? 2 * a.n : 0, c2 = a.db2 ? a.d : 0;
+  const int ny1 = (c1 + 511) / 512, ny2 = (c2 + 511) / 512;
+  const int tiles = a.capacity / kMTile + a.E;  // bound of the list's length
+  tile_colsum_kernel<<<dim3(tiles, ny1 + ny2), dim3(64 * kColsumWaves), 0, s>>>(
+      a.mtiles, {a.dH, c1, nullptr, nullptr}, {a.dO, c2, a.row_token, a.row_w}, ny1, a.part);
+  const hipError_t err = hipGetLastError();
+  if (err != hipSuccess) return err;
+  colsum_reduce_kernel<<<dim3(a.E, (c1 + c2 + 255) / 256), dim3(256), 0, s>>>(a.mtiles, a.offsets, a.part, kMTile, c1,
+                                                                              c2, a.db1, a.db2);
   return hipGetLastError();
 }
 

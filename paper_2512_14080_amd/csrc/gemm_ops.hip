@@ -66,7 +66,6 @@ __device__ __forceinline__ u32x2 pack_bf16x4(float a, float b, float c, float d)
 // one {expert, m0, rows, first global row} entry per m-tile, the full tiles
 // of every expert in expert order first and the partial last tiles after
 // them.  A GEMM workgroup reads its tile's entry with one scalar load.
-constexpr int kMTile = 256;
 typedef int i32x4 __attribute__((ext_vector_type(4)));
 #define SMOE_CONST __attribute__((address_space(4)))
 

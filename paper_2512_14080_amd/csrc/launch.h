@@ -38,6 +38,7 @@ hipError_t launch_router_topk(const RouterTopkArgs& a, hipStream_t s);
 
 // The varlen-M m-tile list (mtiles_kernel): built from the expert offsets
 // once per forward / backward call, read by the up, down, dH and dX~ GEMMs.
+constexpr int kMTile = 256;  // rows of an m-tile
 size_t mtiles_bytes(int64_t capacity, int E);
 hipError_t launch_mtiles(const int32_t* offsets, int E, int32_t* out, hipStream_t s);
 
@@ -120,11 +121,17 @@ hipError_t launch_dwr(const DWrArgs& a, hipStream_t s);
 // products with the bf16 dO are exact in the fp32 accumulation, so the term
 // keeps about 16 bits of b2.  launch_bias_split writes B2s.
 hipError_t launch_bias_split(const float* b2, int E, int d, uint16_t* B2s, hipStream_t s);
-// out[e][c] = sum over the rows r of expert e of w_r * src[g(r)][c], with
-// g(r) = row_token[r] (or r when row_token is null) and w_r = row_w[r] (or 1);
-// fixed summation order, fp32.
-hipError_t launch_expert_colsum(const uint16_t* src, int64_t ld, int cols, const int32_t* offsets,
-                                const int32_t* row_token, const float* row_w, int E, float* out, hipStream_t s);
+// The expert-bias gradients (either may be null): db1[e] = sum over expert e's
+// rows of dH, db2[e] = sum of s * dO of the rows' tokens; fixed summation order,
+// fp32.  part: colsum_part_bytes(capacity, E, d, n) bytes.
+struct ExpertColsumArgs {
+  const uint16_t* dH; const uint16_t* dO; const int32_t* offsets; const int32_t* row_token; const float* row_w;
+  const int32_t* mtiles; float* part; float* db1; float* db2; int d, n, E, capacity;
+};
+inline size_t colsum_part_bytes(int64_t capacity, int E, int d, int n) {
+  return (size_t)(capacity / kMTile + E) * (2 * n + d) * 4;
+}
+hipError_t launch_expert_colsum(const ExpertColsumArgs& a, hipStream_t s);
 
 // aggregation and small kernels
 hipError_t launch_agg_o(const uint16_t* Y, const moe_routing& r, uint16_t* O, int T, int d, hipStream_t s);

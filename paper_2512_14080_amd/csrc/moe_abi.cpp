@@ -136,6 +136,7 @@ struct BwdWs {
   float* dw_part;   // fp32 partials of row-chunked experts
   uint16_t* b2s;    // expert-bias dS term: b2^T as bf16 high/low parts [d][2E]
   float* bq;        // and <dO_t, b2_e> in those two parts [T][2E]
+  float* colsum_part;  // per m-tile column sums of the expert-bias gradients
 };
 
 size_t carve(char* base, size_t off, size_t bytes, void** out) {
@@ -179,6 +180,7 @@ size_t bwd_layout(const moe_dims& m, int64_t cap, char* base, BwdWs* w) {
   off = carve(base, off, smoe::dw_part_bytes(m.d, m.n), w ? (void**)&w->dw_part : nullptr);
   off = carve(base, off, (size_t)m.d * 2 * m.E * 2, w ? (void**)&w->b2s : nullptr);
   off = carve(base, off, (size_t)m.T * 2 * m.E * 4, w ? (void**)&w->bq : nullptr);
+  off = carve(base, off, smoe::colsum_part_bytes(cap, m.E, m.d, m.n), w ? (void**)&w->colsum_part : nullptr);
   return off;
 }
 
@@ -594,12 +596,11 @@ int moe_bwd(moe_dims m, const moe_bf16* dO, const moe_bf16* X, const moe_bf16* H
   HIP_TRY(smoe::launch_bwd_final_reduce(w.klist1, w.dw_part, dW1, m.d, m.n, w.dWr_part, dWr, splits, w.dbias_part,
                                         dbias, m.T, m.E, stream),
           "final reductions (dW1 split experts, dW_r, dbias)");
-  if (eb && eb->db1)
-    HIP_TRY(smoe::launch_expert_colsum(w.dH, 2 * m.n, 2 * m.n, r->offsets, nullptr, nullptr, m.E, eb->db1, stream),
-            "expert-bias gradient db1");
-  if (eb && eb->db2)
-    HIP_TRY(smoe::launch_expert_colsum(dO, m.d, m.d, r->offsets, r->row_token, r->row_w, m.E, eb->db2, stream),
-            "expert-bias gradient db2");
+  if (eb && (eb->db1 || eb->db2))
+    HIP_TRY(smoe::launch_expert_colsum({w.dH, dO, r->offsets, r->row_token, r->row_w, w.mtiles, w.colsum_part, eb->db1,
+                                        eb->db2, m.d, m.n, m.E, r->capacity},
+                                       stream),
+            "expert-bias gradients db1, db2");
   return MOE_OK;
 }
 

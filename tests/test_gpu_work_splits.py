@@ -1,0 +1,23 @@
+"""Parity of the layer with the oracle at the sizes where the kernels' work
+splits change: the edges of tiles and chunks, remainders, the smallest and the
+largest sizes of a variant's range.  Tolerances as in test_gpu_parity."""
+import numpy as np
+import pytest
+
+from paper_2512_14080_amd import workloads as W
+from test_gpu_parity import check_layer, expert_biases
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,shift", [(300, -40.0), (520, 0.0), (1400, 1.5)])
+def test_expert_bias_gradients_over_row_tiles(T, shift):
+    """db1 and db2 are summed per 256-row tile and then over an expert's tiles:
+    experts without rows, with one partial tile, with full tiles only (one
+    expert takes every token; T = 512 of them make two full tiles) and with
+    both.  Column counts off the 512-column chunks."""
+    cfg = W.MoEConfig("colsum", T=T, d=640, n=192, E=8, K=2, m_tile=64)
+    bias = np.array([0, 0.3, shift, 0.6, 40.0, 0, -0.5, 1.0], np.float32)
+    T = 512 if T == 520 else T
+    layer, R = check_layer(cfg, seed=31, T=T, bias=bias, eb=expert_biases(cfg, 31))
+    assert R.counts[4] == T and (shift > -40 or R.counts[2] == 0)
