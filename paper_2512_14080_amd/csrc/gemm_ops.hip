@@ -139,8 +139,15 @@ hipError_t launch_mtiles(const int32_t* offsets, int E, int32_t* out, hipStream_
 // The weight gradients reduce over an expert's rows (varlen K).  With skewed
 // routing a few experts own most rows, and their tiles would run for the
 // whole kernel on a handful of CUs.  The k-chunk list cuts every expert with
-// more than Kc rows into Kc-row chunks (Kc = max(kKcMin, 2P / slabs), so the
-// chunks need at most `slabs` fp32 partial slabs); a split expert's chunks
+// more than max(Kc, whole) rows into Kc-row chunks (Kc = max(kKcMin, 2P /
+// slabs)), which need at most 2P / Kc <= slabs fp32 partial slabs.  `whole` is
+// 5/4 of the mean rows of an expert where the unsplit experts' tiles fill the
+// CUs' rounds well (kchunk_keep_whole), else 0: experts of about equal length
+// balance by themselves, and a split writes and sums two fp32 slabs (at T =
+// 16384, d = 1024, n = 256, E = 64, K = 8 half of the experts are a few rows
+// over 2048: the step takes 1.013 instead of 1.106 ms since they are left
+// whole; a margin of 5/4 Kc without the mean made the T = 32768, E = 256 layer
+// with Zipf-distributed experts 1% slower).  A split expert's chunks
 // write fp32 partials that dw_reduce_kernel sums in chunk order, the others
 // store bf16 directly.  The entries (chunks and unsplit experts) are sorted
 // by length, longest first (a counting sort on k steps), and dealt round-robin
@@ -159,7 +166,7 @@ size_t kchunks_bytes(int E) { return 4 * (16 + 8 * (size_t)(E + kDwSlabs) + 4 * 
 __host__ __device__ inline int kchunks_split_off(int E) { return 16 + 8 * (E + kDwSlabs); }
 
 // bins: LDS [kLenBins]
-__device__ __forceinline__ void kchunks_body(const int32_t* __restrict__ offsets, int E, int tpe, int slabs,
+__device__ __forceinline__ void kchunks_body(const int32_t* __restrict__ offsets, int E, int tpe, int slabs, int keep,
                                              int32_t* __restrict__ out, int* bins, int* scan_lds, int* sh_kc) {
   static_assert(kLenBins == kKChunksThreads, "one bin per thread");
   const int tid = threadIdx.x;
@@ -175,13 +182,14 @@ __device__ __forceinline__ void kchunks_body(const int32_t* __restrict__ offsets
   bins[tid] = 0;
   __syncthreads();
   const int Kc = *sh_kc;
+  const int uncut = keep ? max((int64_t)Kc, (int64_t)offsets[E] * 5 / (4 * E)) : Kc;  // rows of the longest unsplit expert
   // thread t owns experts 4t .. 4t+3 (E <= 4096)
   int f[4], nc[4], sc = 0, su = 0, sx = 0;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int e = 4 * tid + q;
     f[q] = e < E ? offsets[e + 1] - offsets[e] : 0;
-    nc[q] = (e < E && f[q] > Kc) ? (f[q] + Kc - 1) / Kc : 0;  // chunks of a split expert
+    nc[q] = (e < E && f[q] > uncut) ? (f[q] - 1) / Kc + 1 : 0;  // chunks of a split expert
     sc += nc[q];
     su += (e < E && nc[q] == 0);
     sx += nc[q] > 0;
@@ -246,8 +254,8 @@ __device__ __forceinline__ void kchunks_body(const int32_t* __restrict__ offsets
 // 1 and 2 the k-chunk lists of dW2 and dW1.
 static_assert(kMTilesThreads == kKChunksThreads, "one workgroup size");
 __global__ __launch_bounds__(kMTilesThreads) void bwd_lists_kernel(const int32_t* __restrict__ offsets, int E,
-                                                                  int32_t* __restrict__ mtiles, int tpe2, int slabs2,
-                                                                  int32_t* __restrict__ klist2, int tpe1, int slabs1,
+                                                                  int32_t* __restrict__ mtiles, int tpe2, int slabs2, int keep2,
+                                                                  int32_t* __restrict__ klist2, int tpe1, int slabs1, int keep1,
                                                                   int32_t* __restrict__ klist1,
                                                                   const uint16_t* __restrict__ Wr,
                                                                   uint16_t* __restrict__ WrT, int d) {
@@ -257,9 +265,9 @@ __global__ __launch_bounds__(kMTilesThreads) void bwd_lists_kernel(const int32_t
   if (blockIdx.x == 0) {
     mtiles_body(offsets, E, mtiles, lds, lds + 4097, scan_lds);
   } else if (blockIdx.x == 1) {
-    kchunks_body(offsets, E, tpe2, slabs2, klist2, lds, scan_lds, &sh_kc);
+    kchunks_body(offsets, E, tpe2, slabs2, keep2, klist2, lds, scan_lds, &sh_kc);
   } else if (blockIdx.x == 2) {
-    kchunks_body(offsets, E, tpe1, slabs1, klist1, lds, scan_lds, &sh_kc);
+    kchunks_body(offsets, E, tpe1, slabs1, keep1, klist1, lds, scan_lds, &sh_kc);
   } else {  // W_r transpose, one element per thread
     const int idx = (blockIdx.x - 3) * kMTilesThreads + threadIdx.x;
     if (idx < d * E) {
@@ -1621,6 +1629,12 @@ static void dw1_tile(int d, int n, int* bm, int* bn) {
   *bm = *bn = (d % 256 == 0 && (2 * n) % 256 == 0) ? 256 : 128;
 }
 
+// whether E experts of tpe tiles each fill whole rounds of the CUs to 3/4
+static int kchunk_keep_whole(int E, int tpe) {
+  const int64_t tiles = (int64_t)E * tpe, cus = cu_count(), rounds = (tiles + cus - 1) / cus;
+  return 4 * tiles >= 3 * rounds * cus;
+}
+
 hipError_t launch_bwd_lists(const int32_t* offsets, int E, int d, int n, int32_t* mtiles, int32_t* klist2,
                             int32_t* klist1, const uint16_t* Wr, uint16_t* WrT, hipStream_t s) {
   if (E > 4096) return hipErrorInvalidValue;
@@ -1629,8 +1643,10 @@ hipError_t launch_bwd_lists(const int32_t* offsets, int E, int d, int n, int32_t
   dw1_tile(d, n, &bm1, &bn1);
   const int tpe2 = (n / bm2) * (d / bn2), tpe1 = (d / bm1) * (2 * n / bn1);
   const int tr_blocks = Wr ? (d * E + kMTilesThreads - 1) / kMTilesThreads : 0;
-  bwd_lists_kernel<<<3 + tr_blocks, kMTilesThreads, 0, s>>>(offsets, E, mtiles, tpe2, dw_slabs((int64_t)n * d), klist2,
-                                                           tpe1, dw_slabs((int64_t)d * 2 * n), klist1, Wr, WrT, d);
+  bwd_lists_kernel<<<3 + tr_blocks, kMTilesThreads, 0, s>>>(offsets, E, mtiles, tpe2, dw_slabs((int64_t)n * d),
+                                                           kchunk_keep_whole(E, tpe2), klist2, tpe1,
+                                                           dw_slabs((int64_t)d * 2 * n), kchunk_keep_whole(E, tpe1),
+                                                           klist1, Wr, WrT, d);
   return hipGetLastError();
 }
 

@@ -21,3 +21,12 @@ def test_expert_bias_gradients_over_row_tiles(T, shift):
     T = 512 if T == 520 else T
     layer, R = check_layer(cfg, seed=31, T=T, bias=bias, eb=expert_biases(cfg, 31))
     assert R.counts[4] == T and (shift > -40 or R.counts[2] == 0)
+
+
+def test_weight_gradients_of_equal_experts():
+    """Experts of equal length a little over the 2048-row chunk: dW1 (256
+    tiles, whole rounds of the CUs) leaves them whole, dW2 (128 tiles) cuts
+    each into 2048 rows and a 64-row remainder."""
+    cfg = W.MoEConfig("equal", T=2112, d=4096, n=256, E=8, K=8, m_tile=128)
+    layer, R = check_layer(cfg, seed=32)
+    assert (R.counts == 2112).all()
