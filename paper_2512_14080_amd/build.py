@@ -16,7 +16,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsonicmoe.so")
-SOURCES = ["moe_abi.cpp", "route_kernels.hip", "round_kernels.hip", "gemm_ops.hip", "aggregate.hip"]
+SOURCES = ["moe_abi.cpp", "route_kernels.hip", "round_kernels.hip", "gemm_ops.hip", "stream_gemm.hip", "aggregate.hip"]
 ARCH = "gfx950"
 
 

@@ -32,6 +32,15 @@ __device__ __forceinline__ uint32_t pack_bf2(float lo, float hi) {
 }
 // logistic sigmoid with the hardware exp and reciprocal (about 1 ulp each)
 __device__ __forceinline__ float fast_sigmoid(float x) { return __builtin_amdgcn_rcpf(1.f + __expf(-x)); }
+// silu(g) = g * sigmoid(g), and the sigmoid
+__device__ __forceinline__ float silu_sig(float g, float* sig) {
+  const float s = fast_sigmoid(g);
+  *sig = s;
+  return g * s;
+}
+__device__ __forceinline__ u32x2 pack_bf16x4(float a, float b, float c, float d) {
+  return u32x2{pack_bf2(a, b), pack_bf2(c, d)};
+}
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (kWave - 1); }
 

@@ -17,13 +17,6 @@
 
 namespace smoe {
 
-__device__ __forceinline__ float silu_sig(float g, float* sig) {
-  const float s = fast_sigmoid(g);
-  *sig = s;
-  return g * s;
-}
-
-
 // One 32-column accumulator block of a row, as bf16: v[g] holds columns
 // 8g + 4*(lane/32) + [0, 4) (the MFMA output layout).  One lane-pair swap per
 // dword (v_permlane32_swap exchanges the upper half of its first operand with
@@ -53,11 +46,6 @@ __device__ __forceinline__ void load_block_bf16(const uint16_t* row_block, u32x2
     v[g + 1] = u32x2{a[1], b[1]};
   }
 }
-
-__device__ __forceinline__ u32x2 pack_bf16x4(float a, float b, float c, float d) {
-  return u32x2{pack_bf2(a, b), pack_bf2(c, d)};
-}
-
 
 // ---------------------------------------------------------------- scheduling
 // ---------------------------------------------------------------- m-tile list

@@ -59,9 +59,17 @@ struct DownArgs {
   const float* row_w = nullptr;
 };
 hipError_t launch_down(const DownArgs& a, hipStream_t s);
-// strategy 0: as launch_down; 1: Y rows scattered to a.dst[row]; 2: fp32
-// atomic accumulation of s * Y into a.O32 (no Y stored)
+// MOE_AGG_* strategy 0: as launch_down; 1: Y rows scattered to a.dst[row]; 2:
+// fp32 atomic accumulation of s * Y into a.O32 (no Y stored)
 hipError_t launch_down_ablation(const DownArgs& a, int strategy, hipStream_t s);
+
+// The same for few rows per expert (stream_gemm.hip).  stream_row_blocks: the
+// row blocks per workgroup for `rows` routed rows over E experts, or 0 where
+// the tiled GEMMs above (tiles_per_expert tiles of an expert with up to 256
+// rows) are the better ones.
+int stream_row_blocks(int64_t rows, int E, int64_t tiles_per_expert);
+hipError_t launch_stream_up(const UpArgs& a, int mb, int T, hipStream_t s);
+hipError_t launch_stream_down(const DownArgs& a, int strategy, int mb, int T, hipStream_t s);  // MOE_AGG_*
 
 struct DHArgs {
   const uint16_t* dO; const uint16_t* W2; const uint16_t* H; const int32_t* offsets; const int32_t* row_token;

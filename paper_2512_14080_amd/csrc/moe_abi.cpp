@@ -245,6 +245,24 @@ size_t routing_layout(const moe_dims& m, int64_t cap, int flags, char* base, moe
   return off;
 }
 
+// the projections, streaming (few rows per expert) or tiled
+struct Projections {
+  int up, down, T;  // row blocks per streaming workgroup; 0: tiled
+  explicit Projections(const moe_dims& m)
+      : up(smoe::stream_row_blocks((int64_t)m.T * m.K, m.E, (2 * m.n + 255) / 256)),
+        down(smoe::stream_row_blocks((int64_t)m.T * m.K, m.E, (m.d + 255) / 256)),
+        T(m.T) {}
+  hipError_t lists(const int32_t* offsets, int E, int32_t* mtiles, hipStream_t s) const {
+    return up && down ? hipSuccess : smoe::launch_mtiles(offsets, E, mtiles, s);
+  }
+  hipError_t run_up(const smoe::UpArgs& a, hipStream_t s) const {
+    return up ? smoe::launch_stream_up(a, up, T, s) : smoe::launch_up(a, s);
+  }
+  hipError_t run_down(const smoe::DownArgs& a, int strategy, hipStream_t s) const {
+    return down ? smoe::launch_stream_down(a, strategy, down, T, s) : smoe::launch_down_ablation(a, strategy, s);
+  }
+};
+
 #define HIP_TRY(expr, where)                          \
   do {                                                \
     hipError_t _e = (expr);                           \
@@ -448,12 +466,12 @@ int moe_fwd(moe_dims m, const moe_bf16* X, const moe_bf16* W1, const moe_bf16* W
   FwdWs w;
   fwd_layout(m, r->capacity, (char*)ws, &w);
   hipStream_t stream = (hipStream_t)stream_;
-  HIP_TRY(smoe::launch_mtiles(r->offsets, m.E, w.mtiles, stream), "m-tile list");
-  LAUNCH(MOE_KC_UP,
-         smoe::launch_up({X, W1, r->offsets, r->row_token, H, w.A, m.d, m.n, m.E, r->capacity, w.mtiles, b1}, stream),
-         "up-proj");
-  LAUNCH(MOE_KC_DOWN, smoe::launch_down({w.A, W2, r->offsets, w.Y, m.d, m.n, m.E, r->capacity, w.mtiles, b2}, stream),
-         "down-proj");
+  const smoe::UpArgs up{X, W1, r->offsets, r->row_token, H, w.A, m.d, m.n, m.E, r->capacity, w.mtiles, b1};
+  const smoe::DownArgs down{w.A, W2, r->offsets, w.Y, m.d, m.n, m.E, r->capacity, w.mtiles, b2};
+  const Projections proj(m);
+  HIP_TRY(proj.lists(r->offsets, m.E, w.mtiles, stream), "m-tile list");
+  LAUNCH(MOE_KC_UP, proj.run_up(up, stream), "up-proj");
+  LAUNCH(MOE_KC_DOWN, proj.run_down(down, MOE_AGG_GATHER_SUM, stream), "down-proj");
   LAUNCH(MOE_KC_AGG_O, smoe::launch_agg_o(w.Y, *r, O, m.T, m.d, stream), "aggregation");
   return MOE_OK;
 }
@@ -502,21 +520,21 @@ int moe_fwd_aggregation_ablation(moe_dims m, const moe_bf16* X, const moe_bf16* 
   FwdWs w;
   abl_layout(m, r->capacity, (char*)ws, &w, &dst, &o32);
   hipStream_t stream = (hipStream_t)stream_;
-  HIP_TRY(smoe::launch_mtiles(r->offsets, m.E, w.mtiles, stream), "m-tile list");
+  const Projections proj(m);
+  HIP_TRY(proj.lists(r->offsets, m.E, w.mtiles, stream), "m-tile list");
   LAUNCH(MOE_KC_UP,
-         smoe::launch_up({X, W1, r->offsets, r->row_token, H, w.A, m.d, m.n, m.E, r->capacity, w.mtiles, nullptr},
-                         stream),
+         proj.run_up({X, W1, r->offsets, r->row_token, H, w.A, m.d, m.n, m.E, r->capacity, w.mtiles, nullptr}, stream),
          "up-proj");
   smoe::DownArgs da{w.A, W2, r->offsets, w.Y, m.d, m.n, m.E, r->capacity, w.mtiles, nullptr};
   if (strategy == MOE_AGG_GATHER_SUM) {
-    LAUNCH(MOE_KC_DOWN, smoe::launch_down(da, stream), "down-proj");
+    LAUNCH(MOE_KC_DOWN, proj.run_down(da, strategy, stream), "down-proj");
     LAUNCH(MOE_KC_AGG_O, smoe::launch_agg_o(w.Y, *r, O, m.T, m.d, stream), "aggregation");
   } else if (strategy == MOE_AGG_SCATTER_SUM) {
     da.dst = dst;
     LAUNCH(MOE_KC_DOWN,
            [&]() {
              hipError_t e = smoe::launch_tok_slots(*r, m.T, r->capacity, dst, stream);
-             return e == hipSuccess ? smoe::launch_down_ablation(da, 1, stream) : e;
+             return e == hipSuccess ? proj.run_down(da, strategy, stream) : e;
            }(),
            "down-proj (scatter)");
     LAUNCH(MOE_KC_AGG_O, smoe::launch_agg_o_contig(w.Y, *r, O, m.T, m.d, stream), "contiguous sum");
@@ -528,7 +546,7 @@ int moe_fwd_aggregation_ablation(moe_dims m, const moe_bf16* X, const moe_bf16* 
     LAUNCH(MOE_KC_DOWN,
            [&]() {
              hipError_t e = smoe::launch_fill_f32(o32, td, stream);
-             return e == hipSuccess ? smoe::launch_down_ablation(da, 2, stream) : e;
+             return e == hipSuccess ? proj.run_down(da, strategy, stream) : e;
            }(),
            "down-proj (fp32 atomics)");
     LAUNCH(MOE_KC_AGG_O, smoe::launch_f32_to_bf16(o32, O, td, stream), "fp32 -> bf16");

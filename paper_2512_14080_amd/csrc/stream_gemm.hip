@@ -1,0 +1,254 @@
+// Grouped GEMMs over few rows per expert (decode and short prefill calls).
+//
+// With a handful of rows per expert the layer is bound by reading the expert
+// weights once; the 256 x 256 tiles of gemm_core.h then run one latency-bound
+// k loop per CU (T = 1, d = 1536, n = 256, E = 128, K = 8: 16 workgroups of 24
+// dependent 64-deep steps, 26 us for 12.6 MB), and their M side stages 256 rows
+// for the few that exist.  Here the weights stream straight into registers, and
+// nothing but the final sum is shared between waves:
+//   - A workgroup computes 128 columns of one expert for 16 MB rows; its KW
+//     waves split the reduction (wave w takes steps w, w + KW, ... of 32 k), so
+//     every wave is an independent stream of loads without barriers, and even
+//     one row's weights are requested by many waves at once.
+//   - Weights with k outer in memory (W1 and W2 in the forward): a lane loads
+//     16 bytes (8 columns) of 8 consecutive k rows, whole 128- or 256-byte runs
+//     per row, and transposes its 8 x 8 block with 32 v_perm_b32.  MFMA j
+//     (16x16x32) then takes column 8 l + j of lane l: the columns of one MFMA
+//     are 8 apart, which only permutes the accumulators, so a lane ends with
+//     eight consecutive columns of four rows.
+//   - The rows (k contiguous) are MFMA fragments as they lie in memory: 16
+//     bytes per lane of a gathered row, no LDS.
+//   - NBUF steps of loads are in flight per wave (8 KB of weights each).
+//   - At the end the waves' accumulators meet in LDS, 16 rows at a time, and are
+//     added in wave order by the epilogue.
+#include <algorithm>
+
+#include "device_common.h"
+#include "launch.h"
+
+namespace smoe {
+
+// 8 rows (k) x 8 columns of bf16, one row per register quad -> per column the
+// 8 k values (an MFMA operand)
+__device__ __forceinline__ bf16x8 column_of(const u32x4 (&w)[8], int j) {
+  const uint32_t sel = (j & 1) ? 0x07060302u : 0x05040100u;
+  u32x4 f;
+#pragma unroll
+  for (int p = 0; p < 4; ++p) f[p] = __builtin_amdgcn_perm(w[2 * p + 1][j >> 1], w[2 * p][j >> 1], sel);
+  return __builtin_bit_cast(bf16x8, f);
+}
+
+constexpr int kStreamCols = 128;  // columns of a workgroup
+typedef f32x4 StreamPart[16][2][16];  // one wave's 16 x 128 partial: [row][half of 8 columns][lane column]
+
+// the sum over the waves of four consecutive columns, 4 c4 .. 4 c4 + 3 of the tile
+template <int KW>
+__device__ __forceinline__ f32x4 stream_sum(const StreamPart* part, int row, int c4) {
+  f32x4 s = part[0][row][c4 & 1][c4 >> 1];
+#pragma unroll
+  for (int w = 1; w < KW; ++w) {
+    const f32x4 v = part[w][row][c4 & 1][c4 >> 1];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) s[q] += v[q];
+  }
+  return s;
+}
+
+// grid: x column tiles, y experts, z row groups (an expert's groups of 16 MB
+// rows are dealt to the z workgroups).  Op supplies
+//   int k(p), const uint16_t* x_row(p, e, row) (k contiguous),
+//   const uint16_t* w(p, e) with leading dimension ldw(p),
+//   int col(p, tile, l): first of the eight columns of lane column l
+//   template <int KW> void finish(p, e, tile, row0, rows, part): 16 rows
+template <class Op, int MB, int KW, int NBUF, int OCC>
+__global__ __launch_bounds__(64 * KW, OCC) void stream_gemm_kernel(const typename Op::Params p) {
+  __shared__ StreamPart part[KW];
+  const int e = blockIdx.y, tile = blockIdx.x;
+  const int off = p.offsets[e], cnt = p.offsets[e + 1] - off;
+  const int lane = lane_id(), g = lane >> 4, l = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int ns = (Op::k(p) / 32 - wave + KW - 1) / KW;  // this wave's steps
+  const uint16_t* wbase = Op::w(p, e);
+  const uint32_t ldw = Op::ldw(p);
+  const uint32_t wcol = Op::col(p, tile, l);
+  for (int m0 = blockIdx.z * 16 * MB; m0 < cnt; m0 += gridDim.z * 16 * MB) {
+    const uint16_t* xp[MB];
+#pragma unroll
+    for (int b = 0; b < MB; ++b) xp[b] = Op::x_row(p, off + min(m0 + 16 * b + l, cnt - 1)) + 8 * g;
+    f32x4 acc[MB][8];
+#pragma unroll
+    for (int b = 0; b < MB; ++b)
+#pragma unroll
+      for (int j = 0; j < 8; ++j) acc[b][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    u32x4 wv[NBUF][8];
+    bf16x8 xv[NBUF][MB];
+    // step s of this wave; a step past the end reads the step 0 addresses (cached, unused)
+    auto load = [&](int buf, int s) {
+      const uint32_t k = s < ns ? 32 * (wave + KW * s) : 32 * wave;
+      const uint32_t o = (k + 8 * g) * ldw + wcol;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) wv[buf][i] = *(const u32x4*)(wbase + (size_t)(o + i * ldw));
+#pragma unroll
+      for (int b = 0; b < MB; ++b) xv[buf][b] = *(const bf16x8*)(xp[b] + k);
+    };
+    if (ns > 0) {
+#pragma unroll
+      for (int q = 0; q < NBUF; ++q) load(q, q);
+      for (int s = 0;; s += NBUF) {
+#pragma unroll
+        for (int q = 0; q < NBUF; ++q) {
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const bf16x8 wf = column_of(wv[q], j);
+#pragma unroll
+            for (int b = 0; b < MB; ++b)
+              acc[b][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[q][b], wf, acc[b][j], 0, 0, 0);
+          }
+          if (s + q + 1 >= ns) goto done;
+          load(q, s + q + NBUF);
+        }
+      }
+    done:;
+    }
+#pragma unroll
+    for (int b = 0; b < MB; ++b) {
+      if (m0 + 16 * b >= cnt) break;
+      __syncthreads();  // the previous rows' sums have been read
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          part[wave][4 * g + r][h][l] =
+              f32x4{acc[b][4 * h][r], acc[b][4 * h + 1][r], acc[b][4 * h + 2][r], acc[b][4 * h + 3][r]};
+      __syncthreads();
+      Op::template finish<KW>(p, e, tile, off + m0 + 16 * b, min(16, cnt - m0 - 16 * b), part);
+    }
+  }
+}
+
+// H = gather(X) W1_e (+ b1_e), A = SwiGLU(H): 64 gate columns (lane columns
+// 0..7) and the matching up columns (8..15)
+struct StreamUp {
+  using Params = UpArgs;
+  static __host__ __device__ int k(const Params& p) { return p.d; }
+  static __device__ const uint16_t* x_row(const Params& p, int row) { return p.X + (size_t)p.row_token[row] * p.d; }
+  static __device__ const uint16_t* w(const Params& p, int e) { return p.W1 + (size_t)e * p.d * (2 * p.n); }
+  static __device__ uint32_t ldw(const Params& p) { return 2 * p.n; }
+  static __device__ uint32_t col(const Params& p, int tile, int l) {
+    return (l < 8 ? 0 : p.n) + 64 * tile + 8 * (l & 7);
+  }
+  template <int KW>
+  static __device__ void finish(const Params& p, int e, int tile, int row0, int rows, const StreamPart* part) {
+    for (int i = threadIdx.x; i < 256; i += 64 * KW) {
+      const int row = i >> 4, c4 = i & 15;
+      if (row >= rows) break;
+      f32x4 hg = stream_sum<KW>(part, row, c4), hu = stream_sum<KW>(part, row, c4 + 16);
+      const int c = 64 * tile + 4 * c4;
+      if (p.b1) {
+        const float* b = p.b1 + (size_t)e * 2 * p.n + c;
+        const f32x4 bg = *(const f32x4*)b, bu = *(const f32x4*)(b + p.n);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          hg[q] += bg[q];
+          hu[q] += bu[q];
+        }
+      }
+      float a[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        float sg;
+        a[q] = silu_sig(hg[q], &sg) * hu[q];
+      }
+      uint16_t* h = p.H + (size_t)(row0 + row) * (2 * p.n) + c;
+      *(u32x2*)h = pack_bf16x4(hg[0], hg[1], hg[2], hg[3]);
+      *(u32x2*)(h + p.n) = pack_bf16x4(hu[0], hu[1], hu[2], hu[3]);
+      *(u32x2*)(p.A + (size_t)(row0 + row) * p.n + c) = pack_bf16x4(a[0], a[1], a[2], a[3]);
+    }
+  }
+};
+
+// Y = A W2_e (+ b2_e); AGG: how Y leaves (0: Y rows expert-major; 1 and 2: the
+// aggregation ablation's scatter to p.dst[row] and fp32 atomics, as OpDown)
+template <int AGG>
+struct StreamDown {
+  using Params = DownArgs;
+  static __host__ __device__ int k(const Params& p) { return p.n; }
+  static __device__ const uint16_t* x_row(const Params& p, int row) { return p.A + (size_t)row * p.n; }
+  static __device__ const uint16_t* w(const Params& p, int e) { return p.W2 + (size_t)e * p.n * p.d; }
+  static __device__ uint32_t ldw(const Params& p) { return p.d; }
+  static __device__ uint32_t col(const Params& p, int tile, int l) { return kStreamCols * tile + 8 * l; }
+  template <int KW>
+  static __device__ void finish(const Params& p, int e, int tile, int row0, int rows, const StreamPart* part) {
+    for (int i = threadIdx.x; i < 512; i += 64 * KW) {
+      const int row = i >> 5, c4 = i & 31;
+      if (row >= rows) break;
+      f32x4 y = stream_sum<KW>(part, row, c4);
+      const int c = kStreamCols * tile + 4 * c4;
+      if (p.b2) {
+        const f32x4 b = *(const f32x4*)(p.b2 + (size_t)e * p.d + c);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) y[q] += b[q];
+      }
+      const u32x2 v = pack_bf16x4(y[0], y[1], y[2], y[3]);
+      const int r = row0 + row;
+      if constexpr (AGG == 2) {
+        float* o = p.O32 + (size_t)p.row_token[r] * p.d + c;
+        const float s = p.row_w[r];
+        unsafeAtomicAdd(o, s * bf_lo(v[0]));
+        unsafeAtomicAdd(o + 1, s * bf_hi(v[0]));
+        unsafeAtomicAdd(o + 2, s * bf_lo(v[1]));
+        unsafeAtomicAdd(o + 3, s * bf_hi(v[1]));
+      } else {
+        *(u32x2*)(p.Y + (size_t)(AGG == 1 ? p.dst[r] : r) * p.d + c) = v;
+      }
+    }
+  }
+};
+
+// Row blocks per workgroup (us of up-proj / down-proj, streaming against tiled):
+//   T = 1, d = 1536, n = 256, E = 128, K = 8           mean <= 1   9 / 4.5    26 / 7
+//   T = 64, d = 4096, n = 512, E = 128, K = 8          mean 4      208 / 97   218 / 108
+//   T = 128, d = 768, n = 256, E = 32, K = 4           mean 16     9.2 / 6.1  17 / 7.6
+//   T = 256, d = 4096, n = 512, E = 128, K = 8         mean 16     219 / 108  223 / 110
+//   T = 512, the same                                  mean 32     230 / 118  226 / 112
+//   T = 256, d = 1536, n = 1024, E = 16, K = 2         mean 32     29 / 18    41 / 25
+//   T = 512, d = 1024, n = 256, E = 64, K = 8          mean 64     25 / 18    30 / 12.6
+// Up to about 20 rows the weights bind and streaming is never behind.  Beyond,
+// its four row blocks cost registers and row loads, and it only wins where the
+// tiled GEMM has too few tiles for the CUs (the fifth and sixth lines: 128 and 96
+// tiles up and down; 128 against 256 in the last).
+int stream_row_blocks(int64_t rows, int E, int64_t tiles_per_expert) {
+  const int64_t mean = (rows + E - 1) / E;
+  if (mean <= 10) return 1;
+  if (mean <= 20) return 2;
+  return mean <= 64 && E * tiles_per_expert < 192 ? 4 : 0;
+}
+
+template <class Op>
+static hipError_t run_stream(const typename Op::Params& p, int tiles, int mb, int T, hipStream_t s) {
+  // groups of one expert that run at once; more are looped over
+  const dim3 grid(tiles, p.E, std::min((T + 16 * mb - 1) / (16 * mb), 8));
+  // waves and loads in flight: the widest split of k that keeps two or more
+  // steps per wave, within the registers (no spills)
+  if (mb == 1 && Op::k(p) >= 768)
+    stream_gemm_kernel<Op, 1, 8, 3, 2><<<grid, dim3(512), 0, s>>>(p);
+  else if (mb == 1)
+    stream_gemm_kernel<Op, 1, 8, 2, 4><<<grid, dim3(512), 0, s>>>(p);
+  else if (mb == 2)
+    stream_gemm_kernel<Op, 2, 4, 2, 2><<<grid, dim3(256), 0, s>>>(p);
+  else
+    stream_gemm_kernel<Op, 4, 4, 1, 2><<<grid, dim3(256), 0, s>>>(p);
+  return hipGetLastError();
+}
+
+hipError_t launch_stream_up(const UpArgs& a, int mb, int T, hipStream_t s) {
+  return run_stream<StreamUp>(a, a.n / 64, mb, T, s);
+}
+hipError_t launch_stream_down(const DownArgs& a, int strategy, int mb, int T, hipStream_t s) {
+  const int tiles = a.d / kStreamCols;
+  if (strategy == MOE_AGG_SCATTER_SUM) return run_stream<StreamDown<1>>(a, tiles, mb, T, s);
+  if (strategy == MOE_AGG_ATOMIC_F32) return run_stream<StreamDown<2>>(a, tiles, mb, T, s);
+  return run_stream<StreamDown<0>>(a, tiles, mb, T, s);
+}
+
+}  // namespace smoe

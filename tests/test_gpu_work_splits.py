@@ -30,3 +30,24 @@ def test_weight_gradients_of_equal_experts():
     cfg = W.MoEConfig("equal", T=2112, d=4096, n=256, E=8, K=8, m_tile=128)
     layer, R = check_layer(cfg, seed=32)
     assert (R.counts == 2112).all()
+
+
+@pytest.mark.parametrize("T,d,n,E,K,zipf", [
+    (1, 128, 64, 8, 1, 0.0),      # one row; fewer k steps (n: 2, d: 4) than waves
+    (3, 384, 192, 40, 3, 0.0),    # one row block, the last of the k splits uneven
+    (10, 896, 320, 8, 8, 0.0),    # one row block at its largest mean (10 rows an expert), K = E
+    (11, 768, 256, 8, 8, 0.0),    # two row blocks
+    (20, 256, 128, 16, 16, 0.0),  # two row blocks at their largest mean (20)
+    (21, 256, 128, 16, 16, 0.0),  # four row blocks
+    (128, 640, 192, 8, 4, 0.0),   # four at their largest mean (64), rows past one group
+    (129, 640, 192, 8, 4, 0.0),   # the tiled GEMMs
+    (150, 256, 64, 120, 8, 1.5),  # skewed: empty experts, and experts with many groups of 16 rows
+])
+@pytest.mark.parametrize("biased", [False, True])
+def test_few_rows_per_expert(T, d, n, E, K, zipf, biased):
+    """The streaming projections (few rows per expert) on both sides of their
+    row-block rules, with and without expert biases."""
+    cfg = W.MoEConfig("few", T=T, d=d, n=n, E=E, K=K, m_tile=16, zipf_s=zipf)
+    layer, R = check_layer(cfg, seed=33, eb=expert_biases(cfg, 33) if biased else None)
+    if zipf:
+        assert R.counts.max() > 128 and R.counts.min() == 0
