@@ -36,6 +36,27 @@ struct RouterTopkArgs {
 bool router_topk_fusable(int E, int K);
 hipError_t launch_router_topk(const RouterTopkArgs& a, hipStream_t s);
 
+// Routing of few tokens (T <= kFewTokens, E <= kFewExperts): the router GEMM's
+// partial logits of `slices` k slices [slices][T][E], then a wave per token for
+// softmax and top-K, then (T > kFewOneGroup) one launch of metadata.
+constexpr int kFewTokens = 4096, kFewExperts = 1024;
+constexpr int kFewOneGroup = 16;  // tokens whose top-K and metadata are one launch
+inline bool route_few(int T, int E) { return T <= kFewTokens && E <= kFewExperts; }
+struct RouterPartArgs {
+  const uint16_t* X; const uint16_t* Wr; float* part; int T, d, E, slice;
+};
+// slices for part_bytes of partials (1 where two do not fit: the partial logits
+// then go to a [T][E] array)
+int router_slices(int T, int d, int E, size_t part_bytes);
+hipError_t launch_router_part(const uint16_t* X, const uint16_t* Wr, float* part, int slices, int T, int d, int E,
+                              hipStream_t s);
+// in: `slices` slabs of logits (bias added here) or, with do_softmax = 0, the
+// scores.  For T <= kFewOneGroup the launch also builds the metadata (counts_only as in
+// launch_tc_metadata).
+hipError_t launch_topk_few(const float* in, int slices, const float* bias, float* logits, float* scores_t,
+                           const moe_routing& r, int T, int E, int K, int do_softmax, bool counts_only, hipStream_t s);
+hipError_t launch_tc_metadata_few(const moe_routing& r, int T, int E, int K, bool counts_only, hipStream_t s);
+
 // The varlen-M m-tile list (mtiles_kernel): built from the expert offsets
 // once per forward / backward call, read by the up, down, dH and dX~ GEMMs.
 constexpr int kMTile = 256;  // rows of an m-tile

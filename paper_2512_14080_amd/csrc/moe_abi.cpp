@@ -380,6 +380,36 @@ int moe_route(moe_dims m, const moe_bf16* X, const moe_bf16* Wr, const float* bi
   hipStream_t stream = (hipStream_t)stream_;
   float* scores_t = (flags & MOE_ROUTE_WRITE_SCORES_T) ? r->scores_t : nullptr;
   const float* in = r->scores;
+  const bool counts_only = (flags & MOE_ROUTE_COUNTS_ONLY) != 0;
+  r->state = MOE_ROUTING_STATE_EMPTY;  // until the metadata launch is enqueued
+  if (smoe::route_few(m.T, m.E)) {
+    // few tokens: partial logits of the router's k slices in the routing's
+    // scratch (one slice: in r->scores, which the softmax then overwrites)
+    const bool fused = !scores_in && !(flags & MOE_ROUTE_SEPARATE_TOPK) && smoe::router_topk_fusable(m.E, m.K);
+    float* logits = !scores_in && (flags & MOE_ROUTE_WRITE_LOGITS) ? r->logits : nullptr;
+    const int slices = scores_in ? 1 : smoe::router_slices(m.T, m.d, m.E, smoe::round_scratch_bytes(m.T, m.E));
+    float* part = slices > 1 ? (float*)((char*)r->scratch + round_lists_offset(m)) : r->scores;
+    auto gemm = [&]() { return smoe::launch_router_part(X, Wr, part, slices, m.T, m.d, m.E, stream); };
+    auto topk = [&]() {
+      return smoe::launch_topk_few(part, slices, scores_in ? nullptr : bias, logits, scores_t, *r, m.T, m.E, m.K,
+                                   scores_in ? 0 : 1, counts_only, stream);
+    };
+    if (fused) {
+      LAUNCH(MOE_KC_ROUTER_TOPK,
+             [&]() {
+               const hipError_t e = gemm();
+               return e == hipSuccess ? topk() : e;
+             }(),
+             "router gemm with softmax/top-K");
+    } else {
+      if (!scores_in) LAUNCH(MOE_KC_ROUTER_GEMM, gemm(), "router gemm");
+      LAUNCH(MOE_KC_TOPK, topk(), "softmax/top-K");
+    }
+    if (m.T > smoe::kFewOneGroup)
+      LAUNCH(MOE_KC_META, smoe::launch_tc_metadata_few(*r, m.T, m.E, m.K, counts_only, stream), "routing metadata");
+    r->state = counts_only ? MOE_ROUTING_STATE_COUNTS : MOE_ROUTING_STATE_BUILT;
+    return MOE_OK;
+  }
   if (!scores_in && !(flags & MOE_ROUTE_SEPARATE_TOPK) && smoe::router_topk_fusable(m.E, m.K)) {
     float* logits = (flags & MOE_ROUTE_WRITE_LOGITS) ? r->logits : nullptr;
     smoe::RouterTopkArgs a{X, Wr, bias, logits, r->scores, scores_t, r->topk_idx, r->topk_w, r->mask,
@@ -397,8 +427,6 @@ int moe_route(moe_dims m, const moe_bf16* X, const moe_bf16* Wr, const float* bi
                                    r->words, scores_in ? 0 : 1, stream),
            "softmax/top-K");
   }
-  const bool counts_only = (flags & MOE_ROUTE_COUNTS_ONLY) != 0;
-  r->state = MOE_ROUTING_STATE_EMPTY;  // until the metadata launch is enqueued
   LAUNCH(MOE_KC_META, smoe::launch_tc_metadata(*r, m.T, m.E, m.K, counts_only, stream), "routing metadata");
   r->state = counts_only ? MOE_ROUTING_STATE_COUNTS : MOE_ROUTING_STATE_BUILT;
   return MOE_OK;

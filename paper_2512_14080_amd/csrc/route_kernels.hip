@@ -16,6 +16,128 @@
 
 namespace smoe {
 
+// The top K of one token, a wave per token (value j of lane l is expert 64 j +
+// l), ordered by (value desc, expert asc): put(k, e, w) is called once for each
+// of the K positions, by some lane, with w the value over the selected values'
+// sum (added in ascending expert order).
+//
+// EPL <= 16: a select over the bits of the 32-bit keys, most significant first,
+// on ballots.  The candidates with the bit set replace the candidates if they
+// are as many as still wanted, else they are selected and the others stay; it
+// stops once the candidates are exactly as many as wanted, after about half of
+// the bits.  Equal keys at the end go to the lowest experts (lowest j, then
+// lowest lane).  Scalar masks and counts, one vector compare per bit: K rounds
+// of a wave-wide arg-max (six dependent DPP steps each) took 5 us per token
+// with 16 waves on a CU, and the EPL > 16 form below, whose masks would not fit
+// the scalar registers, still does them.
+template <int EPL, class Put>
+__device__ __forceinline__ void wave_topk(const float (&v)[EPL], int E, int K, Put put) {
+  static_assert(EPL >= 1 && EPL <= 64, "the taken mask holds one bit per value of a lane");
+  const int lane = lane_id();
+  float denom = 0.f;
+  if constexpr (EPL <= 16) {
+    uint32_t key[EPL];
+    int rank[EPL];
+    uint64_t alive[EPL], sel[EPL];
+#pragma unroll
+    for (int j = 0; j < EPL; ++j) {
+      key[j] = topk_key(v[j]);
+      rank[j] = 0;
+      alive[j] = __ballot(lane + 64 * j < E);
+      sel[j] = 0;
+    }
+    int na = E, need = K;
+    for (int b = 31; b >= 0 && na > need; --b) {
+      const uint32_t bit = 1u << b;
+      uint64_t one[EPL];
+      int c = 0;
+#pragma unroll
+      for (int j = 0; j < EPL; ++j) {
+        one[j] = __ballot((key[j] & bit) != 0) & alive[j];
+        c += __popcll(one[j]);
+      }
+      const bool more = c >= need;
+#pragma unroll
+      for (int j = 0; j < EPL; ++j) {
+        sel[j] |= more ? 0ull : one[j];
+        alive[j] = more ? one[j] : alive[j] & ~one[j];
+      }
+      na = more ? c : na - c;
+      need = more ? need : need - c;
+    }
+    const bool ties = na > need;  // equal keys: the lowest experts
+#pragma unroll
+    for (int j = 0; j < EPL; ++j) {
+      uint64_t a = alive[j];
+      if (ties) {
+        for (int drop = __popcll(a) - need; drop > 0; --drop) a &= ~(1ull << (63 - __clzll(a)));
+        need -= __popcll(a);
+      }
+      sel[j] |= a;
+    }
+#pragma unroll
+    for (int j = 0; j < EPL; ++j) {
+      for (uint64_t m = sel[j]; m; m &= m - 1) {
+        const int l = __ffsll((unsigned long long)m) - 1;
+        denom += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[j]), l));
+        const uint32_t k = (uint32_t)__builtin_amdgcn_readlane((int)key[j], l);
+        const int e = 64 * j + l;
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) rank[i] += k > key[i] || (k == key[i] && e < lane + 64 * i);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < EPL; ++j)
+      if ((sel[j] >> lane) & 1ull) put(rank[j], lane + 64 * j, topk_value(key[j]) / denom);
+  } else {
+    uint64_t taken = 0;  // bit j: value j of this lane is selected
+    int sel_e[16];
+    float sel_v[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      sel_e[k] = 0;
+      sel_v[k] = 0.f;
+      if (k < K) {
+        uint32_t best = 0;
+        int bj = -1;  // j of this lane's best candidate (the lowest j on equal keys)
+#pragma unroll
+        for (int j = 0; j < EPL; ++j) {
+          const int e = lane + 64 * j;
+          if (e < E && !((taken >> j) & 1ull)) {
+            const uint32_t c = topk_key(v[j]);
+            if (bj < 0 || c > best) {
+              best = c;
+              bj = j;
+            }
+          }
+        }
+        const uint32_t m = dpp_reduce(bj >= 0 ? best : 0u, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
+        int be = 0x7fffffff;
+#pragma unroll
+        for (int j = 0; j < EPL; ++j) {
+          const uint64_t hit = __ballot(bj == j && best == m);
+          if (hit && be == 0x7fffffff) be = __ffsll((unsigned long long)hit) - 1 + 64 * j;
+        }
+        if (be != 0x7fffffff && (be & 63) == lane) taken |= 1ull << (be >> 6);
+        sel_e[k] = be;
+        sel_v[k] = topk_value(m);
+      }
+    }
+#pragma unroll
+    for (int j = 0; j < EPL; ++j) {
+      uint64_t sel = __ballot((taken >> j) & 1ull);
+      while (sel) {
+        const int l = __ffsll((unsigned long long)sel) - 1;
+        denom += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[j]), l));
+        sel &= sel - 1;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+      if (k < K && lane == k) put(k, sel_e[k], sel_v[k] / denom);
+  }
+}
+
 constexpr int kTopkWaves = 16;
 
 // Workgroup = 64 tokens (one membership word).  `in` and `scores` may alias
@@ -30,7 +152,6 @@ __global__ __launch_bounds__(1024) void topk_route_kernel(const float* in, float
                                                          int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
                                                          uint64_t* __restrict__ mask, int T, int E, int K, int W,
                                                          int do_softmax) {
-  static_assert(EPL >= 1 && EPL <= 64, "the taken mask holds one bit per value of a lane");
   extern __shared__ __attribute__((aligned(16))) char dyn[];
   unsigned long long* mword = (unsigned long long*)dyn;                  // [E]
   float* st = (float*)(dyn + ((E * 8 + 15) & ~15));                       // STASH: [E][kStashPitch]
@@ -92,67 +213,16 @@ __global__ __launch_bounds__(1024) void topk_route_kernel(const float* in, float
         }
       }
     }
-    // K rounds of wave arg-max over (value desc, expert asc): the wave maximum
-    // of the 32-bit keys (a DPP max), then the lowest expert holding it from
-    // ballots (expert 64j + l is value j of lane l: lowest j, then lowest lane)
-    uint64_t taken = 0;  // bit j: value j of this lane is selected (EPL <= 64)
-    int sel_e[16];
-    float sel_v[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      sel_e[k] = 0;
-      sel_v[k] = 0.f;
-      if (k < K) {
-        uint32_t best = 0;
-        int bj = -1;  // j of this lane's best candidate (the lowest j on equal keys)
-#pragma unroll
-        for (int j = 0; j < EPL; ++j) {
-          const int e = lane + 64 * j;
-          if (e < E && !((taken >> j) & 1ull)) {
-            const uint32_t c = topk_key(v[j]);
-            if (bj < 0 || c > best) {
-              best = c;
-              bj = j;
-            }
-          }
-        }
-        const uint32_t m = dpp_reduce(bj >= 0 ? best : 0u, [](uint32_t a, uint32_t b) { return a > b ? a : b; });
-        int be = 0x7fffffff;
-#pragma unroll
-        for (int j = 0; j < EPL; ++j) {
-          const uint64_t hit = __ballot(bj == j && best == m);
-          if (hit && be == 0x7fffffff) be = __ffsll((unsigned long long)hit) - 1 + 64 * j;
-        }
-        if (be != 0x7fffffff && (be & 63) == lane) taken |= 1ull << (be >> 6);
-        sel_e[k] = be;
-        sel_v[k] = topk_value(m);
+    wave_topk<EPL>(v, E, K, [&](int k, int e, float wt) {
+      if (STASH) {
+        sidx[i * K + k] = e;
+        sw[i * K + k] = wt;
+      } else {
+        topk_idx[(size_t)t * K + k] = e;
+        topk_w[(size_t)t * K + k] = wt;
       }
-    }
-    // renormalisation denominator: selected scores summed in ascending expert
-    // order (expert 64j + l is value j of lane l; ballots list them in order)
-    float denom = 0.f;
-#pragma unroll
-    for (int j = 0; j < EPL; ++j) {
-      uint64_t sel = __ballot((taken >> j) & 1ull);
-      while (sel) {
-        const int l = __ffsll((unsigned long long)sel) - 1;
-        denom += __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[j]), l));
-        sel &= sel - 1;
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      if (k < K && lane == k) {
-        if (STASH) {
-          sidx[i * K + k] = sel_e[k];
-          sw[i * K + k] = sel_v[k] / denom;
-        } else {
-          topk_idx[(size_t)t * K + k] = sel_e[k];
-          topk_w[(size_t)t * K + k] = sel_v[k] / denom;
-        }
-        atomicOr(&mword[sel_e[k]], 1ull << i);
-      }
-    }
+      atomicOr(&mword[e], 1ull << i);
+    });
   }
   __syncthreads();
   for (int e = threadIdx.x; e < E; e += kTopkWaves * 64) mask[(size_t)e * W + w] = mword[e];
@@ -370,6 +440,216 @@ __global__ __launch_bounds__(64 * NW) void topk_lane_kernel(const float* in, flo
 
 static size_t topk_lane_lds(int E, int KM, int NW) {
   return (size_t)E * 256 + (NW > 1 ? (size_t)NW * 64 * (4 + 4 + 8 * KM + 4 * KM + 4) : 0);
+}
+
+// ------------------------------------------------------------- few tokens
+// Decode and short prefill calls (T <= kFewTokens).  The lane-per-token kernels
+// above are built for many tokens: with few of them they run on a handful of
+// CUs for the latency of a whole token's serial work (T = 1: the one-launch
+// router 21 us, then three metadata launches 15 us).  Here a wave takes one
+// token, and the routing metadata comes from the top-K lists instead of the
+// bitmap: T K entries, counted in LDS.
+
+// rows of one 64-token word from its top-K lists: row = first row of the expert
+// + its tokens in earlier words + its earlier tokens in the word
+__device__ __forceinline__ void place_word(const moe_routing& r, int w, int T, int K, const int* idx, const float* wt,
+                                           const unsigned long long* word, const int* base) {
+  const int nt = min(64, T - 64 * w);
+  for (int i = threadIdx.x; i < nt * K; i += blockDim.x) {
+    const int tl = i / K, t = 64 * w + tl, e = idx[i];
+    int rank = 0;  // the token's selected experts below e
+    for (int k = 0; k < K; ++k) rank += idx[tl * K + k] < e;
+    const int row = base[e] + __popcll(word[e] & ((1ull << tl) - 1));
+    r.tok_rows[(size_t)t * K + rank] = row;
+    r.row_token[row] = t;
+    r.row_expert[row] = e;
+    r.row_w[row] = wt[i];
+  }
+  for (int tl = threadIdx.x; tl < nt; tl += blockDim.x) {
+    r.tok_offsets[64 * w + tl] = (64 * w + tl) * K;
+    r.tok_count[64 * w + tl] = K;
+    if (64 * w + tl == T - 1) r.tok_offsets[T] = T * K;
+  }
+}
+
+// A wave per token: softmax of the summed partial logits (or the scores as
+// given), top-K.  WG16: a workgroup of 16 waves holds 16 tokens, whose
+// transposed scores leave as 64-byte runs.  Else (META) one workgroup holds all
+// T <= 16 tokens and goes on to the metadata.
+constexpr int kFewWaves = kFewOneGroup;
+template <int EPL, bool META>
+__global__ __launch_bounds__(64 * kFewWaves) void topk_few_kernel(const float* in, int slices,
+                                                                 const float* __restrict__ bias, float* logits,
+                                                                 float* __restrict__ scores_t, const moe_routing r,
+                                                                 int T, int E, int K, int do_softmax, int counts_only) {
+  // META: words [E], bases [E], idx and weights [16][K]; else with scores_t: [E][17] scores
+  extern __shared__ __attribute__((aligned(16))) char dyn[];
+  __shared__ int scan_lds[16];
+  unsigned long long* word = (unsigned long long*)dyn;
+  int* base = (int*)(dyn + 8 * (size_t)E);
+  int* sidx = base + E;
+  float* sw = (float*)(sidx + kFewWaves * K);
+  float* st = (float*)dyn;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
+  if constexpr (META) {
+    for (int e = threadIdx.x; e < E; e += 64 * kFewWaves) word[e] = 0ull;
+    __syncthreads();
+  }
+  const size_t slab = (size_t)T * E;
+  if (const int t = blockIdx.x * kFewWaves + wave; t < T) {
+    float v[EPL];
+#pragma unroll
+    for (int j = 0; j < EPL; ++j) {
+      const int e = lane + 64 * j;
+      v[j] = -INFINITY;
+      if (e < E) {
+        const float* p = in + (size_t)t * E + e;
+        float x = p[0];
+#pragma unroll 4
+        for (int q = 1; q < slices; ++q) x += p[q * slab];
+        if (bias) x += bias[e];
+        if (logits) logits[(size_t)t * E + e] = x;
+        v[j] = x;
+      }
+    }
+    if (do_softmax) {
+      float m = -INFINITY;
+#pragma unroll
+      for (int j = 0; j < EPL; ++j) m = fmaxf(m, v[j]);
+      m = dpp_reduce(m, [](float a, float b) { return fmaxf(a, b); });
+      float s = 0.f;
+#pragma unroll
+      for (int j = 0; j < EPL; ++j) {
+        v[j] = lane + 64 * j < E ? expf(v[j] - m) : 0.f;
+        s += v[j];
+      }
+      s = dpp_reduce(s, [](float a, float b) { return a + b; });
+#pragma unroll
+      for (int j = 0; j < EPL; ++j) {
+        const int e = lane + 64 * j;
+        if (e < E) r.scores[(size_t)t * E + e] = v[j] = v[j] / s;
+      }
+    }
+    if (scores_t) {
+#pragma unroll
+      for (int j = 0; j < EPL; ++j) {
+        const int e = lane + 64 * j;
+        if (e >= E) continue;
+        if constexpr (META)
+          scores_t[(size_t)e * T + t] = v[j];
+        else
+          st[e * (kFewWaves + 1) + wave] = v[j];
+      }
+    }
+    wave_topk<EPL>(v, E, K, [&](int k, int e, float wt) {
+      r.topk_idx[(size_t)t * K + k] = e;
+      r.topk_w[(size_t)t * K + k] = wt;
+      if constexpr (META) {
+        sidx[t * K + k] = e;
+        sw[t * K + k] = wt;
+        atomicOr(&word[e], 1ull << t);
+      }
+    });
+  }
+  if constexpr (META) {
+    __syncthreads();
+    int running = 0;
+    for (int e0 = 0; e0 < E; e0 += 64 * kFewWaves) {
+      const int e = e0 + threadIdx.x;
+      const int c = e < E ? __popcll(word[e]) : 0;
+      int total;
+      const int off = running + block_excl_scan<64 * kFewWaves>(c, &total, scan_lds);
+      if (e < E) {
+        r.mask[e] = word[e];
+        r.mask_prefix[e] = 0;
+        r.counts[e] = c;
+        if (!counts_only) r.offsets[e] = off;
+        base[e] = off;
+      }
+      running += total;
+    }
+    if (counts_only) return;
+    if (threadIdx.x == 0) {
+      r.offsets[E] = running;
+      *r.status = 0;
+    }
+    __syncthreads();
+    place_word(r, 0, T, K, sidx, sw, word, base);
+  } else if (scores_t) {
+    __syncthreads();
+    const int t0 = blockIdx.x * kFewWaves, nt = min(kFewWaves, T - t0);
+    for (int i = threadIdx.x; i < E * kFewWaves; i += 64 * kFewWaves) {
+      const int e = i / kFewWaves, tl = i % kFewWaves;
+      if (tl < nt) scores_t[(size_t)e * T + t0 + tl] = st[e * (kFewWaves + 1) + tl];
+    }
+  }
+}
+
+// Bitmap, counts, offsets and rows in one launch: the workgroup of a 64-token
+// word counts every expert's tokens, and those of the earlier words, from the
+// top-K lists (at most kFewTokens x 16 entries, from L2) and places its own.
+__global__ __launch_bounds__(1024) void tc_metadata_few_kernel(const moe_routing r, int T, int E, int K,
+                                                               int counts_only) {
+  extern __shared__ __attribute__((aligned(16))) char dyn[];
+  __shared__ int scan_lds[16];
+  unsigned long long* word = (unsigned long long*)dyn;  // [E]
+  int* total = (int*)(word + E);                        // [E] tokens, then first rows of the word
+  int* before = total + E;                              // [E] tokens of earlier words
+  int* sidx = before + E;                               // [64][K]
+  float* sw = (float*)(sidx + 64 * K);
+  const int w = blockIdx.x, W = gridDim.x;
+  for (int e = threadIdx.x; e < E; e += 1024) {
+    word[e] = 0ull;
+    total[e] = before[e] = 0;
+  }
+  __syncthreads();
+  const int lo = 64 * w * K, hi = min(T, 64 * w + 64) * K;
+  for (int i0 = 0; i0 < T * K; i0 += 4096) {
+    int e[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = i0 + 1024 * q + threadIdx.x;
+      e[q] = i < T * K ? r.topk_idx[i] : -1;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = i0 + 1024 * q + threadIdx.x;
+      if (e[q] < 0) continue;
+      atomicAdd(&total[e[q]], 1);
+      if (i < lo) {
+        atomicAdd(&before[e[q]], 1);
+      } else if (i < hi) {
+        sidx[i - lo] = e[q];
+        sw[i - lo] = r.topk_w[i];
+        atomicOr(&word[e[q]], 1ull << (i / K - 64 * w));
+      }
+    }
+  }
+  __syncthreads();
+  int running = 0;
+  for (int e0 = 0; e0 < E; e0 += 1024) {
+    const int e = e0 + threadIdx.x;
+    const int c = e < E ? total[e] : 0;
+    int sum;
+    const int off = running + block_excl_scan<1024>(c, &sum, scan_lds);
+    if (e < E) {
+      r.mask[(size_t)e * W + w] = word[e];
+      r.mask_prefix[(size_t)e * W + w] = before[e];
+      if (w == 0) {
+        r.counts[e] = c;
+        if (!counts_only) r.offsets[e] = off;
+      }
+      total[e] = off + before[e];
+    }
+    running += sum;
+  }
+  if (counts_only) return;
+  if (w == 0 && threadIdx.x == 0) {
+    r.offsets[E] = running;
+    *r.status = 0;
+  }
+  __syncthreads();
+  place_word(r, w, T, K, sidx, sw, word, total);
 }
 
 // Per expert: popcount prefix over its mask words and its count f_e.
@@ -743,6 +1023,45 @@ hipError_t launch_topk_route(const float* in, float* scores, float* scores_t, in
   SMOE_TOPK(64)
 #undef SMOE_TOPK
   return hipErrorInvalidValue;
+}
+
+hipError_t launch_topk_few(const float* in, int slices, const float* bias, float* logits, float* scores_t,
+                           const moe_routing& r, int T, int E, int K, int do_softmax, bool counts_only, hipStream_t s) {
+  if (T > kFewTokens || E > kFewExperts) return hipErrorInvalidValue;
+  const bool meta = T <= kFewOneGroup;
+  const dim3 grid((T + kFewWaves - 1) / kFewWaves), block(64 * kFewWaves);
+  // META: E * 12 + 16 K * 8 <= 14 KB; else the transposed scores: E * 68 <= 68 KB
+  const size_t lds = meta ? (size_t)E * 12 + kFewWaves * K * 8 : scores_t ? (size_t)E * (kFewWaves + 1) * 4 : 16;
+#define SMOE_FEW(N)                                                                                                  \
+  if (E <= 64 * N) {                                                                                                 \
+    if (meta) {                                                                                                      \
+      topk_few_kernel<N, true><<<grid, block, lds, s>>>(in, slices, bias, logits, scores_t, r, T, E, K, do_softmax,  \
+                                                        counts_only);                                                \
+    } else {                                                                                                         \
+      if (lds > 65536) {                                                                                             \
+        const hipError_t e = hipFuncSetAttribute((const void*)topk_few_kernel<N, false>,                             \
+                                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);             \
+        if (e != hipSuccess) return e;                                                                               \
+      }                                                                                                              \
+      topk_few_kernel<N, false><<<grid, block, lds, s>>>(in, slices, bias, logits, scores_t, r, T, E, K, do_softmax, \
+                                                         counts_only);                                               \
+    }                                                                                                                \
+    return hipGetLastError();                                                                                        \
+  }
+  SMOE_FEW(1)
+  SMOE_FEW(2)
+  SMOE_FEW(4)
+  SMOE_FEW(8)
+  SMOE_FEW(16)
+#undef SMOE_FEW
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_tc_metadata_few(const moe_routing& r, int T, int E, int K, bool counts_only, hipStream_t s) {
+  if (T > kFewTokens || E > kFewExperts) return hipErrorInvalidValue;
+  const size_t lds = (size_t)E * 16 + 64 * K * 8;  // <= 24 KB
+  tc_metadata_few_kernel<<<dim3(r.words), dim3(1024), lds, s>>>(r, T, E, K, counts_only);
+  return hipGetLastError();
 }
 
 hipError_t launch_tc_metadata(const moe_routing& r, int T, int E, int K, bool counts_only, hipStream_t s) {

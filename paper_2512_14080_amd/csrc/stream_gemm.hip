@@ -54,20 +54,24 @@ __device__ __forceinline__ f32x4 stream_sum(const StreamPart* part, int row, int
   return s;
 }
 
-// grid: x column tiles, y experts, z row groups (an expert's groups of 16 MB
-// rows are dealt to the z workgroups).  Op supplies
-//   int k(p), const uint16_t* x_row(p, e, row) (k contiguous),
-//   const uint16_t* w(p, e) with leading dimension ldw(p),
+// grid: x column tiles, y experts (or k slices of the router), z row groups (a
+// y's groups of 16 MB rows are dealt to the z workgroups).  Op supplies
+//   void rows(p, y, off, cnt): the rows [off, off + cnt),
+//   int k0(p, y), int k(p, y): the reduction, a multiple of 32,
+//   const uint16_t* x_row(p, row) (k contiguous from 0),
+//   const uint16_t* w(p, y) with leading dimension ldw(p),
 //   int col(p, tile, l): first of the eight columns of lane column l
-//   template <int KW> void finish(p, e, tile, row0, rows, part): 16 rows
+//   template <int KW> void finish(p, y, tile, row0, rows, part): 16 rows
 template <class Op, int MB, int KW, int NBUF, int OCC>
 __global__ __launch_bounds__(64 * KW, OCC) void stream_gemm_kernel(const typename Op::Params p) {
   __shared__ StreamPart part[KW];
   const int e = blockIdx.y, tile = blockIdx.x;
-  const int off = p.offsets[e], cnt = p.offsets[e + 1] - off;
+  int off, cnt;
+  Op::rows(p, e, off, cnt);
+  const int kbeg = Op::k0(p, e);
   const int lane = lane_id(), g = lane >> 4, l = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int ns = (Op::k(p) / 32 - wave + KW - 1) / KW;  // this wave's steps
+  const int ns = (Op::k(p, e) / 32 - wave + KW - 1) / KW;  // this wave's steps
   const uint16_t* wbase = Op::w(p, e);
   const uint32_t ldw = Op::ldw(p);
   const uint32_t wcol = Op::col(p, tile, l);
@@ -84,7 +88,7 @@ __global__ __launch_bounds__(64 * KW, OCC) void stream_gemm_kernel(const typenam
     bf16x8 xv[NBUF][MB];
     // step s of this wave; a step past the end reads the step 0 addresses (cached, unused)
     auto load = [&](int buf, int s) {
-      const uint32_t k = s < ns ? 32 * (wave + KW * s) : 32 * wave;
+      const uint32_t k = kbeg + 32 * (s < ns ? wave + KW * s : wave);
       const uint32_t o = (k + 8 * g) * ldw + wcol;
 #pragma unroll
       for (int i = 0; i < 8; ++i) wv[buf][i] = *(const u32x4*)(wbase + (size_t)(o + i * ldw));
@@ -126,11 +130,20 @@ __global__ __launch_bounds__(64 * KW, OCC) void stream_gemm_kernel(const typenam
   }
 }
 
+// rows of the routing: expert y's
+template <class Params>
+__device__ __forceinline__ void expert_rows(const Params& p, int y, int& off, int& cnt) {
+  off = p.offsets[y];
+  cnt = p.offsets[y + 1] - off;
+}
+
 // H = gather(X) W1_e (+ b1_e), A = SwiGLU(H): 64 gate columns (lane columns
 // 0..7) and the matching up columns (8..15)
 struct StreamUp {
   using Params = UpArgs;
-  static __host__ __device__ int k(const Params& p) { return p.d; }
+  static __device__ void rows(const Params& p, int y, int& off, int& cnt) { expert_rows(p, y, off, cnt); }
+  static __device__ int k0(const Params&, int) { return 0; }
+  static __device__ int k(const Params& p, int) { return p.d; }
   static __device__ const uint16_t* x_row(const Params& p, int row) { return p.X + (size_t)p.row_token[row] * p.d; }
   static __device__ const uint16_t* w(const Params& p, int e) { return p.W1 + (size_t)e * p.d * (2 * p.n); }
   static __device__ uint32_t ldw(const Params& p) { return 2 * p.n; }
@@ -172,7 +185,9 @@ struct StreamUp {
 template <int AGG>
 struct StreamDown {
   using Params = DownArgs;
-  static __host__ __device__ int k(const Params& p) { return p.n; }
+  static __device__ void rows(const Params& p, int y, int& off, int& cnt) { expert_rows(p, y, off, cnt); }
+  static __device__ int k0(const Params&, int) { return 0; }
+  static __device__ int k(const Params& p, int) { return p.n; }
   static __device__ const uint16_t* x_row(const Params& p, int row) { return p.A + (size_t)row * p.n; }
   static __device__ const uint16_t* w(const Params& p, int e) { return p.W2 + (size_t)e * p.n * p.d; }
   static __device__ uint32_t ldw(const Params& p) { return p.d; }
@@ -224,13 +239,35 @@ int stream_row_blocks(int64_t rows, int E, int64_t tiles_per_expert) {
   return mean <= 64 && E * tiles_per_expert < 192 ? 4 : 0;
 }
 
+// Partial router logits of k slice y: part[y][t][e] = sum over the slice of X W_r
+struct StreamRouter {
+  using Params = RouterPartArgs;
+  static __device__ void rows(const Params& p, int, int& off, int& cnt) {
+    off = 0;
+    cnt = p.T;
+  }
+  static __device__ int k0(const Params& p, int y) { return y * p.slice; }
+  static __device__ int k(const Params& p, int y) { return min(p.slice, p.d - y * p.slice); }
+  static __device__ const uint16_t* x_row(const Params& p, int row) { return p.X + (size_t)row * p.d; }
+  static __device__ const uint16_t* w(const Params& p, int) { return p.Wr; }
+  static __device__ uint32_t ldw(const Params& p) { return p.E; }
+  // (lane columns past E, a multiple of 8, re-read the last ones)
+  static __device__ uint32_t col(const Params& p, int tile, int l) { return min(kStreamCols * tile + 8 * l, p.E - 8); }
+  template <int KW>
+  static __device__ void finish(const Params& p, int y, int tile, int row0, int rows, const StreamPart* part) {
+    for (int i = threadIdx.x; i < 512; i += 64 * KW) {
+      const int row = i >> 5, c4 = i & 31, c = kStreamCols * tile + 4 * c4;
+      if (row >= rows) break;
+      if (c < p.E) *(f32x4*)(p.part + ((size_t)y * p.T + row0 + row) * p.E + c) = stream_sum<KW>(part, row, c4);
+    }
+  }
+};
+
+// waves and loads in flight of the row blocks: the widest split of k that
+// keeps two or more steps per wave, within the registers (no spills)
 template <class Op>
-static hipError_t run_stream(const typename Op::Params& p, int tiles, int mb, int T, hipStream_t s) {
-  // groups of one expert that run at once; more are looped over
-  const dim3 grid(tiles, p.E, std::min((T + 16 * mb - 1) / (16 * mb), 8));
-  // waves and loads in flight: the widest split of k that keeps two or more
-  // steps per wave, within the registers (no spills)
-  if (mb == 1 && Op::k(p) >= 768)
+static hipError_t run_stream(const typename Op::Params& p, dim3 grid, int mb, int k, hipStream_t s) {
+  if (mb == 1 && k >= 768)
     stream_gemm_kernel<Op, 1, 8, 3, 2><<<grid, dim3(512), 0, s>>>(p);
   else if (mb == 1)
     stream_gemm_kernel<Op, 1, 8, 2, 4><<<grid, dim3(512), 0, s>>>(p);
@@ -241,14 +278,50 @@ static hipError_t run_stream(const typename Op::Params& p, int tiles, int mb, in
   return hipGetLastError();
 }
 
+// grid of an expert GEMM: groups of one expert past the eighth are looped over
+static dim3 stream_grid(int tiles, int E, int mb, int T) {
+  return dim3(tiles, E, std::min((T + 16 * mb - 1) / (16 * mb), 8));
+}
+
 hipError_t launch_stream_up(const UpArgs& a, int mb, int T, hipStream_t s) {
-  return run_stream<StreamUp>(a, a.n / 64, mb, T, s);
+  return run_stream<StreamUp>(a, stream_grid(a.n / 64, a.E, mb, T), mb, a.d, s);
 }
 hipError_t launch_stream_down(const DownArgs& a, int strategy, int mb, int T, hipStream_t s) {
-  const int tiles = a.d / kStreamCols;
-  if (strategy == MOE_AGG_SCATTER_SUM) return run_stream<StreamDown<1>>(a, tiles, mb, T, s);
-  if (strategy == MOE_AGG_ATOMIC_F32) return run_stream<StreamDown<2>>(a, tiles, mb, T, s);
-  return run_stream<StreamDown<0>>(a, tiles, mb, T, s);
+  const dim3 grid = stream_grid(a.d / kStreamCols, a.E, mb, T);
+  if (strategy == MOE_AGG_SCATTER_SUM) return run_stream<StreamDown<1>>(a, grid, mb, a.n, s);
+  if (strategy == MOE_AGG_ATOMIC_F32) return run_stream<StreamDown<2>>(a, grid, mb, a.n, s);
+  return run_stream<StreamDown<0>>(a, grid, mb, a.n, s);
+}
+
+// Row blocks of the router's workgroups: one (16 tokens) while that gives up to
+// two workgroups per CU, more as W_r would otherwise be re-read too often.
+static int router_row_blocks(int T, int E, int* groups) {
+  const int tiles = (E + kStreamCols - 1) / kStreamCols;
+  for (int mb = 1;; mb *= 2) {
+    *groups = (T + 16 * mb - 1) / (16 * mb);
+    if (mb == 4 || tiles * *groups <= 512) return mb;
+  }
+}
+
+int router_slices(int T, int d, int E, size_t part_bytes) {
+  int groups;
+  router_row_blocks(T, E, &groups);
+  const int steps = d / 32, wgs = (E + kStreamCols - 1) / kStreamCols * groups;
+  // about one workgroup per two CUs, two or more steps for each of eight waves
+  const int64_t fit = part_bytes / ((size_t)T * E * 4);
+  const int want = std::min({128 / wgs, steps / 16, (int)std::min<int64_t>(fit, 64)});
+  if (want <= 1) return 1;
+  const int per = (steps + want - 1) / want;  // steps of a slice
+  return (steps + per - 1) / per;
+}
+
+hipError_t launch_router_part(const uint16_t* X, const uint16_t* Wr, float* part, int slices, int T, int d, int E,
+                              hipStream_t s) {
+  const int steps = d / 32, slice = 32 * ((steps + slices - 1) / slices);
+  int groups;
+  const int mb = router_row_blocks(T, E, &groups);
+  const dim3 grid((E + kStreamCols - 1) / kStreamCols, slices, groups);
+  return run_stream<StreamRouter>({X, Wr, part, T, d, E, slice}, grid, mb, slice, s);
 }
 
 }  // namespace smoe

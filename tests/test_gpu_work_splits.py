@@ -51,3 +51,72 @@ def test_few_rows_per_expert(T, d, n, E, K, zipf, biased):
     layer, R = check_layer(cfg, seed=33, eb=expert_biases(cfg, 33) if biased else None)
     if zipf:
         assert R.counts.max() > 128 and R.counts.min() == 0
+
+
+@pytest.mark.parametrize("T,d,E,K,mode", [
+    (1, 128, 8, 1, None),        # one token: one workgroup for top-K and metadata; four k steps
+    (64, 1536, 128, 8, None),    # the last word of the one-workgroup form; several k slices
+    (65, 384, 40, 3, None),      # the first T past it: a lone token in the second word
+    (300, 4096, 200, 16, None),  # K > 8, E off the 64-lane groups
+    (1000, 256, 264, 12, "nearest"),
+    (63, 256, 24, 5, "nearest"),  # rounding on the one-workgroup form (counts only)
+    (4096, 128, 64, 8, None),    # the last T of the few-token form
+    (4097, 128, 64, 8, None),    # the first T past it
+    (200, 128, 1024, 2, "up"),   # the largest E of the form, transposed scores beyond 64 KB of LDS
+    (200, 128, 1032, 2, None),   # the first E past it
+])
+def test_few_token_routing(T, d, E, K, mode):
+    """The routing of few tokens: its own router against the oracle's logits,
+    with every integer result a function of the scores it writes (the same
+    call with those scores given, and the oracle's routing of them)."""
+    import oracle
+    from test_gpu_parity import _torch, check_routing, oracle_routing
+    from dense_reference import rel_err
+    torch = _torch()
+    from paper_2512_14080_amd import binding as B
+    from paper_2512_14080_amd.layer import DeviceLayer
+    cfg = W.MoEConfig("route", T=T, d=d, n=64, E=E, K=K, m_tile=16, zipf_s=0.5)
+    inp = W.make_inputs(cfg, 34)
+    layers = []
+    for scores in (None, "given"):
+        if scores:
+            scores = layers[0].tc.arrays()["scores"].cpu().numpy()
+        layer = DeviceLayer(inp, round_mode=mode, scores_in=scores)
+        layer.route()
+        torch.cuda.synchronize()
+        layers.append(layer)
+    L = oracle.router_logits(inp.f32("X"), inp.f32("Wr"), inp.bias, np.float32)
+    a = {k: v.cpu().numpy() for k, v in layers[0].tc.arrays().items() if v is not None}
+    assert rel_err(a["logits"], L) <= 1e-4
+    assert rel_err(a["scores"], oracle.softmax_scores(L).astype(np.float32)) <= 1e-4
+    idx, rdir, R = oracle_routing(a["scores"], K, mode, cfg.m_tile)
+    for layer in layers:
+        check_routing(layer, R, idx, rdir)
+        t = layer.tc.arrays()
+        if mode:
+            np.testing.assert_array_equal(t["scores_t"].cpu().numpy(), a["scores"].T)
+            member = np.zeros((T, E), bool)
+            np.put_along_axis(member, idx, True, axis=1)
+            np.testing.assert_array_equal(t["counts"].cpu().numpy(), member.sum(0))
+
+
+@pytest.mark.parametrize("T,E,K", [(16, 8, 8), (17, 72, 5), (70, 136, 8), (33, 264, 16), (90, 520, 7), (20, 1024, 1)])
+def test_few_token_selection_with_ties(T, E, K):
+    """Given scores with many equal values, zeros of both signs and rows of one
+    value: the selection still takes the lowest experts, in the oracle's order."""
+    from test_gpu_parity import _torch, check_routing, oracle_routing
+    torch = _torch()
+    from paper_2512_14080_amd.layer import DeviceLayer
+    cfg = W.MoEConfig("ties", T=T, d=128, n=64, E=E, K=K, m_tile=16)
+    rng = np.random.default_rng(E + K)
+    S = (rng.integers(1, 5, (T, E)) / np.float32(8)).astype(np.float32)
+    S[0] = 0.25
+    S[1, ::2], S[1, 1::2] = 0.0, -0.0
+    S[1, E // 2] = 0.5
+    layer = DeviceLayer(W.make_inputs(cfg, 35), scores_in=S)
+    layer.route()
+    torch.cuda.synchronize()
+    idx, _, R = oracle_routing(S, K)
+    np.testing.assert_array_equal(layer.tc.arrays()["topk_idx"].cpu().numpy(), idx)
+    np.testing.assert_array_equal(layer.tc.arrays()["row_token"].cpu().numpy(), R.row_token)
+    np.testing.assert_array_equal(layer.tc.arrays()["row_expert"].cpu().numpy(), R.row_expert)
