@@ -498,18 +498,29 @@ __global__ __launch_bounds__(64 * kFewWaves) void topk_few_kernel(const float* i
   const size_t slab = (size_t)T * E;
   if (const int t = blockIdx.x * kFewWaves + wave; t < T) {
     float v[EPL];
+    // slabs in slice order, four at a time (all their loads in flight together)
+    for (int q0 = 0; q0 < slices; q0 += 4) {
+      float x[4][EPL];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int j = 0; j < EPL; ++j) {
+          const int e = lane + 64 * j;
+          x[q][j] = q0 + q < slices && e < E ? in[(q0 + q) * slab + (size_t)t * E + e] : 0.f;
+        }
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int j = 0; j < EPL; ++j) v[j] = q0 + q == 0 ? x[0][j] : v[j] + x[q][j];
+    }
 #pragma unroll
     for (int j = 0; j < EPL; ++j) {
       const int e = lane + 64 * j;
-      v[j] = -INFINITY;
       if (e < E) {
-        const float* p = in + (size_t)t * E + e;
-        float x = p[0];
-#pragma unroll 4
-        for (int q = 1; q < slices; ++q) x += p[q * slab];
-        if (bias) x += bias[e];
-        if (logits) logits[(size_t)t * E + e] = x;
-        v[j] = x;
+        if (bias) v[j] += bias[e];
+        if (logits) logits[(size_t)t * E + e] = v[j];
+      } else {
+        v[j] = -INFINITY;
       }
     }
     if (do_softmax) {
