@@ -22,7 +22,10 @@ __device__ __forceinline__ float bcast_f(float v, int l) {
 }
 
 // One wave per token; lanes cover 8 consecutive bf16 (16 bytes) of the row,
-// in NC chunks of 512 columns starting at column c0.  The token's rows are taken kAggBatch at a time
+// in NC chunks of 512 columns of the workgroup's column slice (rows wider than
+// 2048 columns are cut into slices; neighbouring workgroups take the slices of
+// the same tokens, so a row's pieces are read at about the same time).  The
+// token's rows are taken kAggBatch at a time
 // without branches: lanes 0..7 fetch the batch's row indices and weights
 // (padding slots clamped to the token's last row, weight 0) and broadcast
 // them, then the row loads of every chunk are issued before any is
@@ -34,9 +37,10 @@ __device__ __forceinline__ float bcast_f(float v, int l) {
 template <int NC, bool CONTIG = false>
 __global__ __launch_bounds__(256) void agg_o_kernel(const uint16_t* __restrict__ Y, const int32_t* __restrict__ tok_offsets,
                                                     const int32_t* __restrict__ tok_rows, const float* __restrict__ row_w,
-                                                    uint16_t* __restrict__ O, int T, int d, int c0) {
+                                                    uint16_t* __restrict__ O, int T, int d, int slices) {
+  const int c0 = blockIdx.x % slices * (512 * NC);  // this workgroup's column slice
   // wave-uniform token: row indices and weights become scalar loads
-  const int t = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int t = blockIdx.x / slices * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (t >= T) return;
   const int lane = lane_id();
   const int j0 = tok_offsets[t], j1 = tok_offsets[t + 1];
@@ -88,7 +92,7 @@ __global__ __launch_bounds__(256) void agg_o_kernel(const uint16_t* __restrict__
 // dX_t = sum over the token's rows of dX~ + sum_j dl_j W_r[:, e_j], with the
 // router gradient on the token's selected set dl_j = s_j (dS_j - sum_k s_k dS_k).
 // Also writes the dense router-logit gradient row dL[t, :] (bf16) for dW_r
-// (when dL is given; the launch for column slice 0 does it).
+// (when dL is given; the workgroups of column slice 0 do it).
 // W_r^T [E][d] is a bf16 copy (exact: W_r is bf16), so each row term is one
 // 16-byte load per lane.  As in the forward kernel, a batch's dX~ rows are
 // requested for every column chunk before any is accumulated; the W_r^T rows
@@ -100,9 +104,11 @@ __global__ __launch_bounds__(256) void agg_dx_kernel(const uint16_t* __restrict_
                                                      const int32_t* __restrict__ tok_rows,
                                                      const int32_t* __restrict__ row_expert,
                                                      const float* __restrict__ row_w, uint16_t* __restrict__ dX,
-                                                     uint16_t* __restrict__ dL, int T, int d, int E, int c0) {
+                                                     uint16_t* __restrict__ dL_, int T, int d, int E, int slices) {
+  const int c0 = blockIdx.x % slices * (512 * NC);  // this workgroup's column slice
+  uint16_t* const dL = c0 == 0 ? dL_ : nullptr;  // written by the first slice
   // wave-uniform token: row indices and weights become scalar loads
-  const int t = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int t = blockIdx.x / slices * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (t >= T) return;
   const int lane = lane_id();
   const int j0 = tok_offsets[t], j1 = tok_offsets[t + 1];
@@ -374,28 +380,29 @@ hipError_t launch_expert_colsum(const ExpertColsumArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_agg_o(const uint16_t* Y, const moe_routing& r, uint16_t* O, int T, int d, hipStream_t s) {
-  const dim3 grid((T + 3) / 4), block(256);
-  const int nc = (d + 511) / 512;
-  if (nc <= 1) agg_o_kernel<1><<<grid, block, 0, s>>>(Y, r.tok_offsets, r.tok_rows, r.row_w, O, T, d, 0);
-  else if (nc == 2) agg_o_kernel<2><<<grid, block, 0, s>>>(Y, r.tok_offsets, r.tok_rows, r.row_w, O, T, d, 0);
-  else if (nc == 3) agg_o_kernel<3><<<grid, block, 0, s>>>(Y, r.tok_offsets, r.tok_rows, r.row_w, O, T, d, 0);
-  else  // rows wider than 1536: 2048-column slices, one launch each
-    for (int c0 = 0; c0 < d; c0 += 2048)
-      agg_o_kernel<4><<<grid, block, 0, s>>>(Y, r.tok_offsets, r.tok_rows, r.row_w, O, T, d, c0);
+// slices of at most four 512-column chunks, as equal as they go
+static int agg_slices(int d) { return ((d + 511) / 512 + 3) / 4; }
+
+template <bool CONTIG>
+static hipError_t run_agg_o(const uint16_t* Y, const moe_routing& r, uint16_t* O, int T, int d, hipStream_t s) {
+  const int slices = agg_slices(d), nc = ((d + 511) / 512 + slices - 1) / slices;
+  const dim3 grid((unsigned)((T + 3) / 4) * slices), block(256);
+#define SMOE_AGG(N) \
+  if (nc == N) agg_o_kernel<N, CONTIG><<<grid, block, 0, s>>>(Y, r.tok_offsets, r.tok_rows, r.row_w, O, T, d, slices)
+  SMOE_AGG(1);
+  SMOE_AGG(2);
+  SMOE_AGG(3);
+  SMOE_AGG(4);
+#undef SMOE_AGG
   return hipGetLastError();
 }
 
+hipError_t launch_agg_o(const uint16_t* Y, const moe_routing& r, uint16_t* O, int T, int d, hipStream_t s) {
+  return run_agg_o<false>(Y, r, O, T, d, s);
+}
+
 hipError_t launch_agg_o_contig(const uint16_t* Yt, const moe_routing& r, uint16_t* O, int T, int d, hipStream_t s) {
-  const dim3 grid((T + 3) / 4), block(256);
-  const int nc = (d + 511) / 512;
-  if (nc <= 1) agg_o_kernel<1, true><<<grid, block, 0, s>>>(Yt, r.tok_offsets, r.tok_rows, r.row_w, O, T, d, 0);
-  else if (nc == 2) agg_o_kernel<2, true><<<grid, block, 0, s>>>(Yt, r.tok_offsets, r.tok_rows, r.row_w, O, T, d, 0);
-  else if (nc == 3) agg_o_kernel<3, true><<<grid, block, 0, s>>>(Yt, r.tok_offsets, r.tok_rows, r.row_w, O, T, d, 0);
-  else
-    for (int c0 = 0; c0 < d; c0 += 2048)
-      agg_o_kernel<4, true><<<grid, block, 0, s>>>(Yt, r.tok_offsets, r.tok_rows, r.row_w, O, T, d, c0);
-  return hipGetLastError();
+  return run_agg_o<true>(Yt, r, O, T, d, s);
 }
 
 // dst[tok_rows[j]] = j for the j < tok_offsets[T] (token-major slot of each row)
@@ -433,21 +440,17 @@ hipError_t launch_f32_to_bf16(const float* in, uint16_t* out, size_t n, hipStrea
 
 hipError_t launch_agg_dx(const uint16_t* dXt, const float* dS, const uint16_t* WrT, const moe_routing& r, uint16_t* dX,
                          uint16_t* dL, int T, int d, int E, hipStream_t s) {
-  const dim3 grid((T + 3) / 4), block(256);
-  const int nc = (d + 511) / 512;
-  if (nc <= 1)
-    agg_dx_kernel<1><<<grid, block, 0, s>>>(dXt, dS, WrT, r.tok_offsets, r.tok_rows, r.row_expert, r.row_w, dX, dL, T,
-                                            d, E, 0);
-  else if (nc == 2)
-    agg_dx_kernel<2><<<grid, block, 0, s>>>(dXt, dS, WrT, r.tok_offsets, r.tok_rows, r.row_expert, r.row_w, dX, dL, T,
-                                            d, E, 0);
-  else if (nc == 3)
-    agg_dx_kernel<3><<<grid, block, 0, s>>>(dXt, dS, WrT, r.tok_offsets, r.tok_rows, r.row_expert, r.row_w, dX, dL, T,
-                                            d, E, 0);
-  else  // rows wider than 1536: 2048-column slices, one launch each; the first writes dL
-    for (int c0 = 0; c0 < d; c0 += 2048)
-      agg_dx_kernel<4><<<grid, block, 0, s>>>(dXt, dS, WrT, r.tok_offsets, r.tok_rows, r.row_expert, r.row_w, dX,
-                                              c0 == 0 ? dL : nullptr, T, d, E, c0);
+  const int slices = agg_slices(d), nc = ((d + 511) / 512 + slices - 1) / slices;
+  const dim3 grid((unsigned)((T + 3) / 4) * slices), block(256);
+#define SMOE_AGG(N)                                                                                                   \
+  if (nc == N)                                                                                                        \
+  agg_dx_kernel<N><<<grid, block, 0, s>>>(dXt, dS, WrT, r.tok_offsets, r.tok_rows, r.row_expert, r.row_w, dX, dL, T, \
+                                          d, E, slices)
+  SMOE_AGG(1);
+  SMOE_AGG(2);
+  SMOE_AGG(3);
+  SMOE_AGG(4);
+#undef SMOE_AGG
   return hipGetLastError();
 }
 
