@@ -1547,14 +1547,33 @@ hipError_t launch_router_topk(const RouterTopkArgs& a, hipStream_t s) {
   return run<OpRouterTopk<C128x256r, 8, false>>({a}, tiles, s);
 }
 
+// Whether 256 x 128 tiles serve a varlen-M GEMM of N columns better than 256 x
+// 256: the persistent schedule runs ceil(tiles / CUs) rounds, and a narrow tile
+// takes about 0.58 of a wide one.  So they win where a whole extra round of
+// wide tiles is nearly empty: up to half a round (one round of narrow tiles:
+// 0.58 of the time), and from one to one and a half (three narrow rounds for two
+// wide ones: 0.87).  us, wide and narrow tiles:
+//   dX~   T = 1000, d = 768, n = 1024, E = 32, K = 2     96 wide tiles   43 -> 26
+//   down  T = 1777, d = 1536, n = 512, E = 64, K = 4    384             35.5 -> 32
+//   down  T = 3000, d = 1536, n = 1024, E = 16, K = 2   186             34 -> 38 (not taken)
+//   up    T = 2048, d = 1024, n = 256, E = 64, K = 8    192             40 -> 46 (not taken)
+static bool narrow_tiles(int64_t rows, int E, int N, bool half_round_only) {
+  const int64_t mtiles = std::max<int64_t>(E, rows / kMTile + E / 2);  // about; ragged last tiles included
+  const int64_t tiles = mtiles * (N / 256), cus = cu_count();
+  return 2 * tiles <= cus || (!half_round_only && tiles > cus && 2 * tiles <= 3 * cus);
+}
+
 hipError_t launch_up(const UpArgs& a, hipStream_t s) {
   const int N = 2 * a.n;
-  if (a.n % 128 == 0) return run<OpUp<C256x256w>>({a}, pad8(mtiles_bound(a.capacity, a.E, 256) * (N / 256)), s);
+  // (its 256 x 128 tiles store 64-byte pieces: only for half a round)
+  if (a.n % 128 == 0 && !narrow_tiles(a.rows, a.E, N, true))
+    return run<OpUp<C256x256w>>({a}, pad8(mtiles_bound(a.capacity, a.E, 256) * (N / 256)), s);
   return run<OpUp<C256x128>>({a}, pad8(mtiles_bound(a.capacity, a.E, 256) * (N / 128)), s);  // n % 64
 }
 
 hipError_t launch_down(const DownArgs& a, hipStream_t s) {
-  if (a.d % 256 == 0) return run<OpDown<C256x256s>>({a}, pad8(mtiles_bound(a.capacity, a.E, 256) * (a.d / 256)), s);
+  if (a.d % 256 == 0 && !narrow_tiles(a.rows, a.E, a.d, false))
+    return run<OpDown<C256x256s>>({a}, pad8(mtiles_bound(a.capacity, a.E, 256) * (a.d / 256)), s);
   return run<OpDown<C256x128>>({a}, pad8(mtiles_bound(a.capacity, a.E, 256) * (a.d / 128)), s);
 }
 
@@ -1572,12 +1591,16 @@ hipError_t launch_down_ablation(const DownArgs& a, int strategy, hipStream_t s) 
   return launch_down(a, s);
 }
 
-static int dh_bn(int n) { return n % 256 == 0 ? 256 : (n % 128 == 0 ? 128 : 64); }
-int dh_n_tiles(int n) { return n / dh_bn(n); }
+// (T = 2048, d = 1024, n = 256, E = 64, K = 8, 96 wide tiles: 49 -> 33 us)
+static int dh_bn(int n, int64_t rows, int E) {
+  if (n % 256 == 0 && !narrow_tiles(rows, E, n, true)) return 256;
+  return n % 128 == 0 ? 128 : 64;
+}
+int dh_n_tiles(int n, int64_t rows, int E) { return n / dh_bn(n, rows, E); }
 
 hipError_t launch_dh(const DHArgs& a, hipStream_t s) {
-  const int grid = pad8(mtiles_bound(a.capacity, a.E, 256) * dh_n_tiles(a.n));
-  switch (dh_bn(a.n)) {
+  const int grid = pad8(mtiles_bound(a.capacity, a.E, 256) * dh_n_tiles(a.n, a.rows, a.E));
+  switch (dh_bn(a.n, a.rows, a.E)) {
     case 256: return run<OpDH<C256x256w>>({a}, grid, s);
     case 128: return run<OpDH<C256x128>>({a}, grid, s);
     default: return run<OpDH<C256x64>>({a}, grid, s);
@@ -1585,7 +1608,8 @@ hipError_t launch_dh(const DHArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_dxt(const DXtArgs& a, hipStream_t s) {
-  if (a.d % 256 == 0) return run<OpDXt<C256x256ws>>({a}, pad8(mtiles_bound(a.capacity, a.E, 256) * (a.d / 256)), s);
+  if (a.d % 256 == 0 && !narrow_tiles(a.rows, a.E, a.d, false))
+    return run<OpDXt<C256x256ws>>({a}, pad8(mtiles_bound(a.capacity, a.E, 256) * (a.d / 256)), s);
   return run<OpDXt<C256x128>>({a}, pad8(mtiles_bound(a.capacity, a.E, 256) * (a.d / 128)), s);
 }
 
@@ -1594,8 +1618,11 @@ hipError_t launch_dxt(const DXtArgs& a, hipStream_t s) {
 using W256x256 = GemmCfg<256, 256, 2, 4, 2>;
 using W128x256 = GemmCfg<128, 256, 2, 4, 2>;
 using W64x256 = GemmCfg<64, 256, 2, 4, 2>;
-using W128x128 = GemmCfg<128, 128, 4, 2, 2>;
-using W64x128 = GemmCfg<64, 128, 2, 4, 2>;
+// the small tiles leave room for two workgroups per CU, whose loads cover each
+// other's waits (T = 5003, d = 896, n = 192, E = 40, K = 3: dW1 42 -> 31 us, dW2
+// 37 -> 28 against one)
+using W128x128 = GemmCfg<128, 128, 4, 2, 2, kBK, 2>;
+using W64x128 = GemmCfg<64, 128, 2, 4, 2, kBK, 2>;
 
 // slabs of one weight-gradient GEMM: at most kDwSlabs, within kDwSlabBytes
 int dw_slabs(int64_t mn) {
@@ -1609,12 +1636,16 @@ size_t dw_part_bytes(int d, int n) {
 
 // tile shapes of the weight-gradient GEMMs (their k-chunk lists are built
 // for these shapes); dW2: M = n, N = d; dW1: M = d, N = 2n
-static void dw2_tile(int d, int n, int* bm, int* bn) {
-  *bn = d % 256 == 0 ? 256 : 128;
+// (where the 256-wide tiles of all experts are at most half a round of the CUs,
+// the 128-wide ones, four times as many and two to a CU, take less time)
+static bool dw_small_tiles(int E, int64_t tiles_per_expert) { return 2 * E * tiles_per_expert <= cu_count(); }
+static void dw2_tile(int d, int n, int E, int* bm, int* bn) {
+  *bn = d % 256 == 0 && !(n % 128 == 0 && dw_small_tiles(E, (int64_t)(d / 256) * ((n + 255) / 256))) ? 256 : 128;
   *bm = (*bn == 256 && n % 256 == 0) ? 256 : (n % 128 == 0 ? 128 : 64);
 }
-static void dw1_tile(int d, int n, int* bm, int* bn) {
-  *bm = *bn = (d % 256 == 0 && (2 * n) % 256 == 0) ? 256 : 128;
+static void dw1_tile(int d, int n, int E, int* bm, int* bn) {
+  const bool wide = d % 256 == 0 && (2 * n) % 256 == 0 && !dw_small_tiles(E, (int64_t)(d / 256) * (2 * n / 256));
+  *bm = *bn = wide ? 256 : 128;
 }
 
 // whether E experts of tpe tiles each fill whole rounds of the CUs to 3/4
@@ -1627,8 +1658,8 @@ hipError_t launch_bwd_lists(const int32_t* offsets, int E, int d, int n, int32_t
                             int32_t* klist1, const uint16_t* Wr, uint16_t* WrT, hipStream_t s) {
   if (E > 4096) return hipErrorInvalidValue;
   int bm2, bn2, bm1, bn1;
-  dw2_tile(d, n, &bm2, &bn2);
-  dw1_tile(d, n, &bm1, &bn1);
+  dw2_tile(d, n, E, &bm2, &bn2);
+  dw1_tile(d, n, E, &bm1, &bn1);
   const int tpe2 = (n / bm2) * (d / bn2), tpe1 = (d / bm1) * (2 * n / bn1);
   const int tr_blocks = Wr ? (d * E + kMTilesThreads - 1) / kMTilesThreads : 0;
   bwd_lists_kernel<<<3 + tr_blocks, kMTilesThreads, 0, s>>>(offsets, E, mtiles, tpe2, dw_slabs((int64_t)n * d),
@@ -1651,7 +1682,7 @@ static hipError_t run_dw(const Args& a, int M, int N, uint16_t* dW, bool reduce,
 
 hipError_t launch_dw2(const DW2Args& a, hipStream_t s) {
   int bm, bn;
-  dw2_tile(a.d, a.n, &bm, &bn);
+  dw2_tile(a.d, a.n, a.E, &bm, &bn);
   if (bn == 256) {
     if (bm == 256) return run_dw<OpDW2<W256x256>>(a, a.n, a.d, a.dW2, true, s);
     if (bm == 128) return run_dw<OpDW2<W128x256>>(a, a.n, a.d, a.dW2, true, s);
@@ -1663,7 +1694,7 @@ hipError_t launch_dw2(const DW2Args& a, hipStream_t s) {
 
 hipError_t launch_dw1(const DW1Args& a, hipStream_t s) {
   int bm, bn;
-  dw1_tile(a.d, a.n, &bm, &bn);
+  dw1_tile(a.d, a.n, a.E, &bm, &bn);
   // its split experts are summed by launch_bwd_final_reduce
   if (bm == 256) return run_dw<OpDW1<W256x256>>(a, a.d, 2 * a.n, a.dW1, false, s);
   return run_dw<OpDW1<W128x128>>(a, a.d, 2 * a.n, a.dW1, false, s);

@@ -63,16 +63,18 @@ constexpr int kMTile = 256;  // rows of an m-tile
 size_t mtiles_bytes(int64_t capacity, int E);
 hipError_t launch_mtiles(const int32_t* offsets, int E, int32_t* out, hipStream_t s);
 
+// rows: the routed rows to expect (T K), for the choice of the tiles; capacity
+// bounds them.
 struct UpArgs {
   const uint16_t* X; const uint16_t* W1; const int32_t* offsets; const int32_t* row_token;
-  uint16_t* H; uint16_t* A; int d, n, E, capacity; const int32_t* mtiles;
+  uint16_t* H; uint16_t* A; int d, n, E, capacity; int64_t rows; const int32_t* mtiles;
   const float* b1;  // [E,2n] expert bias added to H, or null
 };
 hipError_t launch_up(const UpArgs& a, hipStream_t s);
 
 struct DownArgs {
   const uint16_t* A; const uint16_t* W2; const int32_t* offsets; uint16_t* Y; int d, n, E, capacity;
-  const int32_t* mtiles;
+  int64_t rows; const int32_t* mtiles;
   const float* b2;  // [E,d] expert bias added to Y, or null
   // aggregation ablation only: token-major destination row of each row
   // (scatter), or the fp32 output and the row tokens / weights (atomics)
@@ -95,17 +97,17 @@ hipError_t launch_stream_down(const DownArgs& a, int strategy, int mb, int T, hi
 struct DHArgs {
   const uint16_t* dO; const uint16_t* W2; const uint16_t* H; const int32_t* offsets; const int32_t* row_token;
   const float* row_w; uint16_t* dH; uint16_t* Ap; float* dS; float* dS_part; int d, n, E, capacity;
-  const int32_t* mtiles;
+  int64_t rows; const int32_t* mtiles;
   // <dO_t, b2_e> of the expert-bias dS term as two fp32 halves [T][2E]
   // (columns e and E + e; see launch_bias_split), or null
   const float* bq;
 };
-int dh_n_tiles(int n);
+int dh_n_tiles(int n, int64_t rows, int E);  // dS partials per row
 hipError_t launch_dh(const DHArgs& a, hipStream_t s);
 
 struct DXtArgs {
   const uint16_t* dH; const uint16_t* W1; const int32_t* offsets; uint16_t* dXt; int d, n, E, capacity;
-  const int32_t* mtiles;
+  int64_t rows; const int32_t* mtiles;
 };
 hipError_t launch_dxt(const DXtArgs& a, hipStream_t s);
 

@@ -162,7 +162,7 @@ size_t abl_layout(const moe_dims& m, int64_t cap, char* base, FwdWs* w, int32_t*
 }
 
 size_t bwd_layout(const moe_dims& m, int64_t cap, char* base, BwdWs* w) {
-  const int nnt = smoe::dh_n_tiles(m.n);
+  const int nnt = smoe::dh_n_tiles(m.n, (int64_t)m.T * m.K, m.E);
   const int splits = smoe::dwr_splits(m.T, m.d, m.E);
   size_t off = 0;
   off = carve(base, off, smoe::mtiles_bytes(cap, m.E), w ? (void**)&w->mtiles : nullptr);
@@ -494,8 +494,9 @@ int moe_fwd(moe_dims m, const moe_bf16* X, const moe_bf16* W1, const moe_bf16* W
   FwdWs w;
   fwd_layout(m, r->capacity, (char*)ws, &w);
   hipStream_t stream = (hipStream_t)stream_;
-  const smoe::UpArgs up{X, W1, r->offsets, r->row_token, H, w.A, m.d, m.n, m.E, r->capacity, w.mtiles, b1};
-  const smoe::DownArgs down{w.A, W2, r->offsets, w.Y, m.d, m.n, m.E, r->capacity, w.mtiles, b2};
+  const int64_t rows = (int64_t)m.T * m.K;
+  const smoe::UpArgs up{X, W1, r->offsets, r->row_token, H, w.A, m.d, m.n, m.E, r->capacity, rows, w.mtiles, b1};
+  const smoe::DownArgs down{w.A, W2, r->offsets, w.Y, m.d, m.n, m.E, r->capacity, rows, w.mtiles, b2};
   const Projections proj(m);
   HIP_TRY(proj.lists(r->offsets, m.E, w.mtiles, stream), "m-tile list");
   LAUNCH(MOE_KC_UP, proj.run_up(up, stream), "up-proj");
@@ -548,12 +549,13 @@ int moe_fwd_aggregation_ablation(moe_dims m, const moe_bf16* X, const moe_bf16* 
   FwdWs w;
   abl_layout(m, r->capacity, (char*)ws, &w, &dst, &o32);
   hipStream_t stream = (hipStream_t)stream_;
+  const int64_t rows = (int64_t)m.T * m.K;
   const Projections proj(m);
   HIP_TRY(proj.lists(r->offsets, m.E, w.mtiles, stream), "m-tile list");
   LAUNCH(MOE_KC_UP,
-         proj.run_up({X, W1, r->offsets, r->row_token, H, w.A, m.d, m.n, m.E, r->capacity, w.mtiles, nullptr}, stream),
+         proj.run_up({X, W1, r->offsets, r->row_token, H, w.A, m.d, m.n, m.E, r->capacity, rows, w.mtiles, nullptr}, stream),
          "up-proj");
-  smoe::DownArgs da{w.A, W2, r->offsets, w.Y, m.d, m.n, m.E, r->capacity, w.mtiles, nullptr};
+  smoe::DownArgs da{w.A, W2, r->offsets, w.Y, m.d, m.n, m.E, r->capacity, rows, w.mtiles, nullptr};
   if (strategy == MOE_AGG_GATHER_SUM) {
     LAUNCH(MOE_KC_DOWN, proj.run_down(da, strategy, stream), "down-proj");
     LAUNCH(MOE_KC_AGG_O, smoe::launch_agg_o(w.Y, *r, O, m.T, m.d, stream), "aggregation");
@@ -614,7 +616,8 @@ int moe_bwd(moe_dims m, const moe_bf16* dO, const moe_bf16* X, const moe_bf16* H
   bwd_layout(m, r->capacity, (char*)ws, &w);
   hipStream_t stream = (hipStream_t)stream_;
   float* dS_out = dS ? dS : w.dS;
-  const int nnt = smoe::dh_n_tiles(m.n);
+  const int64_t rows = (int64_t)m.T * m.K;
+  const int nnt = smoe::dh_n_tiles(m.n, rows, m.E);
   HIP_TRY(smoe::launch_bwd_lists(r->offsets, m.E, m.d, m.n, w.mtiles, w.klist2, w.klist1, Wr, Wr ? w.WrT : nullptr,
                                  stream),
           "tile lists and W_r transpose");
@@ -625,12 +628,12 @@ int moe_bwd(moe_dims m, const moe_bf16* dO, const moe_bf16* X, const moe_bf16* H
   }
   LAUNCH(MOE_KC_DH,
          smoe::launch_dh({dO, W2, H, r->offsets, r->row_token, r->row_w, w.dH, w.Ap, dS_out, w.dS_part, m.d, m.n, m.E,
-                          r->capacity, w.mtiles, b2 ? w.bq : nullptr},
+                          r->capacity, rows, w.mtiles, b2 ? w.bq : nullptr},
                          stream),
          "dH");
   if (nnt > 1) HIP_TRY(smoe::launch_reduce_rowparts(w.dS_part, dS_out, r->capacity, nnt, stream), "dS reduce");
   LAUNCH(MOE_KC_DW2, smoe::launch_dw2({w.Ap, dO, r->offsets, r->row_token, dW2, m.d, m.n, m.E, w.klist2, w.dw_part}, stream), "dW2");
-  LAUNCH(MOE_KC_DXT, smoe::launch_dxt({w.dH, W1, r->offsets, w.dXt, m.d, m.n, m.E, r->capacity, w.mtiles}, stream),
+  LAUNCH(MOE_KC_DXT, smoe::launch_dxt({w.dH, W1, r->offsets, w.dXt, m.d, m.n, m.E, r->capacity, rows, w.mtiles}, stream),
          "dX~");
   LAUNCH(MOE_KC_DW1, smoe::launch_dw1({X, w.dH, r->offsets, r->row_token, dW1, m.d, m.n, m.E, w.klist1, w.dw_part}, stream), "dW1");
   LAUNCH(MOE_KC_AGG_DX,

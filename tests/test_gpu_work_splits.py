@@ -120,3 +120,25 @@ def test_few_token_selection_with_ties(T, E, K):
     np.testing.assert_array_equal(layer.tc.arrays()["topk_idx"].cpu().numpy(), idx)
     np.testing.assert_array_equal(layer.tc.arrays()["row_token"].cpu().numpy(), R.row_token)
     np.testing.assert_array_equal(layer.tc.arrays()["row_expert"].cpu().numpy(), R.row_expert)
+
+
+def test_wide_tiles_on_short_loops():
+    """Enough experts for the 256 x 256 tiles of every GEMM, with the loops at
+    their shortest: down (k = n = 64) and dX~ (k = 2n = 128) on the split LDS
+    ring, and weight gradients over experts of 0 to 4 k steps of 64 rows."""
+    check_layer(W.MoEConfig("ring", T=1600, d=768, n=64, E=72, K=2, m_tile=64), seed=36)
+    cfg = W.MoEConfig("kshort", T=1200, d=512, n=256, E=72, K=2, m_tile=64)
+    bias = np.concatenate([[-40.0], np.linspace(-5.0, 1.5, cfg.E - 1)]).astype(np.float32)
+    for mode in (None, "nearest"):
+        layer, R = check_layer(cfg, seed=37, bias=bias, round_mode=mode)
+        steps = set(int(-(-c // 64)) for c in R.counts)
+        assert steps >= {0, 1, 2, 3}, steps
+
+
+@pytest.mark.parametrize("T,d,n,E,K", [
+    (1280, 512, 512, 16, 2),   # 16 to 24 m-tiles: narrow tiles and small dW tiles throughout
+    (600, 1536, 512, 64, 4),   # 64 m-tiles x 6: between one round and one and a half of down and dX~
+    (1000, 256, 1024, 32, 2),  # up 256 wide tiles, dH 128: on both sides of half a round
+])
+def test_narrow_tiles(T, d, n, E, K):
+    check_layer(W.MoEConfig("narrow", T=T, d=d, n=n, E=E, K=K, m_tile=128), seed=38)
