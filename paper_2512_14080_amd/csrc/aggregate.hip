@@ -12,7 +12,6 @@
 namespace smoe {
 
 constexpr int kAggBatch = 8;  // rows whose loads are in flight together
-constexpr int kColRows = 32;  // tokens per chunk of the dbias column sum
 constexpr int kDLPerLane = 4;  // router-gradient row entries per lane collected in registers (E <= 256)
 static_assert(kAggBatch == 8, "lane & 7 picks a batch slot");
 
@@ -98,7 +97,7 @@ __global__ __launch_bounds__(256) void agg_o_kernel(const uint16_t* __restrict__
 // requested for every column chunk before any is accumulated; the W_r^T rows
 // (a few hundred KB, cache resident) follow chunk by chunk.
 template <int NC>
-__global__ __launch_bounds__(256) void agg_dx_kernel(const uint16_t* __restrict__ dXt, const float* __restrict__ dS,
+__global__ __launch_bounds__(256) void agg_dx_kernel(const uint16_t* __restrict__ dXt, const float* __restrict__ dS, int ds_parts,
                                                      const uint16_t* __restrict__ WrT,
                                                      const int32_t* __restrict__ tok_offsets,
                                                      const int32_t* __restrict__ tok_rows,
@@ -112,6 +111,11 @@ __global__ __launch_bounds__(256) void agg_dx_kernel(const uint16_t* __restrict_
   if (t >= T) return;
   const int lane = lane_id();
   const int j0 = tok_offsets[t], j1 = tok_offsets[t + 1];
+  auto ds_of = [&](int r) {  // dS of a row: its partial sums in order
+    float v = dS[(size_t)r * ds_parts];
+    for (int k = 1; k < ds_parts; ++k) v += dS[(size_t)r * ds_parts + k];
+    return v;
+  };
   // g = sum_k s_k dS_k in row order; lanes 0..7 fetch a batch's terms.  A
   // token whose rows fit one batch (every token-choice token with K <= 8,
   // most rounded ones) forms g in the main loop's only iteration instead, from
@@ -123,7 +127,7 @@ __global__ __launch_bounds__(256) void agg_dx_kernel(const uint16_t* __restrict_
     for (int jb = j0; jb < j1; jb += kAggBatch) {
       const int slot = jb + (lane & 7);
       const int rl = tok_rows[min(slot, j1 - 1)];
-      const float pl = slot < j1 ? row_w[rl] * dS[rl] : 0.f;
+      const float pl = slot < j1 ? row_w[rl] * ds_of(rl) : 0.f;
 #pragma unroll
       for (int u = 0; u < kAggBatch; ++u) g += bcast_f(pl, u);
     }
@@ -141,11 +145,11 @@ __global__ __launch_bounds__(256) void agg_dx_kernel(const uint16_t* __restrict_
     const int rl = tok_rows[min(slot, j1 - 1)];
     const int el = WrT ? row_expert[rl] : 0;
     if (WrT && one_batch) {
-      const float pl = slot < j1 ? row_w[rl] * dS[rl] : 0.f;
+      const float pl = slot < j1 ? row_w[rl] * ds_of(rl) : 0.f;
 #pragma unroll
       for (int u = 0; u < kAggBatch; ++u) g += bcast_f(pl, u);
     }
-    const float dll = (WrT && slot < j1) ? row_w[rl] * (dS[rl] - g) : 0.f;
+    const float dll = (WrT && slot < j1) ? row_w[rl] * (ds_of(rl) - g) : 0.f;
     int r[kAggBatch];
 #pragma unroll
     for (int u = 0; u < kAggBatch; ++u) r[u] = bcast_i(rl, u);
@@ -215,7 +219,7 @@ __global__ __launch_bounds__(256) void agg_dx_kernel(const uint16_t* __restrict_
       float v = 0.f;
       for (int j = j0; j < j1; ++j) {
         const int r = tok_rows[j];
-        if (row_expert[r] == e) v = row_w[r] * (dS[r] - g);
+        if (row_expert[r] == e) v = row_w[r] * (ds_of(r) - g);
       }
       dL[(size_t)t * E + e] = f2bf(v);
     }
@@ -230,21 +234,6 @@ __global__ __launch_bounds__(256) void reduce_rowparts_kernel(const float* __res
   float s = 0.f;
   for (int k = 0; k < parts; ++k) s += part[(size_t)i * parts + k];
   out[i] = s;
-}
-
-// dbias[e] = sum_t dL[t][e] in two fixed-order passes: per chunk of
-// kColRows tokens a column sum (reads of a row are contiguous across the
-// block), then one block per expert reduces the chunk sums with a fixed tree
-// (in bwd_final_reduce_kernel).
-__global__ __launch_bounds__(128) void colsum_rows_kernel(const uint16_t* __restrict__ dL, float* __restrict__ part,
-                                                          int T, int E) {
-  const int r0 = blockIdx.x * kColRows, r1 = min(T, r0 + kColRows);
-  for (int c = threadIdx.x; c < E; c += 128) {
-    float s = 0.f;
-#pragma unroll 8
-    for (int r = r0; r < r1; ++r) s += bf2f(dL[(size_t)r * E + c]);
-    part[(size_t)blockIdx.x * E + c] = s;
-  }
 }
 
 // ---------------------------------------------------------------- expert biases
@@ -438,13 +427,13 @@ hipError_t launch_f32_to_bf16(const float* in, uint16_t* out, size_t n, hipStrea
   return hipGetLastError();
 }
 
-hipError_t launch_agg_dx(const uint16_t* dXt, const float* dS, const uint16_t* WrT, const moe_routing& r, uint16_t* dX,
+hipError_t launch_agg_dx(const uint16_t* dXt, const float* dS, int ds_parts, const uint16_t* WrT, const moe_routing& r, uint16_t* dX,
                          uint16_t* dL, int T, int d, int E, hipStream_t s) {
   const int slices = agg_slices(d), nc = ((d + 511) / 512 + slices - 1) / slices;
   const dim3 grid((unsigned)((T + 3) / 4) * slices), block(256);
 #define SMOE_AGG(N)                                                                                                   \
   if (nc == N)                                                                                                        \
-  agg_dx_kernel<N><<<grid, block, 0, s>>>(dXt, dS, WrT, r.tok_offsets, r.tok_rows, r.row_expert, r.row_w, dX, dL, T, \
+  agg_dx_kernel<N><<<grid, block, 0, s>>>(dXt, dS, ds_parts, WrT, r.tok_offsets, r.tok_rows, r.row_expert, r.row_w, dX, dL, T, \
                                           d, E, slices)
   SMOE_AGG(1);
   SMOE_AGG(2);
@@ -458,14 +447,5 @@ hipError_t launch_reduce_rowparts(const float* part, float* out, int rows, int p
   reduce_rowparts_kernel<<<dim3((rows + 255) / 256), dim3(256), 0, s>>>(part, out, rows, parts);
   return hipGetLastError();
 }
-
-int colsum_chunks(int T) { return (T + kColRows - 1) / kColRows; }
-
-hipError_t launch_colsum_rows(const uint16_t* dL, float* part, int T, int E, hipStream_t s) {
-  const int chunks = colsum_chunks(T);
-  if (chunks > 0) colsum_rows_kernel<<<dim3(chunks), dim3(128), 0, s>>>(dL, part, T, E);
-  return hipGetLastError();
-}
-
 
 }  // namespace smoe

@@ -136,7 +136,7 @@ hipError_t launch_mtiles(const int32_t* offsets, int E, int32_t* out, hipStream_
 // over 2048: the step takes 1.013 instead of 1.106 ms since they are left
 // whole; a margin of 5/4 Kc without the mean made the T = 32768, E = 256 layer
 // with Zipf-distributed experts 1% slower).  A split expert's chunks
-// write fp32 partials that dw_reduce_kernel sums in chunk order, the others
+// write fp32 partials that bwd_final_reduce_kernel sums in chunk order, the others
 // store bf16 directly.  The entries (chunks and unsplit experts) are sorted
 // by length, longest first (a counting sort on k steps), and dealt round-robin
 // to the 8 XCDs; each XCD's entries are contiguous in the list, so its 32
@@ -265,8 +265,8 @@ __global__ __launch_bounds__(kMTilesThreads) void bwd_lists_kernel(const int32_t
   }
 }
 
-// partials of split experts -> bf16 dW: chunk slabs summed in chunk order
-// workgroup (bx, by) of a gx x gy grid
+// Partials of split experts -> bf16 dW: chunk slabs summed in chunk order
+// (workgroup (bx, by) of a gx x gy grid).
 __device__ __forceinline__ void dw_reduce_body(const int32_t* __restrict__ klist, const float* __restrict__ part,
                                                uint16_t* __restrict__ dW, int E, int64_t MN, int bx, int by, int gx,
                                                int gy) {
@@ -289,61 +289,34 @@ __device__ __forceinline__ void dw_reduce_body(const int32_t* __restrict__ klist
   }
 }
 
-__global__ __launch_bounds__(256) void dw_reduce_kernel(const int32_t* __restrict__ klist, const float* __restrict__ part,
-                                                        uint16_t* __restrict__ dW, int E, int64_t MN) {
-  dw_reduce_body(klist, part, dW, E, MN, blockIdx.x, blockIdx.y, gridDim.x, gridDim.y);
-}
-
-static void dw_reduce_grid(int64_t MN, int slabs, int* gx, int* gy) {
-  *gx = (int)std::min<int64_t>((MN / 4 + 255) / 256, 64);
-  // split experts are looped over: most calls have none, and a grid sized for
-  // every possible one would mostly launch workgroups that exit at once
-  *gy = slabs > 0 ? std::min(slabs / 2, 8) : 0;
-}
-
-// The backward's last reductions in one launch: workgroups [0, nd) sum the
-// dW1 chunk slabs of split experts (as dw_reduce_kernel), the next nr the dW_r
-// split-K partials (fixed split order), the last ne the dbias chunk sums of
-// one expert each (fixed tree).
-__global__ __launch_bounds__(256) void bwd_final_reduce_kernel(const int32_t* __restrict__ klist1,
-                                                               const float* __restrict__ part1,
-                                                               uint16_t* __restrict__ dW1, int64_t MN1, int gx1,
-                                                               int gy1, const float* __restrict__ dwr_part,
-                                                               float* __restrict__ dWr, int n, int splits, int nr,
-                                                               const float* __restrict__ cs_part,
-                                                               float* __restrict__ dbias, int chunks, int E) {
-  const int nd = gx1 * gy1;
-  int b = blockIdx.x;
-  if (b < nd) {
-    dw_reduce_body(klist1, part1, dW1, E, MN1, b % gx1, b / gx1, gx1, gy1);
-    return;
-  }
-  b -= nd;
-  if (b < nr) {
-    const int i = b * 256 + threadIdx.x;
-    if (i >= n) return;
-    float s = 0.f;
-    for (int k = 0; k < splits; ++k) s += dwr_part[(size_t)k * n + i];
-    dWr[i] = s;
-    return;
-  }
-  __shared__ float red[4];
-  const int e = b - nr;
-  float s = 0.f;
-  for (int i = threadIdx.x; i < chunks; i += 256) s += cs_part[(size_t)i * E + e];
-  s = wave_sum(s);
-  if (lane_id() == 0) red[threadIdx.x >> 6] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) dbias[e] = (red[0] + red[1]) + (red[2] + red[3]);
-}
-
-hipError_t launch_dw_reduce(const int32_t* klist, const float* part, uint16_t* dW, int E, int64_t MN, int slabs,
-                            hipStream_t s) {
-  if (slabs <= 0) return hipSuccess;
+// The backward's last reductions in one launch: the first workgroups sum the
+// dW2 and then the dW1 chunk slabs of split experts, the next nr the dW_r
+// split-K partials, the rest the dbias ones (all in a fixed order).
+struct DwGrid {
   int gx, gy;
-  dw_reduce_grid(MN, slabs, &gx, &gy);
-  dw_reduce_kernel<<<dim3(gx, gy), dim3(256), 0, s>>>(klist, part, dW, E, MN);
-  return hipGetLastError();
+  int64_t MN;
+  __device__ __host__ int blocks() const { return gx * gy; }
+};
+__global__ __launch_bounds__(256) void bwd_final_reduce_kernel(const FinalReduceArgs a, DwGrid g2, DwGrid g1, int nr) {
+  int b = blockIdx.x;
+  if (b < g2.blocks()) {
+    dw_reduce_body(a.klist2, a.part2, a.dW2, a.E, g2.MN, b % g2.gx, b / g2.gx, g2.gx, g2.gy);
+    return;
+  }
+  b -= g2.blocks();
+  if (b < g1.blocks()) {
+    dw_reduce_body(a.klist1, a.part1, a.dW1, a.E, g1.MN, b % g1.gx, b / g1.gx, g1.gx, g1.gy);
+    return;
+  }
+  b -= g1.blocks();
+  const bool bias = b >= nr;
+  const int n = bias ? a.E : a.d * a.E, i = (bias ? b - nr : b) * 256 + threadIdx.x;
+  if (i >= n) return;
+  const float* part = bias ? a.dbias_part : a.dwr_part;
+  float s = 0.f;
+#pragma unroll 4
+  for (int k = 0; k < a.splits; ++k) s += part[(size_t)k * n + i];
+  (bias ? a.dbias : a.dWr)[i] = s;
 }
 
 // A varlen-K tile from the k-chunk list: entry = id / (tiles per entry).
@@ -1424,19 +1397,31 @@ struct OpDW1 {
   }
 };
 
-// dW_r[d,E] = X^T dL, split over token chunks into fp32 partials
+// dW_r[d,E] = X^T dL, split over token chunks into fp32 partials.  dbias = the
+// column sums of dL is one more row of the product: the last m-tile reads ones in
+// the place of X (every k row the same 256 bytes) and stores its first row.  As
+// a pass of its own over dL it took a launch of 5 us at any size.
+__device__ const uint32_t g_ones_page[64] __attribute__((aligned(256))) = {
+#define SMOE_ONES8 0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u
+    SMOE_ONES8, SMOE_ONES8, SMOE_ONES8, SMOE_ONES8, SMOE_ONES8, SMOE_ONES8, SMOE_ONES8, SMOE_ONES8
+#undef SMOE_ONES8
+};
 template <class Cfg_>
 struct OpDWr {
   using Cfg = Cfg_;
   static constexpr int M_MODE = KOUTER, N_MODE = KOUTER;
   static constexpr int EPI_LDS = 0;
-  struct Params { DWrArgs a; };
+  static_assert(Cfg::BM * 2 <= (int)sizeof(g_ones_page), "a k row of ones");
+  struct Params { DWrArgs a; int mtn; };  // mtn: m-tiles, d / BM of X (with part) and one of ones (with bias_part)
   static __device__ int count(const Params& p, int*) {
-    return p.a.splits * (p.a.d / Cfg::BM) * ((p.a.E + Cfg::BN - 1) / Cfg::BN);
+    return p.a.splits * p.mtn * ((p.a.E + Cfg::BN - 1) / Cfg::BN);
+  }
+  static __device__ bool ones(const Params& p, const TileInfo& ti) {
+    return p.a.bias_part && ti.m0 == (p.mtn - 1) * Cfg::BM;
   }
   static __device__ bool tile(const Params& p, int id, TileInfo& ti, int*) {
-    const int mtn = p.a.d / Cfg::BM, ntn = (p.a.E + Cfg::BN - 1) / Cfg::BN;
-    const int split = id / (mtn * ntn), rem = id % (mtn * ntn);
+    const int ntn = (p.a.E + Cfg::BN - 1) / Cfg::BN;
+    const int split = id / (p.mtn * ntn), rem = id % (p.mtn * ntn);
     ti.e = split;
     ti.m0 = (rem / ntn) * Cfg::BM;
     ti.n0 = (rem % ntn) * Cfg::BN;
@@ -1448,17 +1433,22 @@ struct OpDWr {
     return true;
   }
   static __device__ void init_m(const Params& p, const TileInfo& ti, KOuterSide<Cfg::BM, Cfg::BK, Cfg::NW>& s) {
-    s.init(p.a.X, p.a.d, nullptr, ti.k_begin, ti.k_len, p.a.d, ColOffset{ti.m0});
+    if (ones(p, ti))
+      s.init((const uint16_t*)g_ones_page, 0, nullptr, ti.k_begin, ti.k_len, Cfg::BM, ColOffset{0});
+    else
+      s.init(p.a.X, p.a.d, nullptr, ti.k_begin, ti.k_len, p.a.d, ColOffset{ti.m0});
   }
   static __device__ void init_n(const Params& p, const TileInfo& ti, KOuterSide<Cfg::BN, Cfg::BK, Cfg::NW>& s) {
     s.init(p.a.dL, p.a.E, nullptr, ti.k_begin, ti.k_len, p.a.E, ColOffset{ti.n0});
   }
   static __device__ void epilogue(const Params& p, const TileInfo& ti, Acc<Cfg>& t, char*) {
-    float* out = p.a.part + (size_t)ti.e * p.a.d * p.a.E;
+    const bool sums = ones(p, ti);
+    float* out = sums ? p.a.bias_part + (size_t)ti.e * p.a.E : p.a.part + ((size_t)ti.e * p.a.d + ti.m0) * p.a.E;
 #pragma unroll
     for (int i = 0; i < Cfg::RM; ++i) {
       const int m = t.m_of(i);
-      float* o = out + (size_t)(ti.m0 + m) * p.a.E;
+      if (sums && m != 0) continue;
+      float* o = out + (size_t)m * p.a.E;
 #pragma unroll
       for (int j = 0; j < Cfg::RN; ++j)
 #pragma unroll
@@ -1624,14 +1614,12 @@ using W64x256 = GemmCfg<64, 256, 2, 4, 2>;
 using W128x128 = GemmCfg<128, 128, 4, 2, 2, kBK, 2>;
 using W64x128 = GemmCfg<64, 128, 2, 4, 2, kBK, 2>;
 
-// slabs of one weight-gradient GEMM: at most kDwSlabs, within kDwSlabBytes
-int dw_slabs(int64_t mn) {
+// slabs of one weight-gradient GEMM: at most kDwSlabs, within kDwSlabBytes; none
+// where no expert can exceed the shortest chunk (it has at most T rows)
+int dw_slabs(int T, int64_t mn) {
+  if (T <= kKcMin) return 0;
   const int64_t b = kDwSlabBytes / (mn * 4);
   return (int)std::min<int64_t>(kDwSlabs, b) & ~1;
-}
-size_t dw_part_bytes(int d, int n) {
-  const int64_t mn = (int64_t)d * n;
-  return (size_t)std::max<int64_t>(dw_slabs(2 * mn) * 2 * mn, dw_slabs(mn) * mn) * 4;
 }
 
 // tile shapes of the weight-gradient GEMMs (their k-chunk lists are built
@@ -1654,7 +1642,7 @@ static int kchunk_keep_whole(int E, int tpe) {
   return 4 * tiles >= 3 * rounds * cus;
 }
 
-hipError_t launch_bwd_lists(const int32_t* offsets, int E, int d, int n, int32_t* mtiles, int32_t* klist2,
+hipError_t launch_bwd_lists(const int32_t* offsets, int T, int E, int d, int n, int32_t* mtiles, int32_t* klist2,
                             int32_t* klist1, const uint16_t* Wr, uint16_t* WrT, hipStream_t s) {
   if (E > 4096) return hipErrorInvalidValue;
   int bm2, bn2, bm1, bn1;
@@ -1662,61 +1650,61 @@ hipError_t launch_bwd_lists(const int32_t* offsets, int E, int d, int n, int32_t
   dw1_tile(d, n, E, &bm1, &bn1);
   const int tpe2 = (n / bm2) * (d / bn2), tpe1 = (d / bm1) * (2 * n / bn1);
   const int tr_blocks = Wr ? (d * E + kMTilesThreads - 1) / kMTilesThreads : 0;
-  bwd_lists_kernel<<<3 + tr_blocks, kMTilesThreads, 0, s>>>(offsets, E, mtiles, tpe2, dw_slabs((int64_t)n * d),
+  bwd_lists_kernel<<<3 + tr_blocks, kMTilesThreads, 0, s>>>(offsets, E, mtiles, tpe2, dw_slabs(T, (int64_t)n * d),
                                                            kchunk_keep_whole(E, tpe2), klist2, tpe1,
-                                                           dw_slabs((int64_t)d * 2 * n), kchunk_keep_whole(E, tpe1),
+                                                           dw_slabs(T, (int64_t)d * 2 * n), kchunk_keep_whole(E, tpe1),
                                                            klist1, Wr, WrT, d);
   return hipGetLastError();
 }
 
-// the GEMM over the k-chunk list, then (if reduce) the partials of split experts
+// the GEMM over the k-chunk list (its split experts are summed by
+// launch_bwd_final_reduce)
 template <class Op, class Args>
-static hipError_t run_dw(const Args& a, int M, int N, uint16_t* dW, bool reduce, hipStream_t s) {
+static hipError_t run_dw(const Args& a, int M, int N, hipStream_t s) {
   using Cfg = typename Op::Cfg;
   const int tpe = (M / Cfg::BM) * (N / Cfg::BN);
-  const int slabs = dw_slabs((int64_t)M * N);
-  hipError_t err = run<Op>({a}, pad8((a.E + slabs) * tpe), s);
-  if (err != hipSuccess || !reduce) return err;
-  return launch_dw_reduce(a.klist, a.part, dW, a.E, (int64_t)M * N, slabs, s);
+  return run<Op>({a}, pad8((a.E + dw_slabs(a.T, (int64_t)M * N)) * tpe), s);
 }
 
 hipError_t launch_dw2(const DW2Args& a, hipStream_t s) {
   int bm, bn;
   dw2_tile(a.d, a.n, a.E, &bm, &bn);
   if (bn == 256) {
-    if (bm == 256) return run_dw<OpDW2<W256x256>>(a, a.n, a.d, a.dW2, true, s);
-    if (bm == 128) return run_dw<OpDW2<W128x256>>(a, a.n, a.d, a.dW2, true, s);
-    return run_dw<OpDW2<W64x256>>(a, a.n, a.d, a.dW2, true, s);
+    if (bm == 256) return run_dw<OpDW2<W256x256>>(a, a.n, a.d, s);
+    if (bm == 128) return run_dw<OpDW2<W128x256>>(a, a.n, a.d, s);
+    return run_dw<OpDW2<W64x256>>(a, a.n, a.d, s);
   }
-  if (bm == 128) return run_dw<OpDW2<W128x128>>(a, a.n, a.d, a.dW2, true, s);
-  return run_dw<OpDW2<W64x128>>(a, a.n, a.d, a.dW2, true, s);
+  if (bm == 128) return run_dw<OpDW2<W128x128>>(a, a.n, a.d, s);
+  return run_dw<OpDW2<W64x128>>(a, a.n, a.d, s);
 }
 
 hipError_t launch_dw1(const DW1Args& a, hipStream_t s) {
   int bm, bn;
   dw1_tile(a.d, a.n, a.E, &bm, &bn);
-  // its split experts are summed by launch_bwd_final_reduce
-  if (bm == 256) return run_dw<OpDW1<W256x256>>(a, a.d, 2 * a.n, a.dW1, false, s);
-  return run_dw<OpDW1<W128x128>>(a, a.d, 2 * a.n, a.dW1, false, s);
+  if (bm == 256) return run_dw<OpDW1<W256x256>>(a, a.d, 2 * a.n, s);
+  return run_dw<OpDW1<W128x128>>(a, a.d, 2 * a.n, s);
 }
 
-hipError_t launch_bwd_final_reduce(const int32_t* klist1, const float* part1, uint16_t* dW1, int d, int n,
-                                   const float* dwr_part, float* dWr, int splits, const float* cs_part, float* dbias,
-                                   int T, int E, hipStream_t s) {
-  const int64_t MN1 = (int64_t)d * 2 * n;
-  int gx1, gy1;
-  dw_reduce_grid(MN1, dw_slabs(MN1), &gx1, &gy1);
-  const int nr = dWr ? (d * E + 255) / 256 : 0, ne = dbias ? E : 0;
-  const int blocks = gx1 * gy1 + nr + ne;
+static DwGrid dw_reduce_grid(int T, int64_t MN) {
+  const int slabs = dw_slabs(T, MN);
+  // split experts are looped over: most calls have none, and a grid sized for
+  // every possible one would mostly launch workgroups that exit at once
+  return {(int)std::min<int64_t>((MN / 4 + 255) / 256, 64), std::min(slabs / 2, 8), MN};
+}
+
+hipError_t launch_bwd_final_reduce(const FinalReduceArgs& a, hipStream_t s) {
+  const DwGrid g2 = dw_reduce_grid(a.T, (int64_t)a.n * a.d), g1 = dw_reduce_grid(a.T, (int64_t)a.d * 2 * a.n);
+  const int nr = a.dWr ? (a.d * a.E + 255) / 256 : 0, ne = a.dbias ? (a.E + 255) / 256 : 0;
+  const int blocks = g2.blocks() + g1.blocks() + nr + ne;
   if (blocks == 0) return hipSuccess;
-  bwd_final_reduce_kernel<<<dim3(blocks), dim3(256), 0, s>>>(klist1, part1, dW1, MN1, gx1, gy1, dwr_part, dWr, d * E,
-                                                             splits, nr, cs_part, dbias, colsum_chunks(T), E);
+  bwd_final_reduce_kernel<<<dim3(blocks), dim3(256), 0, s>>>(a, g2, g1, nr);
   return hipGetLastError();
 }
 
 int dwr_splits(int T, int d, int E) {
-  // the output tiles of launch_dwr's configuration: 128 x 64, 128 x 128 or 128 x 256
-  const int tiles = (d / 128) * (E <= 128 ? 1 : (E + 255) / 256);
+  // the output tiles of launch_dwr's configuration: 128 x 64, 128 x 128 or 128
+  // x 256, with the row block of the column sums
+  const int tiles = (d / 128 + 1) * (E <= 128 ? 1 : (E + 255) / 256);
   int s = 256 / tiles;  // at most one tile per CU: a second round would double the time
   const int max_s = (T + 255) / 256;  // at least 256 tokens per split
   if (s > max_s) s = max_s;
@@ -1724,15 +1712,10 @@ int dwr_splits(int T, int d, int E) {
 }
 
 hipError_t launch_dwr(const DWrArgs& a, hipStream_t s) {
-  hipError_t err;
-  const int mtn = a.d / 128;
-  if (a.E <= 64)
-    err = run<OpDWr<C128x64>>({a}, a.splits * mtn, s);
-  else if (a.E <= 128)
-    err = run<OpDWr<C128x128>>({a}, a.splits * mtn, s);
-  else
-    err = run<OpDWr<C128x256>>({a}, a.splits * mtn * ((a.E + 255) / 256), s);
-  return err;  // the partials are summed by launch_bwd_final_reduce
+  const int mtn = (a.part ? a.d / 128 : 0) + (a.bias_part ? 1 : 0);
+  if (a.E <= 64) return run<OpDWr<C128x64>>({a, mtn}, a.splits * mtn, s);
+  if (a.E <= 128) return run<OpDWr<C128x128>>({a, mtn}, a.splits * mtn, s);
+  return run<OpDWr<C128x256>>({a, mtn}, a.splits * mtn * ((a.E + 255) / 256), s);
 }
 
 }  // namespace smoe

@@ -113,35 +113,39 @@ hipError_t launch_dxt(const DXtArgs& a, hipStream_t s);
 
 // Weight gradients (varlen K over each expert's rows).  klist: the GEMM's
 // k-chunk list (kchunks_bytes(E) bytes, written by launch_bwd_lists); part:
-// dw_part_bytes(d, n) bytes of fp32 partials for experts split into row
-// chunks.
+// dw_part_bytes bytes of fp32 partials for experts split into row chunks, which
+// launch_bwd_final_reduce sums.
 constexpr int kDwSlabs = 128;                                // partial slabs per GEMM at most
 constexpr int64_t kDwSlabBytes = (int64_t)256 << 20;         // and at most this many bytes
 size_t kchunks_bytes(int E);
-size_t dw_part_bytes(int d, int n);
-int dw_slabs(int64_t mn);
+// slabs of a GEMM with mn outputs per expert (0: no expert is split)
+int dw_slabs(int T, int64_t mn);
+inline size_t dw_part_bytes(int T, int64_t mn) { return (size_t)dw_slabs(T, mn) * mn * 4; }
 // the backward's m-tile list (as launch_mtiles) and the k-chunk lists of dW2
 // and dW1, in one launch; with Wr non-null the same launch writes WrT[e][i] =
 // Wr[i][e] (the dX aggregation's router term reads W_r by expert)
-hipError_t launch_bwd_lists(const int32_t* offsets, int E, int d, int n, int32_t* mtiles, int32_t* klist2,
+hipError_t launch_bwd_lists(const int32_t* offsets, int T, int E, int d, int n, int32_t* mtiles, int32_t* klist2,
                             int32_t* klist1, const uint16_t* Wr, uint16_t* WrT, hipStream_t s);
 
 struct DW2Args {
   const uint16_t* Ap; const uint16_t* dO; const int32_t* offsets; const int32_t* row_token; uint16_t* dW2;
-  int d, n, E;
+  int T, d, n, E;
   int32_t* klist; float* part;
 };
 hipError_t launch_dw2(const DW2Args& a, hipStream_t s);
 
 struct DW1Args {
   const uint16_t* X; const uint16_t* dH; const int32_t* offsets; const int32_t* row_token; uint16_t* dW1;
-  int d, n, E;
+  int T, d, n, E;
   int32_t* klist; float* part;
 };
 hipError_t launch_dw1(const DW1Args& a, hipStream_t s);
 
+// dW_r = X^T dL and dbias (column sums of dL), split over token chunks: partials
+// part [splits][d][E] (null: no dW_r) and bias_part [splits][E] (null: no dbias),
+// summed by launch_bwd_final_reduce
 struct DWrArgs {
-  const uint16_t* X; const uint16_t* dL; float* part; float* dWr; int T, d, E, splits;
+  const uint16_t* X; const uint16_t* dL; float* part; float* bias_part; int T, d, E, splits;
 };
 int dwr_splits(int T, int d, int E);
 hipError_t launch_dwr(const DWrArgs& a, hipStream_t s);
@@ -172,18 +176,19 @@ hipError_t launch_tok_slots(const moe_routing& r, int T, int P_bound, int32_t* d
 hipError_t launch_agg_o_contig(const uint16_t* Yt, const moe_routing& r, uint16_t* O, int T, int d, hipStream_t s);
 hipError_t launch_fill_f32(float* p, size_t n, hipStream_t s);
 hipError_t launch_f32_to_bf16(const float* in, uint16_t* out, size_t n, hipStream_t s);
-hipError_t launch_agg_dx(const uint16_t* dXt, const float* dS, const uint16_t* WrT, const moe_routing& r, uint16_t* dX,
+// dS of row r: the sum of its ds_parts values at dS[r * ds_parts]
+hipError_t launch_agg_dx(const uint16_t* dXt, const float* dS, int ds_parts, const uint16_t* WrT, const moe_routing& r, uint16_t* dX,
                          uint16_t* dL, int T, int d, int E, hipStream_t s);
 hipError_t launch_reduce_rowparts(const float* part, float* out, int rows, int parts, hipStream_t s);
-// dbias = column sums of dL [T][E]: per-chunk sums into part (colsum_chunks(T)
-// * E floats), then launch_bwd_final_reduce sums them.  That launch also sums
-// the dW1 chunk slabs of split experts (launch_dw1 leaves them) and the dW_r
-// split-K partials (dwr_part: splits x d x E floats); dWr and dbias may be null.
-int colsum_chunks(int T);
-hipError_t launch_colsum_rows(const uint16_t* dL, float* part, int T, int E, hipStream_t s);
-hipError_t launch_bwd_final_reduce(const int32_t* klist1, const float* part1, uint16_t* dW1, int d, int n,
-                                   const float* dwr_part, float* dWr, int splits, const float* cs_part, float* dbias,
-                                   int T, int E, hipStream_t s);
+// The backward's last reductions: the chunk slabs of split experts in dW2 and
+// dW1 (klist*, part*), the dW_r split-K partials and the dbias partials (dWr and
+// dbias may be null).
+struct FinalReduceArgs {
+  const int32_t* klist2; const float* part2; uint16_t* dW2;
+  const int32_t* klist1; const float* part1; uint16_t* dW1;
+  const float* dwr_part; float* dWr; const float* dbias_part; float* dbias; int T, d, n, E, splits;
+};
+hipError_t launch_bwd_final_reduce(const FinalReduceArgs& a, hipStream_t s);
 
 // timing hooks (moe_abi.cpp)
 void prof_begin(int kernel_class, hipStream_t s);

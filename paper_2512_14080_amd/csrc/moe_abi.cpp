@@ -133,7 +133,8 @@ struct BwdWs {
   float* dbias_part;
   int32_t* klist2;  // k-chunk lists of the weight gradients
   int32_t* klist1;
-  float* dw_part;   // fp32 partials of row-chunked experts
+  float* dw2_part;  // fp32 partials of row-chunked experts
+  float* dw1_part;
   uint16_t* b2s;    // expert-bias dS term: b2^T as bf16 high/low parts [d][2E]
   float* bq;        // and <dO_t, b2_e> in those two parts [T][2E]
   float* colsum_part;  // per m-tile column sums of the expert-bias gradients
@@ -174,10 +175,11 @@ size_t bwd_layout(const moe_dims& m, int64_t cap, char* base, BwdWs* w) {
   off = carve(base, off, (size_t)m.T * m.E * 2, w ? (void**)&w->dL : nullptr);
   off = carve(base, off, (size_t)m.E * m.d * 2, w ? (void**)&w->WrT : nullptr);
   off = carve(base, off, (size_t)splits * m.d * m.E * 4, w ? (void**)&w->dWr_part : nullptr);
-  off = carve(base, off, (size_t)smoe::colsum_chunks(m.T) * m.E * 4, w ? (void**)&w->dbias_part : nullptr);
+  off = carve(base, off, (size_t)splits * m.E * 4, w ? (void**)&w->dbias_part : nullptr);
   off = carve(base, off, smoe::kchunks_bytes(m.E), w ? (void**)&w->klist2 : nullptr);
   off = carve(base, off, smoe::kchunks_bytes(m.E), w ? (void**)&w->klist1 : nullptr);
-  off = carve(base, off, smoe::dw_part_bytes(m.d, m.n), w ? (void**)&w->dw_part : nullptr);
+  off = carve(base, off, smoe::dw_part_bytes(m.T, (int64_t)m.n * m.d), w ? (void**)&w->dw2_part : nullptr);
+  off = carve(base, off, smoe::dw_part_bytes(m.T, (int64_t)m.d * 2 * m.n), w ? (void**)&w->dw1_part : nullptr);
   off = carve(base, off, (size_t)m.d * 2 * m.E * 2, w ? (void**)&w->b2s : nullptr);
   off = carve(base, off, (size_t)m.T * 2 * m.E * 4, w ? (void**)&w->bq : nullptr);
   off = carve(base, off, smoe::colsum_part_bytes(cap, m.E, m.d, m.n), w ? (void**)&w->colsum_part : nullptr);
@@ -618,7 +620,7 @@ int moe_bwd(moe_dims m, const moe_bf16* dO, const moe_bf16* X, const moe_bf16* H
   float* dS_out = dS ? dS : w.dS;
   const int64_t rows = (int64_t)m.T * m.K;
   const int nnt = smoe::dh_n_tiles(m.n, rows, m.E);
-  HIP_TRY(smoe::launch_bwd_lists(r->offsets, m.E, m.d, m.n, w.mtiles, w.klist2, w.klist1, Wr, Wr ? w.WrT : nullptr,
+  HIP_TRY(smoe::launch_bwd_lists(r->offsets, m.T, m.E, m.d, m.n, w.mtiles, w.klist2, w.klist1, Wr, Wr ? w.WrT : nullptr,
                                  stream),
           "tile lists and W_r transpose");
   if (b2) {
@@ -631,20 +633,28 @@ int moe_bwd(moe_dims m, const moe_bf16* dO, const moe_bf16* X, const moe_bf16* H
                           r->capacity, rows, w.mtiles, b2 ? w.bq : nullptr},
                          stream),
          "dH");
-  if (nnt > 1) HIP_TRY(smoe::launch_reduce_rowparts(w.dS_part, dS_out, r->capacity, nnt, stream), "dS reduce");
-  LAUNCH(MOE_KC_DW2, smoe::launch_dw2({w.Ap, dO, r->offsets, r->row_token, dW2, m.d, m.n, m.E, w.klist2, w.dw_part}, stream), "dW2");
+  // dS in parts (one per N tile of dH): a few are summed where they are read,
+  // unless the caller wants dS itself
+  const bool ds_in_parts = nnt > 1 && nnt <= 4 && !dS;
+  if (nnt > 1 && !ds_in_parts)
+    HIP_TRY(smoe::launch_reduce_rowparts(w.dS_part, dS_out, r->capacity, nnt, stream), "dS reduce");
+  LAUNCH(MOE_KC_DW2, smoe::launch_dw2({w.Ap, dO, r->offsets, r->row_token, dW2, m.T, m.d, m.n, m.E, w.klist2, w.dw2_part}, stream), "dW2");
   LAUNCH(MOE_KC_DXT, smoe::launch_dxt({w.dH, W1, r->offsets, w.dXt, m.d, m.n, m.E, r->capacity, rows, w.mtiles}, stream),
          "dX~");
-  LAUNCH(MOE_KC_DW1, smoe::launch_dw1({X, w.dH, r->offsets, r->row_token, dW1, m.d, m.n, m.E, w.klist1, w.dw_part}, stream), "dW1");
+  LAUNCH(MOE_KC_DW1, smoe::launch_dw1({X, w.dH, r->offsets, r->row_token, dW1, m.T, m.d, m.n, m.E, w.klist1, w.dw1_part}, stream), "dW1");
   LAUNCH(MOE_KC_AGG_DX,
-         smoe::launch_agg_dx(w.dXt, dS_out, Wr ? w.WrT : nullptr, *r, dX, Wr ? w.dL : nullptr, m.T, m.d, m.E, stream),
+         smoe::launch_agg_dx(w.dXt, ds_in_parts ? w.dS_part : dS_out, ds_in_parts ? nnt : 1, Wr ? w.WrT : nullptr, *r, dX, Wr ? w.dL : nullptr, m.T, m.d, m.E, stream),
          "dX aggregation");
   const int splits = smoe::dwr_splits(m.T, m.d, m.E);
-  if (dWr) LAUNCH(MOE_KC_DWR, smoe::launch_dwr({X, w.dL, w.dWr_part, dWr, m.T, m.d, m.E, splits}, stream), "dW_r");
-  if (dbias) HIP_TRY(smoe::launch_colsum_rows(w.dL, w.dbias_part, m.T, m.E, stream), "dbias");
-  HIP_TRY(smoe::launch_bwd_final_reduce(w.klist1, w.dw_part, dW1, m.d, m.n, w.dWr_part, dWr, splits, w.dbias_part,
-                                        dbias, m.T, m.E, stream),
-          "final reductions (dW1 split experts, dW_r, dbias)");
+  if (dWr || dbias)
+    LAUNCH(MOE_KC_DWR,
+           smoe::launch_dwr({X, w.dL, dWr ? w.dWr_part : nullptr, dbias ? w.dbias_part : nullptr, m.T, m.d, m.E, splits},
+                            stream),
+           "dW_r and dbias");
+  HIP_TRY(smoe::launch_bwd_final_reduce({w.klist2, w.dw2_part, dW2, w.klist1, w.dw1_part, dW1, w.dWr_part, dWr,
+                                         w.dbias_part, dbias, m.T, m.d, m.n, m.E, splits},
+                                        stream),
+          "final reductions (split experts' weight gradients, dW_r, dbias)");
   if (eb && (eb->db1 || eb->db2))
     HIP_TRY(smoe::launch_expert_colsum({w.dH, dO, r->offsets, r->row_token, r->row_w, w.mtiles, w.colsum_part, eb->db1,
                                         eb->db2, m.d, m.n, m.E, r->capacity},
