@@ -57,6 +57,7 @@ struct TileInfo {
   int m0;       // first m of the tile inside the group
   int mrows;    // valid m rows in the tile (<= BM)
   int n0;       // first n of the tile
+  int ncols;    // valid n columns in the tile (<= BN, a multiple of 64)
   int row_base; // global row of m = 0 for varlen-M (expert offset + m0)
   int k_begin;  // first k (global row index for varlen-K)
   int k_len;    // reduction length
@@ -405,8 +406,8 @@ template <class Op>
 struct IdxLds<Op, std::void_t<decltype(Op::IDX_LDS)>> : std::integral_constant<int, Op::IDX_LDS> {};
 
 // Ops define  static constexpr int EPI_STORES : a lower bound on the vector
-// memory instructions each wave issues in the epilogue of a full tile (all
-// BM rows valid).  A wave's vector memory operations retire in issue order,
+// memory instructions each wave issues in the epilogue of a full tile (all BM
+// rows and BN columns valid).  A wave's vector memory operations retire in issue order,
 // loads and stores alike, so a wait for stage 0 of a tile only has to leave
 // outstanding the operations issued after it: the other prologue stages and
 // the previous tile's epilogue stores.
@@ -562,8 +563,9 @@ __global__ __launch_bounds__(Op::Cfg::THREADS, Op::Cfg::OCC) void grouped_gemm_k
     const int nk = (ti.k_len + BK - 1) / BK;
     // a wave whose rows all lie past the tile's valid rows skips its MFMAs
     // (it still issues its share of the DMA and joins every barrier); the
-    // weight-gradient GEMMs (k outer on both sides) always have full tiles
-    const bool active = wm0 < ti.mrows;
+    // weight-gradient GEMMs run all waves of their few partial tiles (with both
+    // forms of the k loop in the kernel they spilled)
+    const bool active = kLateSides || wm0 < ti.mrows;
     // gathered k rows: their index loads are younger than the DMA, so only a
     // full drain covers them
     bool gathered = false;
@@ -815,7 +817,7 @@ __global__ __launch_bounds__(Op::Cfg::THREADS, Op::Cfg::OCC) void grouped_gemm_k
       prologue(tn, ms, ns);
     }
     Op::epilogue(p, ti, acc, smem + Cfg::LDS_BYTES);
-    prev_full = ti.mrows == BM;
+    prev_full = ti.mrows == BM && ti.ncols == BN;
     if (idn < 0) break;
     ti = tn;
     acc.zero();

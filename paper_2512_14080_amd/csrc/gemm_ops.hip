@@ -276,14 +276,21 @@ __device__ __forceinline__ void dw_reduce_body(const int32_t* __restrict__ klist
     const i32x4 sp = spl[si];
     const int e = sp[0], first = sp[1], nc = sp[2];
     for (int64_t i = 4 * ((int64_t)bx * 256 + threadIdx.x); i < MN; i += 4 * (int64_t)gx * 256) {
+      // in chunk order, up to four slabs' loads in flight
       f32x4 a = *(const f32x4*)(part + (size_t)first * MN + i);
-      for (int c = 1; c < nc; ++c) {
-        const f32x4 b = *(const f32x4*)(part + (size_t)(first + c) * MN + i);
-        a[0] += b[0];
-        a[1] += b[1];
-        a[2] += b[2];
-        a[3] += b[3];
-      }
+      auto add = [&](auto count, int c) {
+        constexpr int N = decltype(count)::value;
+        f32x4 b[N];
+#pragma unroll
+        for (int u = 0; u < N; ++u) b[u] = *(const f32x4*)(part + (size_t)(first + c + u) * MN + i);
+#pragma unroll
+        for (int u = 0; u < N; ++u)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) a[q] += b[u][q];
+      };
+      int c = 1;
+      for (; c + 4 <= nc; c += 4) add(std::integral_constant<int, 4>{}, c);
+      for (; c < nc; ++c) add(std::integral_constant<int, 1>{}, c);
       *(u32x2*)(dW + (size_t)e * MN + i) = u32x2{pack_bf2(a[0], a[1]), pack_bf2(a[2], a[3])};
     }
   }
@@ -322,14 +329,15 @@ __global__ __launch_bounds__(256) void bwd_final_reduce_kernel(const FinalReduce
 // A varlen-K tile from the k-chunk list: entry = id / (tiles per entry).
 template <int BM, int BN>
 __device__ __forceinline__ bool tile_kchunk(const int32_t* klist, int E, int M, int N, int id, TileInfo& ti) {
-  const int mtn = M / BM, ntn = N / BN;
+  const int mtn = (M + BM - 1) / BM, ntn = (N + BN - 1) / BN;
   const SMOE_CONST i32x4* ent = (const SMOE_CONST i32x4*)(klist + 16);
   const i32x4 t = ent[id / (mtn * ntn)];
   const int rem = id % (mtn * ntn);
   ti.e = t[0];
   ti.m0 = (rem / ntn) * BM;
   ti.n0 = (rem % ntn) * BN;
-  ti.mrows = BM;
+  ti.mrows = min(BM, M - ti.m0);
+  ti.ncols = min(BN, N - ti.n0);
   ti.row_base = t[3];  // partial slab, or -1
   ti.k_begin = t[1];
   ti.k_len = t[2];
@@ -343,14 +351,17 @@ __device__ __forceinline__ void kchunk_xcd_range(const int32_t* klist, int x, in
 
 // fp32 tile of a partial slab [M][ld]
 template <class Cfg>
-__device__ __forceinline__ void store_part_f32(float* out, int64_t ld, int m0, int n0, Acc<Cfg>& t) {
+__device__ __forceinline__ void store_part_f32(float* out, int64_t ld, int m0, int n0, int mrows, int ncols,
+                                               Acc<Cfg>& t) {
 #pragma unroll
   for (int i = 0; i < Cfg::RM; ++i) {
+    if (t.m_of(i) >= mrows) continue;
     float* o = out + (size_t)(m0 + t.m_of(i)) * ld + n0;
 #pragma unroll
     for (int j = 0; j < Cfg::RN; ++j)
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
+        if (t.n_of(j, g) >= ncols) continue;
         f32x4 v;
 #pragma unroll
         for (int q = 0; q < 4; ++q) v[q] = t.acc[i][j][4 * g + q];
@@ -366,7 +377,7 @@ __device__ __forceinline__ void store_part_f32(float* out, int64_t ld, int m0, i
 template <int BM, int BN>
 __device__ __forceinline__ bool tile_varlen_m(const int32_t* mtiles, int N, int K, int id, TileInfo& ti) {
   static_assert(BM == kMTile, "varlen-M tiles are the m-tile list's tiles");
-  const int nnt = N / BN;
+  const int nnt = (N + BN - 1) / BN;
   const bool partial = (id & kPartialTile) != 0;
   id &= kPartialTile - 1;
   const int mt = id / nnt, nt = id % nnt;
@@ -380,6 +391,7 @@ __device__ __forceinline__ bool tile_varlen_m(const int32_t* mtiles, int N, int 
   ti.mrows = t[2];
   ti.row_base = t[3];
   ti.n0 = nt * BN;
+  ti.ncols = min(BN, N - ti.n0);
   ti.k_begin = 0;
   ti.k_len = K;
   return true;
@@ -387,12 +399,12 @@ __device__ __forceinline__ bool tile_varlen_m(const int32_t* mtiles, int N, int 
 
 template <int BN>
 __device__ __forceinline__ int count_varlen_m(const int32_t* mtiles, int N) {
-  return ((const SMOE_CONST i32x4*)mtiles)[0][0] * (N / BN);
+  return ((const SMOE_CONST i32x4*)mtiles)[0][0] * ((N + BN - 1) / BN);
 }
 // tiles of the tail class (partial m-tiles)
 template <int BN>
 __device__ __forceinline__ int count_varlen_m_tail(const int32_t* mtiles, int N) {
-  return ((const SMOE_CONST i32x4*)mtiles)[0][1] * (N / BN);
+  return ((const SMOE_CONST i32x4*)mtiles)[0][1] * ((N + BN - 1) / BN);
 }
 
 template <int BM, int BN>
@@ -405,6 +417,7 @@ __device__ __forceinline__ bool tile_plain_m(int M, int N, int K, int id, TileIn
   ti.mrows = min(BM, M - ti.m0);
   ti.row_base = ti.m0;
   ti.n0 = nt * BN;
+  ti.ncols = min(BN, N - ti.n0);
   ti.k_begin = 0;
   ti.k_len = K;
   return true;
@@ -417,14 +430,17 @@ struct ColOffset {
 
 // Adds bias[colmap(c)] to every accumulator of tile-local column c (the
 // expert biases of the projections).  A lane's accumulator block (j, g) holds
-// four consecutive columns, which colmap keeps consecutive.
+// four consecutive columns, which colmap keeps consecutive; columns from `cols`
+// on (past the matrix, never stored) are left alone.
 template <class Cfg, class ColMap>
-__device__ __forceinline__ void add_col_bias(Acc<Cfg>& t, const float* bias, ColMap colmap) {
+__device__ __forceinline__ void add_col_bias(Acc<Cfg>& t, const float* bias, ColMap colmap, int cols) {
 #pragma unroll
   for (int j = 0; j < Cfg::RN; ++j)
 #pragma unroll
     for (int g = 0; g < 4; ++g) {
-      const f32x4 b = *(const f32x4*)(bias + colmap(t.n_of(j, g)));
+      const int c = colmap(t.n_of(j, g));
+      if (c >= cols) continue;
+      const f32x4 b = *(const f32x4*)(bias + c);
 #pragma unroll
       for (int i = 0; i < Cfg::RM; ++i)
 #pragma unroll
@@ -837,7 +853,7 @@ __device__ __forceinline__ void store_staged32_split(const char* wh, const char*
 }
 
 template <class Cfg>
-__device__ __forceinline__ void store_rows_bf16(uint16_t* out, int64_t ld, int row_base, int mrows, int n0,
+__device__ __forceinline__ void store_rows_bf16(uint16_t* out, int64_t ld, int row_base, int mrows, int n0, int ncols,
                                                 Acc<Cfg>& t, char* epi) {
   if constexpr (!kStagedStores<Cfg>) {
 #pragma unroll
@@ -847,6 +863,7 @@ __device__ __forceinline__ void store_rows_bf16(uint16_t* out, int64_t ld, int r
       uint16_t* y = out + (size_t)(row_base + m) * ld + n0;
 #pragma unroll
       for (int j = 0; j < Cfg::RN; ++j) {
+        if (t.n_of(j, 0) >= ncols) continue;
         u32x2 v[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g)
@@ -864,6 +881,7 @@ __device__ __forceinline__ void store_rows_bf16(uint16_t* out, int64_t ld, int r
     if (m0 >= mrows) continue;
 #pragma unroll
     for (int j = 0; j + 1 < Cfg::RN; j += 2) {
+      if (t.n_of(j, 0) >= ncols) continue;
       u32x2 v0[4], v1[4];
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
@@ -927,7 +945,7 @@ struct OpUp {
     const int n = p.a.n;
     const int j0 = (ti.n0 / Cfg::BN) * (Cfg::BN / 2);
     const int wn = t.wave_n();
-    if (p.a.b1) add_col_bias<Cfg>(t, p.a.b1 + (size_t)ti.e * (2 * n), ColMap{j0, n});
+    if (p.a.b1) add_col_bias<Cfg>(t, p.a.b1 + (size_t)ti.e * (2 * n), ColMap{j0, n}, 2 * n);
     if constexpr (STAGED) {
       char* wl = epi + (threadIdx.x >> 6) * kStageBytesPerWave;
       const int wm0 = t.m_of(0) - (threadIdx.x & 31);
@@ -939,6 +957,7 @@ struct OpUp {
 #pragma unroll
         for (int j = 0; j < RN / 2; j += 2) {
           const int col = j0 + wn * (Wn / 2) + 32 * j;  // first column of the 64-column pair
+          if (col >= n) continue;
           u32x2 hg[2][4], hu[2][4], ha[2][4];
 #pragma unroll
           for (int q = 0; q < 2; ++q)
@@ -988,6 +1007,7 @@ struct OpUp {
 #pragma unroll
       for (int j = 0; j < RN / 2; ++j) {
         const int col = j0 + wn * (Wn / 2) + 32 * j;  // first column of the 32-column block
+        if (col >= n) continue;
         u32x2 hg[4], hu[4], ha[4];
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -1018,7 +1038,7 @@ struct OpUp {
 // through the 2 KB epilogue area.
 template <class Cfg>
 __device__ __forceinline__ void store_rows_bf16_stage(uint16_t* out, int64_t ld, int row_base, int mrows, int n0,
-                                                      Acc<Cfg>& t, char* epi) {
+                                                      int ncols, Acc<Cfg>& t, char* epi) {
   static_assert(Cfg::RN % 2 == 0 && Cfg::STAGE_BYTES >= Cfg::NW * 4096, "a 4 KB share of the last stage per wave");
   char* st = epi - Cfg::STAGE_BYTES + (threadIdx.x >> 6) * 4096;
   const int wm0 = t.m_of(0) - (threadIdx.x & 31);
@@ -1028,6 +1048,7 @@ __device__ __forceinline__ void store_rows_bf16_stage(uint16_t* out, int64_t ld,
     if (m0 >= mrows) continue;
 #pragma unroll
     for (int j = 0; j + 1 < Cfg::RN; j += 2) {
+      if (t.n_of(j, 0) >= ncols) continue;
       u32x2 v0[4], v1[4];
 #pragma unroll
       for (int g = 0; g < 4; ++g) {
@@ -1046,11 +1067,11 @@ __device__ __forceinline__ void store_rows_bf16_stage(uint16_t* out, int64_t ld,
 // the one-round form where the last stage buffer allows it
 template <class Cfg>
 __device__ __forceinline__ void store_rows_bf16_any(uint16_t* out, int64_t ld, int row_base, int mrows, int n0,
-                                                    Acc<Cfg>& t, char* epi) {
+                                                    int ncols, Acc<Cfg>& t, char* epi) {
   if constexpr (Cfg::RN % 2 == 0 && Cfg::STAGE_BYTES >= Cfg::NW * 4096)
-    store_rows_bf16_stage<Cfg>(out, ld, row_base, mrows, n0, t, epi);
+    store_rows_bf16_stage<Cfg>(out, ld, row_base, mrows, n0, ncols, t, epi);
   else
-    store_rows_bf16<Cfg>(out, ld, row_base, mrows, n0, t, epi);
+    store_rows_bf16<Cfg>(out, ld, row_base, mrows, n0, ncols, t, epi);
 }
 
 // ================================================================== down-proj
@@ -1085,9 +1106,9 @@ struct OpDown {
     s.init(w, p.a.d, nullptr, 0, p.a.n, p.a.d, ColOffset{ti.n0});
   }
   static __device__ void epilogue(const Params& p, const TileInfo& ti, Acc<Cfg>& t, char* epi) {
-    if (p.a.b2) add_col_bias<Cfg>(t, p.a.b2 + (size_t)ti.e * p.a.d, ColOffset{ti.n0});
+    if (p.a.b2) add_col_bias<Cfg>(t, p.a.b2 + (size_t)ti.e * p.a.d, ColOffset{ti.n0}, p.a.d);
     if constexpr (AGG == kAggGather) {
-      store_rows_bf16_any<Cfg>(p.a.Y, p.a.d, ti.row_base, ti.mrows, ti.n0, t, epi);
+      store_rows_bf16_any<Cfg>(p.a.Y, p.a.d, ti.row_base, ti.mrows, ti.n0, ti.ncols, t, epi);
     } else if constexpr (AGG == kAggScatter) {
       static_assert(Cfg::RN % 2 == 0 && Cfg::STAGE_BYTES >= Cfg::NW * 4096, "staged rows");
       char* st = epi - Cfg::STAGE_BYTES + (threadIdx.x >> 6) * 4096;
@@ -1098,6 +1119,7 @@ struct OpDown {
         if (m0 >= ti.mrows) continue;
 #pragma unroll
         for (int j = 0; j + 1 < Cfg::RN; j += 2) {
+          if (t.n_of(j, 0) >= ti.ncols) continue;
           u32x2 v0[4], v1[4];
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
@@ -1127,6 +1149,7 @@ struct OpDown {
           for (int g = 0; g < 4; ++g)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
+              if (t.n_of(j, g) >= ti.ncols) continue;
               const float y = bf2f(f2bf(t.acc[i][j][4 * g + r]));
               unsafeAtomicAdd(o + t.n_of(j, g) + r, w * y);
             }
@@ -1168,7 +1191,7 @@ struct OpDH {
   }
   static __device__ void init_n(const Params& p, const TileInfo& ti, RowsSide<Cfg::BN, Cfg::BK, Cfg::NW>& s) {
     // rows of W2_e [n][d] are the n columns of dA', with d contiguous
-    s.init(p.a.W2 + (size_t)ti.e * p.a.n * p.a.d, p.a.d, nullptr, ti.n0, Cfg::BN);
+    s.init(p.a.W2 + (size_t)ti.e * p.a.n * p.a.d, p.a.d, nullptr, ti.n0, ti.ncols);
   }
   static __device__ void epilogue(const Params& p, const TileInfo& ti, Acc<Cfg>& t, char* smem) {
     constexpr int RM = Cfg::RM, RN = Cfg::RN;
@@ -1195,7 +1218,7 @@ struct OpDH {
       const int m = m_of(i);
       const size_t row = (size_t)(ti.row_base + (m < ti.mrows ? m : 0));
       const uint16_t* h = p.a.H + row * (2 * n);
-      const int col = col_of(j);
+      const int col = min(col_of(j), n - 32);  // (columns past n are not used)
       load_block_bf16(h + col, hg[b]);
       load_block_bf16(h + n + col, hu[b]);
     };
@@ -1216,7 +1239,7 @@ struct OpDH {
         // barrier); A' of the even block waits in the wave's 2 KB of the
         // epilogue area, the odd one in the gate area once that is stored.
         const int m0 = wm0 + 32 * i;
-        if (m0 < ti.mrows) {
+        if (m0 < ti.mrows && col_of(j) < n) {
           u32x2 vg[4], vu[4], va[4];
 #pragma unroll
           for (int g = 0; g < 4; ++g) {
@@ -1255,7 +1278,7 @@ struct OpDH {
             store_staged32_split(wh, st, p.a.Ap + r0 * n + col, n, rv);
           }
         }
-      } else if (valid) {
+      } else if (valid && col_of(j) < n) {
         uint16_t* dh = p.a.dH + row * (2 * n);
         uint16_t* ap = p.a.Ap + row * n;
         const int col = col_of(j);
@@ -1291,7 +1314,7 @@ struct OpDH {
       }
     }
     barrier_lds();
-    const int nnt = n / Cfg::BN;
+    const int nnt = (n + Cfg::BN - 1) / Cfg::BN;
     const int nt = ti.n0 / Cfg::BN;
     for (int m = threadIdx.x; m < ti.mrows; m += Cfg::THREADS) {
       float v = 0.f;
@@ -1333,10 +1356,10 @@ struct OpDXt {
   }
   static __device__ void init_n(const Params& p, const TileInfo& ti, RowsSide<Cfg::BN, Cfg::BK, Cfg::NW>& s) {
     // rows of W1_e [d][2n] are the d columns of dX~, with 2n contiguous
-    s.init(p.a.W1 + (size_t)ti.e * p.a.d * (2 * p.a.n), 2 * p.a.n, nullptr, ti.n0, Cfg::BN);
+    s.init(p.a.W1 + (size_t)ti.e * p.a.d * (2 * p.a.n), 2 * p.a.n, nullptr, ti.n0, ti.ncols);
   }
   static __device__ void epilogue(const Params& p, const TileInfo& ti, Acc<Cfg>& t, char* epi) {
-    store_rows_bf16_any<Cfg>(p.a.dXt, p.a.d, ti.row_base, ti.mrows, ti.n0, t, epi);
+    store_rows_bf16_any<Cfg>(p.a.dXt, p.a.d, ti.row_base, ti.mrows, ti.n0, ti.ncols, t, epi);
   }
 };
 
@@ -1362,10 +1385,12 @@ struct OpDW2 {
     s.init(p.a.dO, p.a.d, p.a.row_token, ti.k_begin, ti.k_len, p.a.d, ColOffset{ti.n0});
   }
   static __device__ void epilogue(const Params& p, const TileInfo& ti, Acc<Cfg>& t, char* epi) {
+    // (the limits are formed here: held across the k loop they cost registers)
+    const int mrows = p.a.n - ti.m0, ncols = p.a.d - ti.n0;
     if (ti.row_base >= 0)
-      store_part_f32<Cfg>(p.a.part + (size_t)ti.row_base * p.a.n * p.a.d, p.a.d, ti.m0, ti.n0, t);
+      store_part_f32<Cfg>(p.a.part + (size_t)ti.row_base * p.a.n * p.a.d, p.a.d, ti.m0, ti.n0, mrows, ncols, t);
     else
-      store_rows_bf16_any<Cfg>(p.a.dW2 + (size_t)ti.e * p.a.n * p.a.d, p.a.d, ti.m0, Cfg::BM, ti.n0, t, epi);
+      store_rows_bf16_any<Cfg>(p.a.dW2 + (size_t)ti.e * p.a.n * p.a.d, p.a.d, ti.m0, mrows, ti.n0, ncols, t, epi);
   }
 };
 
@@ -1390,10 +1415,13 @@ struct OpDW1 {
     s.init(p.a.dH, 2 * p.a.n, nullptr, ti.k_begin, ti.k_len, 2 * p.a.n, ColOffset{ti.n0});
   }
   static __device__ void epilogue(const Params& p, const TileInfo& ti, Acc<Cfg>& t, char* epi) {
+    const int mrows = p.a.d - ti.m0, ncols = 2 * p.a.n - ti.n0;
     if (ti.row_base >= 0)
-      store_part_f32<Cfg>(p.a.part + (size_t)ti.row_base * p.a.d * (2 * p.a.n), 2 * p.a.n, ti.m0, ti.n0, t);
+      store_part_f32<Cfg>(p.a.part + (size_t)ti.row_base * p.a.d * (2 * p.a.n), 2 * p.a.n, ti.m0, ti.n0, mrows, ncols,
+                          t);
     else
-      store_rows_bf16_any<Cfg>(p.a.dW1 + (size_t)ti.e * p.a.d * (2 * p.a.n), 2 * p.a.n, ti.m0, Cfg::BM, ti.n0, t, epi);
+      store_rows_bf16_any<Cfg>(p.a.dW1 + (size_t)ti.e * p.a.d * (2 * p.a.n), 2 * p.a.n, ti.m0, mrows, ti.n0, ncols, t,
+                               epi);
   }
 };
 
@@ -1426,6 +1454,7 @@ struct OpDWr {
     ti.m0 = (rem / ntn) * Cfg::BM;
     ti.n0 = (rem % ntn) * Cfg::BN;
     ti.mrows = Cfg::BM;
+    ti.ncols = min((int)Cfg::BN, p.a.E - ti.n0);
     ti.row_base = 0;
     const int chunk = (((p.a.T + p.a.splits - 1) / p.a.splits) + Cfg::BK - 1) / Cfg::BK * Cfg::BK;
     ti.k_begin = split * chunk;
@@ -1537,38 +1566,54 @@ hipError_t launch_router_topk(const RouterTopkArgs& a, hipStream_t s) {
   return run<OpRouterTopk<C128x256r, 8, false>>({a}, tiles, s);
 }
 
-// Whether 256 x 128 tiles serve a varlen-M GEMM of N columns better than 256 x
-// 256: the persistent schedule runs ceil(tiles / CUs) rounds, and a narrow tile
-// takes about 0.58 of a wide one.  So they win where a whole extra round of
-// wide tiles is nearly empty: up to half a round (one round of narrow tiles:
-// 0.58 of the time), and from one to one and a half (three narrow rounds for two
-// wide ones: 0.87).  us, wide and narrow tiles:
-//   dX~   T = 1000, d = 768, n = 1024, E = 32, K = 2     96 wide tiles   43 -> 26
-//   down  T = 1777, d = 1536, n = 512, E = 64, K = 4    384             35.5 -> 32
-//   down  T = 3000, d = 1536, n = 1024, E = 16, K = 2   186             34 -> 38 (not taken)
-//   up    T = 2048, d = 1024, n = 256, E = 64, K = 8    192             40 -> 46 (not taken)
-static bool narrow_tiles(int64_t rows, int E, int N, bool half_round_only) {
+// Tile width of a varlen-M GEMM of N columns (256-row tiles).  The persistent
+// schedule runs ceil(tiles / CUs) rounds, and the last tile of a row is partly
+// empty where N is not a multiple of its width; a narrower tile takes less time,
+// but more than its share.  The width with the least rounds x time is taken (the
+// widest within 5%).  us, wide and narrow tiles:
+//   dX~   T = 1000, d = 768, n = 1024, E = 32, K = 2    96 wide tiles    43 -> 26
+//   down  T = 1777, d = 1536, n = 512, E = 64, K = 4    384              35.5 -> 32
+//   down  T = 3000, d = 1536, n = 1024, E = 16, K = 2   186              34 -> 38 (not taken)
+//   up    T = 2048, d = 1024, n = 256, E = 64, K = 8    192              40 -> 46 (not taken)
+//   dH    T = 2048, d = 1024, n = 256, E = 64, K = 8    96               49 -> 33, 64 wide 36
+//   dH    T = 13676, d = 2304, n = 320, E = 8, K = 2    333 of 128       108 -> 99 for 64 wide
+struct TileTimes { int t256, t128, t64; };      // relative; 0: no such tile
+constexpr TileTimes kTimesUp{100, 62, 0};       // (256 x 128: unstaged stores)
+constexpr TileTimes kTimesDown{100, 58, 0};     // down and dX~
+constexpr TileTimes kTimesDH{100, 61, 33};
+
+static int n_tiles(int N, int BN) { return (N + BN - 1) / BN; }
+static int tile_width(const TileTimes& times, int64_t rows, int E, int N) {
   const int64_t mtiles = std::max<int64_t>(E, rows / kMTile + E / 2);  // about; ragged last tiles included
-  const int64_t tiles = mtiles * (N / 256), cus = cu_count();
-  return 2 * tiles <= cus || (!half_round_only && tiles > cus && 2 * tiles <= 3 * cus);
+  const int64_t cus = cu_count();
+  int best = 0;
+  int64_t least = 0;
+  for (const int w : {256, 128, 64}) {
+    const int t = w == 256 ? times.t256 : w == 128 ? times.t128 : times.t64;
+    if (!t) continue;
+    const int64_t cost = (mtiles * n_tiles(N, w) + cus - 1) / cus * t;
+    if (!best || 100 * cost < 95 * least) {
+      best = w;
+      least = cost;
+    }
+  }
+  return best;
 }
 
 hipError_t launch_up(const UpArgs& a, hipStream_t s) {
-  const int N = 2 * a.n;
-  // (its 256 x 128 tiles store 64-byte pieces: only for half a round)
-  if (a.n % 128 == 0 && !narrow_tiles(a.rows, a.E, N, true))
-    return run<OpUp<C256x256w>>({a}, pad8(mtiles_bound(a.capacity, a.E, 256) * (N / 256)), s);
-  return run<OpUp<C256x128>>({a}, pad8(mtiles_bound(a.capacity, a.E, 256) * (N / 128)), s);  // n % 64
+  const int N = 2 * a.n, w = tile_width(kTimesUp, a.rows, a.E, N);
+  const int grid = pad8(mtiles_bound(a.capacity, a.E, 256) * n_tiles(N, w));
+  return w == 256 ? run<OpUp<C256x256w>>({a}, grid, s) : run<OpUp<C256x128>>({a}, grid, s);
 }
 
 hipError_t launch_down(const DownArgs& a, hipStream_t s) {
-  if (a.d % 256 == 0 && !narrow_tiles(a.rows, a.E, a.d, false))
-    return run<OpDown<C256x256s>>({a}, pad8(mtiles_bound(a.capacity, a.E, 256) * (a.d / 256)), s);
-  return run<OpDown<C256x128>>({a}, pad8(mtiles_bound(a.capacity, a.E, 256) * (a.d / 128)), s);
+  const int w = tile_width(kTimesDown, a.rows, a.E, a.d);
+  const int grid = pad8(mtiles_bound(a.capacity, a.E, 256) * n_tiles(a.d, w));
+  return w == 256 ? run<OpDown<C256x256s>>({a}, grid, s) : run<OpDown<C256x128>>({a}, grid, s);
 }
 
 hipError_t launch_down_ablation(const DownArgs& a, int strategy, hipStream_t s) {
-  const int g256 = pad8(mtiles_bound(a.capacity, a.E, 256) * (a.d / 256));
+  const int g256 = pad8(mtiles_bound(a.capacity, a.E, 256) * n_tiles(a.d, 256));
   const int g128 = pad8(mtiles_bound(a.capacity, a.E, 256) * (a.d / 128));
   if (strategy == kAggScatter) {
     if (a.d % 256 == 0) return run<OpDown<C256x256, kAggScatter>>({a}, g256, s);
@@ -1581,16 +1626,12 @@ hipError_t launch_down_ablation(const DownArgs& a, int strategy, hipStream_t s) 
   return launch_down(a, s);
 }
 
-// (T = 2048, d = 1024, n = 256, E = 64, K = 8, 96 wide tiles: 49 -> 33 us)
-static int dh_bn(int n, int64_t rows, int E) {
-  if (n % 256 == 0 && !narrow_tiles(rows, E, n, true)) return 256;
-  return n % 128 == 0 ? 128 : 64;
-}
-int dh_n_tiles(int n, int64_t rows, int E) { return n / dh_bn(n, rows, E); }
+int dh_n_tiles(int n, int64_t rows, int E) { return n_tiles(n, tile_width(kTimesDH, rows, E, n)); }
 
 hipError_t launch_dh(const DHArgs& a, hipStream_t s) {
-  const int grid = pad8(mtiles_bound(a.capacity, a.E, 256) * dh_n_tiles(a.n, a.rows, a.E));
-  switch (dh_bn(a.n, a.rows, a.E)) {
+  const int w = tile_width(kTimesDH, a.rows, a.E, a.n);
+  const int grid = pad8(mtiles_bound(a.capacity, a.E, 256) * n_tiles(a.n, w));
+  switch (w) {
     case 256: return run<OpDH<C256x256w>>({a}, grid, s);
     case 128: return run<OpDH<C256x128>>({a}, grid, s);
     default: return run<OpDH<C256x64>>({a}, grid, s);
@@ -1598,9 +1639,9 @@ hipError_t launch_dh(const DHArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_dxt(const DXtArgs& a, hipStream_t s) {
-  if (a.d % 256 == 0 && !narrow_tiles(a.rows, a.E, a.d, false))
-    return run<OpDXt<C256x256ws>>({a}, pad8(mtiles_bound(a.capacity, a.E, 256) * (a.d / 256)), s);
-  return run<OpDXt<C256x128>>({a}, pad8(mtiles_bound(a.capacity, a.E, 256) * (a.d / 128)), s);
+  const int w = tile_width(kTimesDown, a.rows, a.E, a.d);
+  const int grid = pad8(mtiles_bound(a.capacity, a.E, 256) * n_tiles(a.d, w));
+  return w == 256 ? run<OpDXt<C256x256ws>>({a}, grid, s) : run<OpDXt<C256x128>>({a}, grid, s);
 }
 
 // varlen-K GEMMs gather their k rows: two stages (the row indices of the next
@@ -1622,18 +1663,41 @@ int dw_slabs(int T, int64_t mn) {
   return (int)std::min<int64_t>(kDwSlabs, b) & ~1;
 }
 
-// tile shapes of the weight-gradient GEMMs (their k-chunk lists are built
-// for these shapes); dW2: M = n, N = d; dW1: M = d, N = 2n
-// (where the 256-wide tiles of all experts are at most half a round of the CUs,
-// the 128-wide ones, four times as many and two to a CU, take less time)
-static bool dw_small_tiles(int E, int64_t tiles_per_expert) { return 2 * E * tiles_per_expert <= cu_count(); }
-static void dw2_tile(int d, int n, int E, int* bm, int* bn) {
-  *bn = d % 256 == 0 && !(n % 128 == 0 && dw_small_tiles(E, (int64_t)(d / 256) * ((n + 255) / 256))) ? 256 : 128;
-  *bm = (*bn == 256 && n % 256 == 0) ? 256 : (n % 128 == 0 ? 128 : 64);
-}
-static void dw1_tile(int d, int n, int E, int* bm, int* bn) {
-  const bool wide = d % 256 == 0 && (2 * n) % 256 == 0 && !dw_small_tiles(E, (int64_t)(d / 256) * (2 * n / 256));
-  *bm = *bn = wide ? 256 : 128;
+// Tile shapes of the weight-gradient GEMMs, M x N per expert (dW2: M = n, N = d;
+// dW1: M = d, N = 2n); their k-chunk lists are built for these shapes.  Rounds
+// over the CUs (two 128-wide tiles share one) times a tile's time per k step and
+// a few steps' worth of start, with partly empty edge tiles counted whole; the
+// widest within 7% of the least is taken.  us, 256 x 256 / 128 x 256 / 128 x 128:
+//   d = 1024, n = 256, E = 64, 1024 rows each   dW1 85 / 117 / 109   dW2 48 / 58 / 65
+//   the same, 256 rows                          dW1 34 / 39 / 36     dW2 19 / 20 / 20
+//   d = 896, n = 192, E = 40, 375 rows          dW1 46 / 44 / 32     dW2 36 / 31 / 27
+//   the same, 1500 rows                         dW1 100 / 116 / 78   dW2 59 / 73 / 68
+//   d = 768, n = 384, E = 96, 65 rows           dW1 34 / 33 / 31     dW2 26 / 20 / 17
+//   d = 1664, n = 512, E = 88, 796 rows         dW1 326 / - / 412    dW2 171 / - / 219
+//   d = 2304, n = 320, E = 8, 3419 rows, skewed dW1 181 / 251 / 203  dW2 112 / - / -
+//   d = 2048, n = 128, E = 256, skewed                               dW2 - / 266 / 291
+//   d = 1280, n = 64, E = 24, 9874 rows         dW2 134 / 119 / 188, 64 x 256 115, 64 x 128 192
+// So 256 x 256 or 128 x 128 for more than 128 rows of output, and tiles of their
+// own height, with the wide one preferred, below.
+struct DwTile { int bm, bn, occ, step, start; };
+static DwTile dw_tile(int M, int N, int E, int64_t rows) {
+  static const DwTile shapes[] = {
+      {256, 256, 1, 100, 600}, {128, 256, 1, 62, 400}, {64, 256, 1, 57, 400}, {128, 128, 2, 64, 200}, {64, 128, 2, 60, 200}};
+  const int high = M <= 64 ? 64 : M <= 128 ? 128 : 256;
+  const int64_t entries = std::max<int64_t>(E, rows / kKcMin);
+  const int64_t steps = std::min<int64_t>(rows / E, kKcMin) / kBK + 3;
+  const DwTile* best = nullptr;
+  int64_t least = 0;
+  for (const DwTile& t : shapes) {
+    if (t.bm != high && !(high == 256 && t.bm == 128 && t.bn == 128)) continue;
+    const int64_t slots = (int64_t)cu_count() * t.occ, tiles = entries * n_tiles(M, t.bm) * n_tiles(N, t.bn);
+    const int64_t cost = (tiles + slots - 1) / slots * t.step * steps + t.start;
+    if (!best || 100 * cost < 93 * least) {
+      best = &t;
+      least = cost;
+    }
+  }
+  return *best;
 }
 
 // whether E experts of tpe tiles each fill whole rounds of the CUs to 3/4
@@ -1642,13 +1706,11 @@ static int kchunk_keep_whole(int E, int tpe) {
   return 4 * tiles >= 3 * rounds * cus;
 }
 
-hipError_t launch_bwd_lists(const int32_t* offsets, int T, int E, int d, int n, int32_t* mtiles, int32_t* klist2,
+hipError_t launch_bwd_lists(const int32_t* offsets, int T, int64_t rows, int E, int d, int n, int32_t* mtiles, int32_t* klist2,
                             int32_t* klist1, const uint16_t* Wr, uint16_t* WrT, hipStream_t s) {
   if (E > 4096) return hipErrorInvalidValue;
-  int bm2, bn2, bm1, bn1;
-  dw2_tile(d, n, E, &bm2, &bn2);
-  dw1_tile(d, n, E, &bm1, &bn1);
-  const int tpe2 = (n / bm2) * (d / bn2), tpe1 = (d / bm1) * (2 * n / bn1);
+  const DwTile t2 = dw_tile(n, d, E, rows), t1 = dw_tile(d, 2 * n, E, rows);
+  const int tpe2 = n_tiles(n, t2.bm) * n_tiles(d, t2.bn), tpe1 = n_tiles(d, t1.bm) * n_tiles(2 * n, t1.bn);
   const int tr_blocks = Wr ? (d * E + kMTilesThreads - 1) / kMTilesThreads : 0;
   bwd_lists_kernel<<<3 + tr_blocks, kMTilesThreads, 0, s>>>(offsets, E, mtiles, tpe2, dw_slabs(T, (int64_t)n * d),
                                                            kchunk_keep_whole(E, tpe2), klist2, tpe1,
@@ -1659,37 +1721,27 @@ hipError_t launch_bwd_lists(const int32_t* offsets, int T, int E, int d, int n, 
 
 // the GEMM over the k-chunk list (its split experts are summed by
 // launch_bwd_final_reduce)
-template <class Op, class Args>
+template <template <class> class Op, class Args>
 static hipError_t run_dw(const Args& a, int M, int N, hipStream_t s) {
-  using Cfg = typename Op::Cfg;
-  const int tpe = (M / Cfg::BM) * (N / Cfg::BN);
-  return run<Op>({a}, pad8((a.E + dw_slabs(a.T, (int64_t)M * N)) * tpe), s);
-}
-
-hipError_t launch_dw2(const DW2Args& a, hipStream_t s) {
-  int bm, bn;
-  dw2_tile(a.d, a.n, a.E, &bm, &bn);
-  if (bn == 256) {
-    if (bm == 256) return run_dw<OpDW2<W256x256>>(a, a.n, a.d, s);
-    if (bm == 128) return run_dw<OpDW2<W128x256>>(a, a.n, a.d, s);
-    return run_dw<OpDW2<W64x256>>(a, a.n, a.d, s);
+  const DwTile t = dw_tile(M, N, a.E, a.rows);
+  const int grid = pad8((a.E + dw_slabs(a.T, (int64_t)M * N)) * n_tiles(M, t.bm) * n_tiles(N, t.bn));
+  if (t.bn == 256) {
+    if (t.bm == 256) return run<Op<W256x256>>({a}, grid, s);
+    if (t.bm == 128) return run<Op<W128x256>>({a}, grid, s);
+    return run<Op<W64x256>>({a}, grid, s);
   }
-  if (bm == 128) return run_dw<OpDW2<W128x128>>(a, a.n, a.d, s);
-  return run_dw<OpDW2<W64x128>>(a, a.n, a.d, s);
+  if (t.bm == 128) return run<Op<W128x128>>({a}, grid, s);
+  return run<Op<W64x128>>({a}, grid, s);
 }
 
-hipError_t launch_dw1(const DW1Args& a, hipStream_t s) {
-  int bm, bn;
-  dw1_tile(a.d, a.n, a.E, &bm, &bn);
-  if (bm == 256) return run_dw<OpDW1<W256x256>>(a, a.d, 2 * a.n, s);
-  return run_dw<OpDW1<W128x128>>(a, a.d, 2 * a.n, s);
-}
+hipError_t launch_dw2(const DW2Args& a, hipStream_t s) { return run_dw<OpDW2>(a, a.n, a.d, s); }
+hipError_t launch_dw1(const DW1Args& a, hipStream_t s) { return run_dw<OpDW1>(a, a.d, 2 * a.n, s); }
 
 static DwGrid dw_reduce_grid(int T, int64_t MN) {
   const int slabs = dw_slabs(T, MN);
   // split experts are looped over: most calls have none, and a grid sized for
   // every possible one would mostly launch workgroups that exit at once
-  return {(int)std::min<int64_t>((MN / 4 + 255) / 256, 64), std::min(slabs / 2, 8), MN};
+  return {(int)std::min<int64_t>((MN / 4 + 255) / 256, 128), std::min(slabs / 2, 8), MN};
 }
 
 hipError_t launch_bwd_final_reduce(const FinalReduceArgs& a, hipStream_t s) {

@@ -124,19 +124,19 @@ inline size_t dw_part_bytes(int T, int64_t mn) { return (size_t)dw_slabs(T, mn) 
 // the backward's m-tile list (as launch_mtiles) and the k-chunk lists of dW2
 // and dW1, in one launch; with Wr non-null the same launch writes WrT[e][i] =
 // Wr[i][e] (the dX aggregation's router term reads W_r by expert)
-hipError_t launch_bwd_lists(const int32_t* offsets, int T, int E, int d, int n, int32_t* mtiles, int32_t* klist2,
+hipError_t launch_bwd_lists(const int32_t* offsets, int T, int64_t rows, int E, int d, int n, int32_t* mtiles, int32_t* klist2,
                             int32_t* klist1, const uint16_t* Wr, uint16_t* WrT, hipStream_t s);
 
 struct DW2Args {
   const uint16_t* Ap; const uint16_t* dO; const int32_t* offsets; const int32_t* row_token; uint16_t* dW2;
-  int T, d, n, E;
+  int T; int64_t rows; int d, n, E;
   int32_t* klist; float* part;
 };
 hipError_t launch_dw2(const DW2Args& a, hipStream_t s);
 
 struct DW1Args {
   const uint16_t* X; const uint16_t* dH; const int32_t* offsets; const int32_t* row_token; uint16_t* dW1;
-  int T, d, n, E;
+  int T; int64_t rows; int d, n, E;
   int32_t* klist; float* part;
 };
 hipError_t launch_dw1(const DW1Args& a, hipStream_t s);

@@ -620,7 +620,7 @@ int moe_bwd(moe_dims m, const moe_bf16* dO, const moe_bf16* X, const moe_bf16* H
   float* dS_out = dS ? dS : w.dS;
   const int64_t rows = (int64_t)m.T * m.K;
   const int nnt = smoe::dh_n_tiles(m.n, rows, m.E);
-  HIP_TRY(smoe::launch_bwd_lists(r->offsets, m.T, m.E, m.d, m.n, w.mtiles, w.klist2, w.klist1, Wr, Wr ? w.WrT : nullptr,
+  HIP_TRY(smoe::launch_bwd_lists(r->offsets, m.T, rows, m.E, m.d, m.n, w.mtiles, w.klist2, w.klist1, Wr, Wr ? w.WrT : nullptr,
                                  stream),
           "tile lists and W_r transpose");
   if (b2) {
@@ -638,10 +638,10 @@ int moe_bwd(moe_dims m, const moe_bf16* dO, const moe_bf16* X, const moe_bf16* H
   const bool ds_in_parts = nnt > 1 && nnt <= 4 && !dS;
   if (nnt > 1 && !ds_in_parts)
     HIP_TRY(smoe::launch_reduce_rowparts(w.dS_part, dS_out, r->capacity, nnt, stream), "dS reduce");
-  LAUNCH(MOE_KC_DW2, smoe::launch_dw2({w.Ap, dO, r->offsets, r->row_token, dW2, m.T, m.d, m.n, m.E, w.klist2, w.dw2_part}, stream), "dW2");
+  LAUNCH(MOE_KC_DW2, smoe::launch_dw2({w.Ap, dO, r->offsets, r->row_token, dW2, m.T, rows, m.d, m.n, m.E, w.klist2, w.dw2_part}, stream), "dW2");
   LAUNCH(MOE_KC_DXT, smoe::launch_dxt({w.dH, W1, r->offsets, w.dXt, m.d, m.n, m.E, r->capacity, rows, w.mtiles}, stream),
          "dX~");
-  LAUNCH(MOE_KC_DW1, smoe::launch_dw1({X, w.dH, r->offsets, r->row_token, dW1, m.T, m.d, m.n, m.E, w.klist1, w.dw1_part}, stream), "dW1");
+  LAUNCH(MOE_KC_DW1, smoe::launch_dw1({X, w.dH, r->offsets, r->row_token, dW1, m.T, rows, m.d, m.n, m.E, w.klist1, w.dw1_part}, stream), "dW1");
   LAUNCH(MOE_KC_AGG_DX,
          smoe::launch_agg_dx(w.dXt, ds_in_parts ? w.dS_part : dS_out, ds_in_parts ? nnt : 1, Wr ? w.WrT : nullptr, *r, dX, Wr ? w.dL : nullptr, m.T, m.d, m.E, stream),
          "dX aggregation");

@@ -142,3 +142,18 @@ def test_wide_tiles_on_short_loops():
 ])
 def test_narrow_tiles(T, d, n, E, K):
     check_layer(W.MoEConfig("narrow", T=T, d=d, n=n, E=E, K=K, m_tile=128), seed=38)
+
+
+@pytest.mark.parametrize("T,d,n,E,K,mode", [
+    (3000, 896, 192, 40, 3, None),         # dH one 256-wide tile, dW 256 x 256: columns and rows past both
+    (3000, 1152, 320, 24, 4, "nearest"),   # down and dX~ 256-wide over d = 4.5 tiles, up over n = 2.5
+    (9000, 1152, 448, 8, 4, None),         # the same with split experts' fp32 slabs
+    (2500, 640, 64, 48, 4, None),          # n of one narrow tile
+    (700, 640, 576, 8, 2, None),           # few tiles: narrow shapes with masked halves
+])
+@pytest.mark.parametrize("biased", [False, True])
+def test_columns_off_the_wide_tiles(T, d, n, E, K, mode, biased):
+    """d an odd multiple of 128 and n an odd multiple of 64: the last 256-wide
+    tile of a row is partly past the matrix, in every GEMM of the layer."""
+    cfg = W.MoEConfig("offgrid", T=T, d=d, n=n, E=E, K=K, m_tile=128, zipf_s=1.2 if T == 9000 else 0.0)
+    check_layer(cfg, seed=39, round_mode=mode, eb=expert_biases(cfg, 39) if biased else None)
