@@ -264,13 +264,20 @@ struct StreamRouter {
 };
 
 // waves and loads in flight of the row blocks: the widest split of k that
-// keeps two or more steps per wave, within the registers (no spills)
+// keeps two or more steps per wave, within the registers (no spills); a short k
+// (the down-projection of a narrow expert) has two waves with a step or two each,
+// (T = 65, d = 1664, n = 64, E = 312, K = 8: down 26 us with eight waves,
+// six of them idle, 13 with two)
 template <class Op>
 static hipError_t run_stream(const typename Op::Params& p, dim3 grid, int mb, int k, hipStream_t s) {
   if (mb == 1 && k >= 768)
     stream_gemm_kernel<Op, 1, 8, 3, 2><<<grid, dim3(512), 0, s>>>(p);
-  else if (mb == 1)
+  else if (mb == 1 && k > 128)
     stream_gemm_kernel<Op, 1, 8, 2, 4><<<grid, dim3(512), 0, s>>>(p);
+  else if (mb == 1)
+    stream_gemm_kernel<Op, 1, 2, 2, 3><<<grid, dim3(128), 0, s>>>(p);
+  else if (mb == 2 && k <= 128)
+    stream_gemm_kernel<Op, 2, 2, 1, 3><<<grid, dim3(128), 0, s>>>(p);
   else if (mb == 2)
     stream_gemm_kernel<Op, 2, 4, 2, 2><<<grid, dim3(256), 0, s>>>(p);
   else
