@@ -326,16 +326,38 @@ __global__ __launch_bounds__(256) void bwd_final_reduce_kernel(const FinalReduce
   (bias ? a.dbias : a.dWr)[i] = s;
 }
 
+// Order of the tiles of an M-tile x N-tile grid.  The 32 workgroups of an XCD run
+// neighbouring ids at about the same time and share operands through its L2.
+// Row by row, 32 ids are whole rows of a few columns, but 1 x 32 tiles (33
+// operand slabs) of a wide matrix, whose weights are then read again for every
+// m-tile.  In blocks of B rows (1, 4 or 8), column by column within a block,
+// they are 4 x 8 tiles (12 slabs).  us, row by row / B = 4 / B = 8:
+//   E = 8, d = 4096, n = 14336, 1024 rows each  up 2280 / 2070 / 2083   down 1262 / 1220 / 1207
+//   E = 128, d = 4096, n = 512, 2048 rows       dX~ 2108 / 2105 / 2147  down 1293 / 1293 / 1321
+//   E = 256, d = 2048, n = 128, skewed          dX~ 449 / 453 / 432     down 353 / 356 / 335
+//   E = 64, d = 4096, n = 2048, 256 rows        up 790 / 814 / 820      dW2 485 / 469 / 460
+__device__ __forceinline__ void tile_order(int id, int rows, int cols, int B, int* row, int* col) {
+  const int q = id / cols, c = id - q * cols;
+  *row = q;
+  *col = c;
+  if ((q | (B - 1)) < rows) {  // (a last block of fewer rows goes row by row)
+    const int r = (q & (B - 1)) * cols + c;
+    *row = (q & ~(B - 1)) + (r & (B - 1));
+    *col = B == 1 ? c : r >> (B == 4 ? 2 : 3);
+  }
+}
+
 // A varlen-K tile from the k-chunk list: entry = id / (tiles per entry).
 template <int BM, int BN>
 __device__ __forceinline__ bool tile_kchunk(const int32_t* klist, int E, int M, int N, int id, TileInfo& ti) {
   const int mtn = (M + BM - 1) / BM, ntn = (N + BN - 1) / BN;
   const SMOE_CONST i32x4* ent = (const SMOE_CONST i32x4*)(klist + 16);
   const i32x4 t = ent[id / (mtn * ntn)];
-  const int rem = id % (mtn * ntn);
+  int mt, nt;
+  tile_order(id % (mtn * ntn), mtn, ntn, ntn >= 8 ? 4 : 1, &mt, &nt);
   ti.e = t[0];
-  ti.m0 = (rem / ntn) * BM;
-  ti.n0 = (rem % ntn) * BN;
+  ti.m0 = mt * BM;
+  ti.n0 = nt * BN;
   ti.mrows = min(BM, M - ti.m0);
   ti.ncols = min(BN, N - ti.n0);
   ti.row_base = t[3];  // partial slab, or -1
@@ -370,20 +392,25 @@ __device__ __forceinline__ void store_part_f32(float* out, int64_t ld, int m0, i
   }
 }
 
-// Logical tile ids are m-tile-major within their class (full m-tiles, then
-// the partial ones): id = mt * (N / BN) + nt, so neighbouring ids share the
-// rows of one m-tile and the weights of one expert.  The list entry is
+// Logical tile ids run over the tiles of their class (full m-tiles, then the
+// partial ones) in tile_order, so neighbouring ids share the rows of an m-tile
+// and the weights of an expert.  The list entry is
 // read with a scalar load (the id is workgroup-uniform).
 template <int BM, int BN>
-__device__ __forceinline__ bool tile_varlen_m(const int32_t* mtiles, int N, int K, int id, TileInfo& ti) {
+__device__ __forceinline__ bool tile_varlen_m(const int32_t* mtiles, int E, int N, int K, int id, TileInfo& ti) {
   static_assert(BM == kMTile, "varlen-M tiles are the m-tile list's tiles");
   const int nnt = (N + BN - 1) / BN;
   const bool partial = (id & kPartialTile) != 0;
   id &= kPartialTile - 1;
-  const int mt = id / nnt, nt = id % nnt;
   const SMOE_CONST i32x4* list = (const SMOE_CONST i32x4*)mtiles;
   const i32x4 h = list[0];
-  const int idx = partial ? h[0] - h[1] + mt : mt;
+  const int full = h[0] - h[1];
+  int mt, nt;
+  // blocks of m-tiles where an expert has several: taller for a short k, whose
+  // time goes into the outputs
+  const int block = nnt < 8 || h[0] < 4 * E ? 1 : K <= 256 ? 8 : 4;
+  tile_order(id, partial ? h[1] : full, nnt, block, &mt, &nt);
+  const int idx = partial ? full + mt : mt;
   if (idx >= h[0]) return false;
   const i32x4 t = list[1 + idx];
   ti.e = t[0];
@@ -931,7 +958,7 @@ struct OpUp {
     return count_varlen_m_tail<Cfg::BN>(p.a.mtiles, 2 * p.a.n);
   }
   static __device__ bool tile(const Params& p, int id, TileInfo& ti, int* sh) {
-    return tile_varlen_m<Cfg::BM, Cfg::BN>(p.a.mtiles, 2 * p.a.n, p.a.d, id, ti);
+    return tile_varlen_m<Cfg::BM, Cfg::BN>(p.a.mtiles, p.a.E, 2 * p.a.n, p.a.d, id, ti);
   }
   static __device__ void init_m(const Params& p, const TileInfo& ti, RowsSide<Cfg::BM, Cfg::BK, Cfg::NW, true>& s) {
     s.init(p.a.X, p.a.d, p.a.row_token, ti.row_base, ti.mrows);
@@ -1096,7 +1123,7 @@ struct OpDown {
     return count_varlen_m_tail<Cfg::BN>(p.a.mtiles, p.a.d);
   }
   static __device__ bool tile(const Params& p, int id, TileInfo& ti, int* sh) {
-    return tile_varlen_m<Cfg::BM, Cfg::BN>(p.a.mtiles, p.a.d, p.a.n, id, ti);
+    return tile_varlen_m<Cfg::BM, Cfg::BN>(p.a.mtiles, p.a.E, p.a.d, p.a.n, id, ti);
   }
   static __device__ void init_m(const Params& p, const TileInfo& ti, RowsSide<Cfg::BM, Cfg::BK, Cfg::NW>& s) {
     s.init(p.a.A, p.a.n, nullptr, ti.row_base, ti.mrows);
@@ -1184,7 +1211,7 @@ struct OpDH {
     return count_varlen_m_tail<Cfg::BN>(p.a.mtiles, p.a.n);
   }
   static __device__ bool tile(const Params& p, int id, TileInfo& ti, int* sh) {
-    return tile_varlen_m<Cfg::BM, Cfg::BN>(p.a.mtiles, p.a.n, p.a.d, id, ti);
+    return tile_varlen_m<Cfg::BM, Cfg::BN>(p.a.mtiles, p.a.E, p.a.n, p.a.d, id, ti);
   }
   static __device__ void init_m(const Params& p, const TileInfo& ti, RowsSide<Cfg::BM, Cfg::BK, Cfg::NW, true>& s) {
     s.init(p.a.dO, p.a.d, p.a.row_token, ti.row_base, ti.mrows);
@@ -1349,7 +1376,7 @@ struct OpDXt {
     return count_varlen_m_tail<Cfg::BN>(p.a.mtiles, p.a.d);
   }
   static __device__ bool tile(const Params& p, int id, TileInfo& ti, int* sh) {
-    return tile_varlen_m<Cfg::BM, Cfg::BN>(p.a.mtiles, p.a.d, 2 * p.a.n, id, ti);
+    return tile_varlen_m<Cfg::BM, Cfg::BN>(p.a.mtiles, p.a.E, p.a.d, 2 * p.a.n, id, ti);
   }
   static __device__ void init_m(const Params& p, const TileInfo& ti, RowsSide<Cfg::BM, Cfg::BK, Cfg::NW>& s) {
     s.init(p.a.dH, 2 * p.a.n, nullptr, ti.row_base, ti.mrows);
