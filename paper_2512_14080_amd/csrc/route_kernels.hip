@@ -604,7 +604,7 @@ __global__ __launch_bounds__(1024) void tc_metadata_few_kernel(const moe_routing
   extern __shared__ __attribute__((aligned(16))) char dyn[];
   __shared__ int scan_lds[16];
   unsigned long long* word = (unsigned long long*)dyn;  // [E]
-  int* total = (int*)(word + E);                        // [E] tokens, then first rows of the word
+  int* total = (int*)(word + E);                        // [E] tokens of later words, then first rows of the word
   int* before = total + E;                              // [E] tokens of earlier words
   int* sidx = before + E;                               // [64][K]
   float* sw = (float*)(sidx + 64 * K);
@@ -615,21 +615,23 @@ __global__ __launch_bounds__(1024) void tc_metadata_few_kernel(const moe_routing
   }
   __syncthreads();
   const int lo = 64 * w * K, hi = min(T, 64 * w + 64) * K;
-  for (int i0 = 0; i0 < T * K; i0 += 4096) {
-    int e[4];
+  // one LDS count per entry outside the word: entries before it and after it
+  for (int i0 = 0; i0 < T * K; i0 += 8192) {
+    int e[8];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < 8; ++q) {
       const int i = i0 + 1024 * q + threadIdx.x;
       e[q] = i < T * K ? r.topk_idx[i] : -1;
     }
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+    for (int q = 0; q < 8; ++q) {
       const int i = i0 + 1024 * q + threadIdx.x;
       if (e[q] < 0) continue;
-      atomicAdd(&total[e[q]], 1);
       if (i < lo) {
         atomicAdd(&before[e[q]], 1);
-      } else if (i < hi) {
+      } else if (i >= hi) {
+        atomicAdd(&total[e[q]], 1);
+      } else {
         sidx[i - lo] = e[q];
         sw[i - lo] = r.topk_w[i];
         atomicOr(&word[e[q]], 1ull << (i / K - 64 * w));
@@ -640,7 +642,7 @@ __global__ __launch_bounds__(1024) void tc_metadata_few_kernel(const moe_routing
   int running = 0;
   for (int e0 = 0; e0 < E; e0 += 1024) {
     const int e = e0 + threadIdx.x;
-    const int c = e < E ? total[e] : 0;
+    const int c = e < E ? before[e] + __popcll(word[e]) + total[e] : 0;
     int sum;
     const int off = running + block_excl_scan<1024>(c, &sum, scan_lds);
     if (e < E) {
