@@ -284,8 +284,8 @@ __global__ __launch_bounds__(64 * NW) void topk_lane_kernel(const float* in, flo
   float* xmax = (float*)(dyn + (size_t)E * 256);           // [NW][64]
   float* xsum = xmax + NW * 64;                            // [NW][64]
   uint64_t* lists = (uint64_t*)(xsum + NW * 64);           // [NW][KM][64]
-  float* sv = (float*)(lists + NW * KM * 64);              // [NW][KM][64] selected scores, expert order
-  int* nsel = (int*)(sv + NW * KM * 64);                   // [NW][64]
+  int* nsel = (int*)(lists + NW * KM * 64);                // [NW][64]
+  float* sv = (float*)lists;                               // [NW][KM][64] selected scores, expert order (lists read)
   // a lane past T reads token 0's row and discards it
   const f32x4* row = (const f32x4*)(in + (size_t)(live ? t : 0) * E + e0);
   const f32x4 ninf = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
@@ -383,6 +383,7 @@ __global__ __launch_bounds__(64 * NW) void topk_lane_kernel(const float* in, flo
       topk_merge<KM>(top, b);
     }
   }
+  if constexpr (NW > 1) __syncthreads();  // the lists' space is reused for sv
   uint64_t thr = top[0];
 #pragma unroll
   for (int k = 1; k < KM; ++k)
@@ -439,7 +440,9 @@ __global__ __launch_bounds__(64 * NW) void topk_lane_kernel(const float* in, flo
 }
 
 static size_t topk_lane_lds(int E, int KM, int NW) {
-  return (size_t)E * 256 + (NW > 1 ? (size_t)NW * 64 * (4 + 4 + 8 * KM + 4 * KM + 4) : 0);
+  // E = 128, K = 8: 51 KB, three workgroups per CU (with sv in its own space two,
+  // and T = 40960 ran two rounds: 32.5 -> 28 us)
+  return (size_t)E * 256 + (NW > 1 ? (size_t)NW * 64 * (4 + 4 + 8 * KM + 4) : 0);
 }
 
 // ------------------------------------------------------------- few tokens
