@@ -159,9 +159,11 @@ enum {
  * r->capacity must be >= T*K.  On success r->state is MOE_ROUTING_STATE_BUILT
  * (MOE_ROUTING_STATE_COUNTS with MOE_ROUTE_COUNTS_ONLY) and the device word
  * r->status is cleared by the metadata kernels.
- * With E <= 256 and K <= 8 the softmax and top-K run in the
+ * With T > 4096, E <= 256 and K <= 8 the softmax and top-K run in the
  * router GEMM's epilogue (one launch; the logits are written only with
- * MOE_ROUTE_WRITE_LOGITS).  Its scores may differ from the two-launch path's
+ * MOE_ROUTE_WRITE_LOGITS).  With T <= 4096 and E <= 1024 the router GEMM's
+ * partial sums pass through r->scratch or r->scores, with or without
+ * MOE_ROUTE_SEPARATE_TOPK.  Its scores may differ from the two-launch path's
  * in the last bits (the order of the softmax sum); selection, mask and weights
  * are those the two-launch path derives from the scores it writes.
  * Scores are compared through the order-preserving image of their fp32 bit
