@@ -247,13 +247,15 @@ size_t routing_layout(const moe_dims& m, int64_t cap, int flags, char* base, moe
   return off;
 }
 
-// the projections, streaming (few rows per expert) or tiled
+// the projections, streaming (few rows per expert; 32-bit offsets within an
+// expert's weights) or tiled
 struct Projections {
   int up, down, T;  // row blocks per streaming workgroup; 0: tiled
-  explicit Projections(const moe_dims& m)
-      : up(smoe::stream_row_blocks((int64_t)m.T * m.K, m.E, (2 * m.n + 255) / 256)),
-        down(smoe::stream_row_blocks((int64_t)m.T * m.K, m.E, (m.d + 255) / 256)),
-        T(m.T) {}
+  explicit Projections(const moe_dims& m) : up(0), down(0), T(m.T) {
+    if ((int64_t)m.d * 2 * m.n > INT32_MAX) return;
+    up = smoe::stream_row_blocks((int64_t)m.T * m.K, m.E, (2 * m.n + 255) / 256);
+    down = smoe::stream_row_blocks((int64_t)m.T * m.K, m.E, (m.d + 255) / 256);
+  }
   hipError_t lists(const int32_t* offsets, int E, int32_t* mtiles, hipStream_t s) const {
     return up && down ? hipSuccess : smoe::launch_mtiles(offsets, E, mtiles, s);
   }
