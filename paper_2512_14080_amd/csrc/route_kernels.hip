@@ -668,12 +668,14 @@ __global__ __launch_bounds__(1024) void tc_metadata_few_kernel(const moe_routing
   place_word(r, w, T, K, sidx, sw, word, total);
 }
 
-// Per expert: popcount prefix over its mask words and its count f_e.
+// Per expert: popcount prefix over its mask words and its count f_e.  status
+// (nullable) is cleared for a placement launch that may flag it.
 __global__ __launch_bounds__(256) void expert_scan_kernel(const uint64_t* __restrict__ mask,
                                                           int32_t* __restrict__ prefix, int32_t* __restrict__ counts,
-                                                          int W) {
+                                                          int W, int32_t* __restrict__ status) {
   __shared__ int lds[16];
   const int e = blockIdx.x;
+  if (status && e == 0 && threadIdx.x == 0) *status = 0;
   const uint64_t* m = mask + (size_t)e * W;
   int32_t* p = prefix + (size_t)e * W;
   int running = 0;
@@ -691,9 +693,8 @@ __global__ __launch_bounds__(256) void expert_scan_kernel(const uint64_t* __rest
 // out[0..n] = exclusive scan of cnt[0..n-1] (one block of 1024 threads, four
 // values per thread per pass).
 __global__ __launch_bounds__(1024) void scan_kernel(const int32_t* __restrict__ cnt, int32_t* __restrict__ out,
-                                                    int n, int32_t* __restrict__ status) {
+                                                    int n) {
   __shared__ int lds[16];
-  if (status && threadIdx.x == 0) *status = 0;  // cleared before the placement that may flag it
   int running = 0;
   for (int c0 = 0; c0 < n; c0 += 4096) {
     const int i0 = c0 + threadIdx.x * 4;
@@ -713,34 +714,56 @@ __global__ __launch_bounds__(1024) void scan_kernel(const int32_t* __restrict__ 
   if (threadIdx.x == 0) out[n] = running;
 }
 
-__device__ __forceinline__ int expert_row(const uint64_t* __restrict__ mask, const int32_t* __restrict__ prefix,
-                                          const int32_t* __restrict__ offsets, int e, int W, int w, uint64_t below) {
-  const uint64_t word = mask[(size_t)e * W + w];
-  return offsets[e] + prefix[(size_t)e * W + w] + __popcll(word & below);
-}
-
 // Token-choice placement: every token has exactly K rows, so the token-major
 // offsets are t*K.  Each token's experts are visited in ascending order.
+// Every workgroup sums the experts' counts to their first rows itself, while
+// its top-K lists load, and workgroup 0 writes them: as a launch of its own
+// between the counts and the rows the scan was one workgroup's chain of latencies
+// (T = 6000, d = 1024, n = 256, E = 64, K = 8 forward 185.9 -> 184.0 us; T = 4999,
+// d = 1536, E = 128 253.3 -> 250.8; T = 8192, E = 512 480.5 -> 478.4).
 __global__ __launch_bounds__(256) void tc_place_kernel(const int32_t* __restrict__ topk_idx,
                                                        const float* __restrict__ topk_w,
                                                        const uint64_t* __restrict__ mask,
                                                        const int32_t* __restrict__ prefix,
-                                                       const int32_t* __restrict__ offsets,
+                                                       const int32_t* __restrict__ counts,
+                                                       int32_t* __restrict__ offsets,
                                                        int32_t* __restrict__ tok_offsets, int32_t* __restrict__ tok_count,
                                                        int32_t* __restrict__ tok_rows, int32_t* __restrict__ row_token,
                                                        int32_t* __restrict__ row_expert, float* __restrict__ row_w, int T,
-                                                       int K, int W, int32_t* __restrict__ status) {
-  const int t = blockIdx.x * blockDim.x + threadIdx.x;
-  if (t >= T) return;
+                                                       int E, int K, int W, int32_t* __restrict__ status) {
+  extern __shared__ int first_row[];  // [E]
+  __shared__ int scan_lds[16];
+  const int t = blockIdx.x * 256 + threadIdx.x;
   const int w = t >> 6, b = t & 63;
   const uint64_t below = b ? (~0ull >> (64 - b)) : 0ull;
   int ex[16];
   float wt[16];
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
-    ex[k] = k < K ? topk_idx[(size_t)t * K + k] : 0x7fffffff;
-    wt[k] = k < K ? topk_w[(size_t)t * K + k] : 0.f;
+    ex[k] = k < K && t < T ? topk_idx[(size_t)t * K + k] : 0x7fffffff;
+    wt[k] = k < K && t < T ? topk_w[(size_t)t * K + k] : 0.f;
   }
+  int running = 0;
+  for (int e0 = 0; e0 < E; e0 += 1024) {
+    const int e = e0 + 4 * threadIdx.x;
+    int v[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = e + q < E ? counts[e + q] : 0;
+    int total;
+    int row = running + block_excl_scan<256>(v[0] + v[1] + v[2] + v[3], &total, scan_lds);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (e + q < E) {
+        first_row[e + q] = row;
+        if (blockIdx.x == 0) offsets[e + q] = row;
+      }
+      row += v[q];
+    }
+    running += total;
+  }
+  if (blockIdx.x == 0 && threadIdx.x == 0) offsets[E] = running;
+  __syncthreads();
+  if (t >= T) return;
   int last = -1;
 #pragma unroll
   for (int r = 0; r < 16; ++r) {
@@ -763,7 +786,8 @@ __global__ __launch_bounds__(256) void tc_place_kernel(const int32_t* __restrict
         tok_rows[(size_t)t * K + r] = 0;
         continue;
       }
-      const int row = expert_row(mask, prefix, offsets, e, W, w, below);
+      const size_t ew = (size_t)e * W + w;
+      const int row = first_row[e] + prefix[ew] + __popcll(mask[ew] & below);
       tok_rows[(size_t)t * K + r] = row;
       row_token[row] = t;
       row_expert[row] = e;
@@ -1082,12 +1106,13 @@ hipError_t launch_tc_metadata_few(const moe_routing& r, int T, int E, int K, boo
 
 hipError_t launch_tc_metadata(const moe_routing& r, int T, int E, int K, bool counts_only, hipStream_t s) {
   const int W = r.words;
-  expert_scan_kernel<<<dim3(E), dim3(256), 0, s>>>(r.mask, r.mask_prefix, r.counts, W);
+  expert_scan_kernel<<<dim3(E), dim3(256), 0, s>>>(r.mask, r.mask_prefix, r.counts, W,
+                                                   counts_only ? nullptr : r.status);
   if (counts_only) return hipGetLastError();
-  scan_kernel<<<dim3(1), dim3(1024), 0, s>>>(r.counts, r.offsets, E, r.status);
-  tc_place_kernel<<<dim3((T + 255) / 256), dim3(256), 0, s>>>(r.topk_idx, r.topk_w, r.mask, r.mask_prefix, r.offsets,
-                                                              r.tok_offsets, r.tok_count, r.tok_rows, r.row_token,
-                                                              r.row_expert, r.row_w, T, K, W, r.status);
+  if (E > 4096) return hipErrorInvalidValue;  // the first rows take 16 KB of LDS
+  tc_place_kernel<<<dim3((T + 255) / 256), dim3(256), (size_t)E * 4, s>>>(
+      r.topk_idx, r.topk_w, r.mask, r.mask_prefix, r.counts, r.offsets, r.tok_offsets, r.tok_count, r.tok_rows,
+      r.row_token, r.row_expert, r.row_w, T, E, K, W, r.status);
   return hipGetLastError();
 }
 
@@ -1095,14 +1120,14 @@ hipError_t launch_metadata(const moe_routing& r, const float* scores_t, int T, i
   const int W = r.words;
   int32_t* word_sum = r.scratch + E + 64;  // [W]
   int32_t* word_base = word_sum + W + 1;   // [W + 1]
-  if (!counted) expert_scan_kernel<<<dim3(E), dim3(256), 0, s>>>(r.mask, r.mask_prefix, r.counts, W);
+  if (!counted) expert_scan_kernel<<<dim3(E), dim3(256), 0, s>>>(r.mask, r.mask_prefix, r.counts, W, nullptr);
   // one extra workgroup turns the expert counts into offsets
   token_count_kernel<<<dim3(W + 1), dim3(64), 0, s>>>(r.mask, scores_t, r.tok_count, r.tok_denom, word_sum, r.counts,
                                                       r.offsets, T, E, W, r.status);
   // up to kPlaceSumWords words every placement workgroup sums the word sums
   // before it itself; beyond that a scan kernel provides the bases
   const bool scan_words = W > kPlaceSumWords;
-  if (scan_words) scan_kernel<<<dim3(1), dim3(1024), 0, s>>>(word_sum, word_base, W, nullptr);
+  if (scan_words) scan_kernel<<<dim3(1), dim3(1024), 0, s>>>(word_sum, word_base, W);
   token_place_kernel<<<dim3(W), dim3(64 * kPlaceWaves), 0, s>>>(r.mask, r.mask_prefix, r.offsets, r.tok_count,
                                                                 scan_words ? word_base : nullptr, word_sum,
                                                                 r.tok_offsets, scores_t, r.tok_denom, r.tok_rows,

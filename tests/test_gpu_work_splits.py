@@ -64,6 +64,7 @@ def test_few_rows_per_expert(T, d, n, E, K, zipf, biased):
     (4097, 128, 64, 8, None),    # the first T past it
     (200, 128, 1024, 2, "up"),   # the largest E of the form, transposed scores beyond 64 KB of LDS
     (200, 128, 1032, 2, None),   # the first E past it
+    (700, 128, 2056, 4, None),   # three workgroups of rows, the last partial, each over three passes of experts
 ])
 def test_few_token_routing(T, d, E, K, mode):
     """The routing of few tokens: its own router against the oracle's logits,
