@@ -36,12 +36,15 @@ struct RouterTopkArgs {
 bool router_topk_fusable(int E, int K);
 hipError_t launch_router_topk(const RouterTopkArgs& a, hipStream_t s);
 
-// Routing of few tokens (T <= kFewTokens, E <= kFewExperts): the router GEMM's
+// Routing of few tokens (T <= kFewTokens, E <= kFewExperts, 32-bit offsets within
+// W_r): the router GEMM's
 // partial logits of `slices` k slices [slices][T][E], then a wave per token for
 // softmax and top-K, then (T > kFewOneGroup) one launch of metadata.
 constexpr int kFewTokens = 4096, kFewExperts = 1024;
 constexpr int kFewOneGroup = 16;  // tokens whose top-K and metadata are one launch
-inline bool route_few(int T, int E) { return T <= kFewTokens && E <= kFewExperts; }
+inline bool route_few(int T, int d, int E) {
+  return T <= kFewTokens && E <= kFewExperts && (int64_t)d * E <= INT32_MAX;
+}
 struct RouterPartArgs {
   const uint16_t* X; const uint16_t* Wr; float* part; int T, d, E, slice;
 };

@@ -386,7 +386,7 @@ int moe_route(moe_dims m, const moe_bf16* X, const moe_bf16* Wr, const float* bi
   const float* in = r->scores;
   const bool counts_only = (flags & MOE_ROUTE_COUNTS_ONLY) != 0;
   r->state = MOE_ROUTING_STATE_EMPTY;  // until the metadata launch is enqueued
-  if (smoe::route_few(m.T, m.E)) {
+  if (smoe::route_few(m.T, m.d, m.E)) {
     // few tokens: partial logits of the router's k slices in the routing's
     // scratch (one slice: in r->scores, which the softmax then overwrites)
     const bool fused = !scores_in && !(flags & MOE_ROUTE_SEPARATE_TOPK) && smoe::router_topk_fusable(m.E, m.K);

@@ -101,6 +101,24 @@ def test_few_token_routing(T, d, E, K, mode):
             np.testing.assert_array_equal(t["counts"].cpu().numpy(), member.sum(0))
 
 
+def test_router_weights_past_32_bit_offsets():
+    """W_r of 2^32 values and more (the few-token router's offsets have 32 bits):
+    the logits come from the last row of W_r, the only one that is not zero."""
+    from test_gpu_parity import _torch
+    torch = _torch()
+    from paper_2512_14080_amd import binding as B
+    d, E = (1 << 22) + 128, 1024
+    X = torch.zeros((1, d), dtype=torch.bfloat16, device="cuda")
+    Wr = torch.zeros((d, E), dtype=torch.bfloat16, device="cuda")
+    X[0, -1] = 1.0
+    Wr[-1] = torch.arange(E, device="cuda") / 256.0  # at most 8 significant bits up to 1, rounded beyond
+    D = B.dims(1, d, 64, E, 8)
+    r = B.Routing(D, 8, B.MOE_ROUTING_LOGITS)
+    B.moe_route(D, X, Wr, None, B.MOE_ROUTE_WRITE_LOGITS, r)
+    torch.cuda.synchronize()
+    assert torch.equal(r.arrays()["logits"][0], Wr[-1].float())
+
+
 @pytest.mark.parametrize("T,E,K", [(16, 8, 8), (17, 72, 5), (70, 136, 8), (33, 264, 16), (90, 520, 7), (20, 1024, 1)])
 def test_few_token_selection_with_ties(T, E, K):
     """Given scores with many equal values, zeros of both signs and rows of one

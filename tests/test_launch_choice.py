@@ -1,0 +1,20 @@
+"""Which kernels the host path chooses: the rules on sizes, without a GPU."""
+import os
+
+import pytest
+
+from launch_recorder import record
+from paper_2512_14080_amd import binding as B
+
+pytestmark = pytest.mark.skipif(not os.path.exists(B.LIB_PATH), reason="libsonicmoe.so not built")
+
+
+def names(launches):
+    return [l[0] for l in launches]
+
+
+def test_few_token_router_within_32_bit_offsets(tmp_path):
+    """W_r of more than 2^32 values: not the few-token router, whose offsets have 32 bits."""
+    small, large = record([{"call": "route", "dims": (1, d, 64, 1024, 8)} for d in (1 << 20, (1 << 22) + 128)], tmp_path)
+    assert "StreamRouter" in names(small)[0]
+    assert not any("StreamRouter" in n for n in names(large)) and "OpRouter" in names(large)[0]
