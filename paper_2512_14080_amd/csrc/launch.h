@@ -106,6 +106,7 @@ struct DHArgs {
   const float* bq;
 };
 int dh_n_tiles(int n, int64_t rows, int E);  // dS partials per row
+inline int dh_max_n_tiles(int n) { return (n + 63) / 64; }  // at the narrowest tile
 hipError_t launch_dh(const DHArgs& a, hipStream_t s);
 
 struct DXtArgs {

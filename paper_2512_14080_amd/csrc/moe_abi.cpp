@@ -163,7 +163,9 @@ size_t abl_layout(const moe_dims& m, int64_t cap, char* base, FwdWs* w, int32_t*
 }
 
 size_t bwd_layout(const moe_dims& m, int64_t cap, char* base, BwdWs* w) {
-  const int nnt = smoe::dh_n_tiles(m.n, (int64_t)m.T * m.K, m.E);
+  // (the narrowest tiles' dS parts: which are taken depends on the device's CUs,
+  // which the size must not)
+  const int nnt = smoe::dh_max_n_tiles(m.n);
   const int splits = smoe::dwr_splits(m.T, m.d, m.E);
   size_t off = 0;
   off = carve(base, off, smoe::mtiles_bytes(cap, m.E), w ? (void**)&w->mtiles : nullptr);

@@ -9,7 +9,7 @@ A call is a dict: "dims" (T, d, n, E, K) and "call", one of
   fwd    moe_fwd on the routing of route, or with "round" = (m_tile, mode) of moe_round_tokens
   bwd    moe_bwd on the same; "dbias", "dS": whether they are asked for
   ws     moe_workspace_bytes of "which", with the default or given "capacity"
-and "cus", the CUs that the device reports (256).
+and "cus", the CUs that the device reports (256; the library asks once per process).
 """
 import ctypes
 import json

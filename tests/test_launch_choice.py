@@ -18,3 +18,11 @@ def test_few_token_router_within_32_bit_offsets(tmp_path):
     small, large = record([{"call": "route", "dims": (1, d, 64, 1024, 8)} for d in (1 << 20, (1 << 22) + 128)], tmp_path)
     assert "StreamRouter" in names(small)[0]
     assert not any("StreamRouter" in n for n in names(large)) and "OpRouter" in names(large)[0]
+
+
+@pytest.mark.parametrize("dims", [(32768, 1536, 256, 128, 8), (1000, 768, 1024, 32, 2), (13676, 2304, 320, 8, 2)])
+@pytest.mark.parametrize("which", [B.MOE_WS_FWD, B.MOE_WS_BWD])
+def test_workspace_size_does_not_depend_on_the_device(tmp_path, dims, which):
+    """A workspace sized on one device (or without one) serves the call on any other."""
+    sizes = [record([{"call": "ws", "dims": dims, "which": which, "cus": c}], tmp_path)[0] for c in (256, 32, 64, 304)]
+    assert len(set(sizes)) == 1, sizes
