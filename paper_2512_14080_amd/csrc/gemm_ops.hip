@@ -1780,10 +1780,10 @@ hipError_t launch_bwd_final_reduce(const FinalReduceArgs& a, hipStream_t s) {
   return hipGetLastError();
 }
 
-int dwr_splits(int T, int d, int E) {
+int dwr_splits(int T, int d, int E, bool dbias) {
   // the output tiles of launch_dwr's configuration: 128 x 64, 128 x 128 or 128
-  // x 256, with the row block of the column sums
-  const int tiles = (d / 128 + 1) * (E <= 128 ? 1 : (E + 255) / 256);
+  // x 256, with the row block of the column sums where they are asked for
+  const int tiles = (d / 128 + dbias) * (E <= 128 ? 1 : (E + 255) / 256);
   int s = 256 / tiles;  // at most one tile per CU: a second round would double the time
   const int max_s = (T + 255) / 256;  // at least 256 tokens per split
   if (s > max_s) s = max_s;

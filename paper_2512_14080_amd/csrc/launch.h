@@ -151,7 +151,7 @@ hipError_t launch_dw1(const DW1Args& a, hipStream_t s);
 struct DWrArgs {
   const uint16_t* X; const uint16_t* dL; float* part; float* bias_part; int T, d, E, splits;
 };
-int dwr_splits(int T, int d, int E);
+int dwr_splits(int T, int d, int E, bool dbias);  // (most without dbias)
 hipError_t launch_dwr(const DWrArgs& a, hipStream_t s);
 
 // Expert biases.  The down-projection bias term of dS, <dO_t, b2_e> for every

@@ -166,7 +166,7 @@ size_t bwd_layout(const moe_dims& m, int64_t cap, char* base, BwdWs* w) {
   // (the narrowest tiles' dS parts: which are taken depends on the device's CUs,
   // which the size must not)
   const int nnt = smoe::dh_max_n_tiles(m.n);
-  const int splits = smoe::dwr_splits(m.T, m.d, m.E);
+  const int splits = smoe::dwr_splits(m.T, m.d, m.E, false);
   size_t off = 0;
   off = carve(base, off, smoe::mtiles_bytes(cap, m.E), w ? (void**)&w->mtiles : nullptr);
   off = carve(base, off, (size_t)cap * 2 * m.n * 2, w ? (void**)&w->dH : nullptr);
@@ -649,7 +649,7 @@ int moe_bwd(moe_dims m, const moe_bf16* dO, const moe_bf16* X, const moe_bf16* H
   LAUNCH(MOE_KC_AGG_DX,
          smoe::launch_agg_dx(w.dXt, ds_in_parts ? w.dS_part : dS_out, ds_in_parts ? nnt : 1, Wr ? w.WrT : nullptr, *r, dX, Wr ? w.dL : nullptr, m.T, m.d, m.E, stream),
          "dX aggregation");
-  const int splits = smoe::dwr_splits(m.T, m.d, m.E);
+  const int splits = smoe::dwr_splits(m.T, m.d, m.E, dbias != nullptr);
   if (dWr || dbias)
     LAUNCH(MOE_KC_DWR,
            smoe::launch_dwr({X, w.dL, dWr ? w.dWr_part : nullptr, dbias ? w.dbias_part : nullptr, m.T, m.d, m.E, splits},

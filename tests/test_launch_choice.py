@@ -26,3 +26,13 @@ def test_workspace_size_does_not_depend_on_the_device(tmp_path, dims, which):
     """A workspace sized on one device (or without one) serves the call on any other."""
     sizes = [record([{"call": "ws", "dims": dims, "which": which, "cus": c}], tmp_path)[0] for c in (256, 32, 64, 304)]
     assert len(set(sizes)) == 1, sizes
+
+
+def test_router_gradient_splits_without_dbias(tmp_path):
+    """dW_r alone has 32 tiles of rows at d = 4096, in eight splits (one per CU); with the row block of dbias there
+    are 33, in seven."""
+    call = {"call": "bwd", "dims": (32768, 4096, 512, 128, 8)}
+    for dbias, splits in ((False, 8), (True, 7)):
+        launches, = record([{**call, "dbias": dbias}], tmp_path)
+        dwr, = [l for l in launches if "OpDWr" in l[0]]
+        assert dwr[1] == -(-splits * (33 if dbias else 32) // 8) * 8
