@@ -71,7 +71,8 @@ typedef struct {
   int32_t state;         /* host-side build state, MOE_ROUTING_STATE_*: set by
                             moe_routing_init / moe_route / moe_round_tokens
                             (what has been enqueued), checked by the consumers */
-  int32_t reserved;      /* zero                                               */
+  int32_t reserved;      /* internal, host-side: m_tile of the rounding that built
+                            it, else zero; it only guides the choice of kernels */
   float *logits;         /* [T,E] router logits (nullable: MOE_ROUTING_LOGITS)  */
   float *scores;         /* [T,E] S_full = softmax over all E experts          */
   float *scores_t;       /* [E,T] transposed S_full (nullable: MOE_ROUTING_SCORES_T;

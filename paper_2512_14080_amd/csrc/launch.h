@@ -89,13 +89,17 @@ hipError_t launch_down(const DownArgs& a, hipStream_t s);
 // fp32 atomic accumulation of s * Y into a.O32 (no Y stored)
 hipError_t launch_down_ablation(const DownArgs& a, int strategy, hipStream_t s);
 
-// The same for few rows per expert (stream_gemm.hip).  stream_row_blocks: the
-// row blocks per workgroup for `rows` routed rows over E experts, or 0 where
-// the tiled GEMMs above (tiles_per_expert tiles of an expert with up to 256
-// rows) are the better ones.
-int stream_row_blocks(int64_t rows, int E, int64_t tiles_per_expert);
-hipError_t launch_stream_up(const UpArgs& a, int mb, int T, hipStream_t s);
-hipError_t launch_stream_down(const DownArgs& a, int strategy, int mb, int T, hipStream_t s);  // MOE_AGG_*
+// The same for few rows per expert (stream_gemm.hip).  stream_shape: for a routing
+// of at most `capacity` rows (m_tile: of the rounding that built it, else 0), or
+// mb = 0 where the tiled GEMMs above (tiles_per_expert tiles of an expert with up to
+// 256 rows) are the better ones.
+struct StreamShape {
+  int mb;       // row blocks per workgroup
+  int further;  // workgroups (per column tile) for the experts' groups past the first
+};
+StreamShape stream_shape(const moe_dims& m, int capacity, int m_tile, int64_t tiles_per_expert);
+hipError_t launch_stream_up(const UpArgs& a, const StreamShape& t, hipStream_t s);
+hipError_t launch_stream_down(const DownArgs& a, int strategy, const StreamShape& t, hipStream_t s);  // MOE_AGG_*
 
 struct DHArgs {
   const uint16_t* dO; const uint16_t* W2; const uint16_t* H; const int32_t* offsets; const int32_t* row_token;

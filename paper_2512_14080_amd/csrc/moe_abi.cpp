@@ -249,23 +249,20 @@ size_t routing_layout(const moe_dims& m, int64_t cap, int flags, char* base, moe
   return off;
 }
 
-// the projections, streaming (few rows per expert; 32-bit offsets within an
-// expert's weights) or tiled
+// the projections, streaming (few rows per expert) or tiled
 struct Projections {
-  int up, down, T;  // row blocks per streaming workgroup; 0: tiled
-  explicit Projections(const moe_dims& m) : up(0), down(0), T(m.T) {
-    if ((int64_t)m.d * 2 * m.n > INT32_MAX) return;
-    up = smoe::stream_row_blocks((int64_t)m.T * m.K, m.E, (2 * m.n + 255) / 256);
-    down = smoe::stream_row_blocks((int64_t)m.T * m.K, m.E, (m.d + 255) / 256);
-  }
+  smoe::StreamShape up, down;  // mb = 0: tiled
+  Projections(const moe_dims& m, const moe_routing& r)
+      : up(smoe::stream_shape(m, r.capacity, r.reserved, (2 * m.n + 255) / 256)),
+        down(smoe::stream_shape(m, r.capacity, r.reserved, (m.d + 255) / 256)) {}
   hipError_t lists(const int32_t* offsets, int E, int32_t* mtiles, hipStream_t s) const {
-    return up && down ? hipSuccess : smoe::launch_mtiles(offsets, E, mtiles, s);
+    return up.mb && down.mb ? hipSuccess : smoe::launch_mtiles(offsets, E, mtiles, s);
   }
   hipError_t run_up(const smoe::UpArgs& a, hipStream_t s) const {
-    return up ? smoe::launch_stream_up(a, up, T, s) : smoe::launch_up(a, s);
+    return up.mb ? smoe::launch_stream_up(a, up, s) : smoe::launch_up(a, s);
   }
   hipError_t run_down(const smoe::DownArgs& a, int strategy, hipStream_t s) const {
-    return down ? smoe::launch_stream_down(a, strategy, down, T, s) : smoe::launch_down_ablation(a, strategy, s);
+    return down.mb ? smoe::launch_stream_down(a, strategy, down, s) : smoe::launch_down_ablation(a, strategy, s);
   }
 };
 
@@ -388,6 +385,7 @@ int moe_route(moe_dims m, const moe_bf16* X, const moe_bf16* Wr, const float* bi
   const float* in = r->scores;
   const bool counts_only = (flags & MOE_ROUTE_COUNTS_ONLY) != 0;
   r->state = MOE_ROUTING_STATE_EMPTY;  // until the metadata launch is enqueued
+  r->reserved = 0;
   if (smoe::route_few(m.T, m.d, m.E)) {
     // few tokens: partial logits of the router's k slices in the routing's
     // scratch (one slice: in r->scores, which the softmax then overwrites)
@@ -457,6 +455,7 @@ int moe_round_tokens(moe_dims m, int32_t m_tile, int mode, const float* u, const
   if (tr == tc || tr->mask == tc->mask) return fail(MOE_ERR_INVALID_ARG, "tr must not alias tc");
   hipStream_t stream = (hipStream_t)stream_;
   tr->state = MOE_ROUTING_STATE_EMPTY;
+  tr->reserved = m_tile;
   smoe::prof_begin(MOE_KC_ROUND, stream);
   bool counted = false;
   uint64_t* list = (uint64_t*)((char*)tr->scratch + round_lists_offset(m));
@@ -503,7 +502,7 @@ int moe_fwd(moe_dims m, const moe_bf16* X, const moe_bf16* W1, const moe_bf16* W
   const int64_t rows = (int64_t)m.T * m.K;
   const smoe::UpArgs up{X, W1, r->offsets, r->row_token, H, w.A, m.d, m.n, m.E, r->capacity, rows, w.mtiles, b1};
   const smoe::DownArgs down{w.A, W2, r->offsets, w.Y, m.d, m.n, m.E, r->capacity, rows, w.mtiles, b2};
-  const Projections proj(m);
+  const Projections proj(m, *r);
   HIP_TRY(proj.lists(r->offsets, m.E, w.mtiles, stream), "m-tile list");
   LAUNCH(MOE_KC_UP, proj.run_up(up, stream), "up-proj");
   LAUNCH(MOE_KC_DOWN, proj.run_down(down, MOE_AGG_GATHER_SUM, stream), "down-proj");
@@ -556,7 +555,7 @@ int moe_fwd_aggregation_ablation(moe_dims m, const moe_bf16* X, const moe_bf16* 
   abl_layout(m, r->capacity, (char*)ws, &w, &dst, &o32);
   hipStream_t stream = (hipStream_t)stream_;
   const int64_t rows = (int64_t)m.T * m.K;
-  const Projections proj(m);
+  const Projections proj(m, *r);
   HIP_TRY(proj.lists(r->offsets, m.E, w.mtiles, stream), "m-tile list");
   LAUNCH(MOE_KC_UP,
          proj.run_up({X, W1, r->offsets, r->row_token, H, w.A, m.d, m.n, m.E, r->capacity, rows, w.mtiles, nullptr}, stream),

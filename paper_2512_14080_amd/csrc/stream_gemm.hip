@@ -54,8 +54,61 @@ __device__ __forceinline__ f32x4 stream_sum(const StreamPart* part, int row, int
   return s;
 }
 
-// grid: x column tiles, y experts (or k slices of the router), z row groups (a
-// y's groups of 16 MB rows are dealt to the z workgroups).  Op supplies
+// The i-th further group (of `rows` rows; each expert's first is not counted, the
+// others follow in expert order): its expert and first row.  False where there are
+// no more than i.  Called by every thread of a workgroup of NT; lds: 18 words.
+template <int NT>
+__device__ __forceinline__ bool find_group(const int32_t* __restrict__ offsets, int E, int rows, int i, int* lds,
+                                           int* expert, int* first_row) {
+  constexpr int kOwn = 8;  // consecutive experts of a thread (E is a multiple of 8)
+  if (i >= offsets[E] / rows) return false;  // (c rows have at most c / rows further groups)
+  int* found = lds + 16;
+  int base = 0;
+  for (int e0 = 0; e0 < E; e0 += kOwn * NT) {
+    const int e = e0 + kOwn * threadIdx.x;
+    int n[kOwn], sum = 0;
+    if (e < E) {
+      int o[kOwn + 1];
+#pragma unroll
+      for (int q = 0; q <= kOwn; ++q) o[q] = offsets[e + q];
+#pragma unroll
+      for (int q = 0; q < kOwn; ++q) {
+        n[q] = o[q + 1] > o[q] ? (o[q + 1] - o[q] - 1) / rows : 0;
+        sum += n[q];
+      }
+    }
+    int total;
+    int at = base + block_excl_scan<NT>(sum, &total, lds);
+    if (base + total > i) {  // here: one thread holds it
+      if (at <= i && i < at + sum)
+#pragma unroll
+        for (int q = 0; q < kOwn; ++q) {
+          if (at <= i && i < at + n[q]) {
+            found[0] = e + q;
+            found[1] = (i - at + 1) * rows;
+          }
+          at += n[q];
+        }
+      __syncthreads();
+      *expert = __builtin_amdgcn_readfirstlane(found[0]);
+      *first_row = __builtin_amdgcn_readfirstlane(found[1]);
+      return true;
+    }
+    base += total;
+  }
+  return false;
+}
+
+// grid: x column tiles.  Router: y k slices, z groups of 16 MB rows.  Experts: y
+// < E the first group of expert y, y >= E the experts' other groups, in expert
+// order.  Most experts have one group, but with a skewed router a hot one has up
+// to T rows; a workgroup past E finds its group in the sums of the experts'
+// further groups (find_group), about 2 us beside the first groups' loads.
+// (Eight workgroups per expert and tile that looped over its groups, most of them
+// empty, ran a hot expert's groups one after the other: T = 1024, d = 1536, n =
+// 256, E = 512, K = 8, Zipf 2: 207 us a forward call, now 134; balanced 291, 284.)
+// Op supplies
+//   EXPERTS: rows and groups by expert,
 //   void rows(p, y, off, cnt): the rows [off, off + cnt),
 //   int k0(p, y), int k(p, y): the reduction, a multiple of 32,
 //   const uint16_t* x_row(p, row) (k contiguous from 0),
@@ -65,9 +118,13 @@ __device__ __forceinline__ f32x4 stream_sum(const StreamPart* part, int row, int
 template <class Op, int MB, int KW, int NBUF, int OCC>
 __global__ __launch_bounds__(64 * KW, OCC) void stream_gemm_kernel(const typename Op::Params p) {
   __shared__ StreamPart part[KW];
-  const int e = blockIdx.y, tile = blockIdx.x;
+  const int tile = blockIdx.x;
+  int e = blockIdx.y, m0 = blockIdx.z * 16 * MB;
+  if constexpr (Op::EXPERTS)
+    if (e >= p.E && !find_group<64 * KW>(p.offsets, p.E, 16 * MB, e - p.E, (int*)part, &e, &m0)) return;
   int off, cnt;
   Op::rows(p, e, off, cnt);
+  if (m0 >= cnt) return;
   const int kbeg = Op::k0(p, e);
   const int lane = lane_id(), g = lane >> 4, l = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -75,58 +132,56 @@ __global__ __launch_bounds__(64 * KW, OCC) void stream_gemm_kernel(const typenam
   const uint16_t* wbase = Op::w(p, e);
   const uint32_t ldw = Op::ldw(p);
   const uint32_t wcol = Op::col(p, tile, l);
-  for (int m0 = blockIdx.z * 16 * MB; m0 < cnt; m0 += gridDim.z * 16 * MB) {
-    const uint16_t* xp[MB];
+  const uint16_t* xp[MB];
 #pragma unroll
-    for (int b = 0; b < MB; ++b) xp[b] = Op::x_row(p, off + min(m0 + 16 * b + l, cnt - 1)) + 8 * g;
-    f32x4 acc[MB][8];
+  for (int b = 0; b < MB; ++b) xp[b] = Op::x_row(p, off + min(m0 + 16 * b + l, cnt - 1)) + 8 * g;
+  f32x4 acc[MB][8];
 #pragma unroll
-    for (int b = 0; b < MB; ++b)
+  for (int b = 0; b < MB; ++b)
 #pragma unroll
-      for (int j = 0; j < 8; ++j) acc[b][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    u32x4 wv[NBUF][8];
-    bf16x8 xv[NBUF][MB];
-    // step s of this wave; a step past the end reads the step 0 addresses (cached, unused)
-    auto load = [&](int buf, int s) {
-      const uint32_t k = kbeg + 32 * (s < ns ? wave + KW * s : wave);
-      const uint32_t o = (k + 8 * g) * ldw + wcol;
+    for (int j = 0; j < 8; ++j) acc[b][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  u32x4 wv[NBUF][8];
+  bf16x8 xv[NBUF][MB];
+  // step s of this wave; a step past the end reads the step 0 addresses (cached, unused)
+  auto load = [&](int buf, int s) {
+    const uint32_t k = kbeg + 32 * (s < ns ? wave + KW * s : wave);
+    const uint32_t o = (k + 8 * g) * ldw + wcol;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) wv[buf][i] = *(const u32x4*)(wbase + (size_t)(o + i * ldw));
+    for (int i = 0; i < 8; ++i) wv[buf][i] = *(const u32x4*)(wbase + (size_t)(o + i * ldw));
 #pragma unroll
-      for (int b = 0; b < MB; ++b) xv[buf][b] = *(const bf16x8*)(xp[b] + k);
-    };
-    if (ns > 0) {
+    for (int b = 0; b < MB; ++b) xv[buf][b] = *(const bf16x8*)(xp[b] + k);
+  };
+  if (ns > 0) {
 #pragma unroll
-      for (int q = 0; q < NBUF; ++q) load(q, q);
-      for (int s = 0;; s += NBUF) {
+    for (int q = 0; q < NBUF; ++q) load(q, q);
+    for (int s = 0;; s += NBUF) {
 #pragma unroll
-        for (int q = 0; q < NBUF; ++q) {
+      for (int q = 0; q < NBUF; ++q) {
 #pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const bf16x8 wf = column_of(wv[q], j);
+        for (int j = 0; j < 8; ++j) {
+          const bf16x8 wf = column_of(wv[q], j);
 #pragma unroll
-            for (int b = 0; b < MB; ++b)
-              acc[b][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[q][b], wf, acc[b][j], 0, 0, 0);
-          }
-          if (s + q + 1 >= ns) goto done;
-          load(q, s + q + NBUF);
+          for (int b = 0; b < MB; ++b)
+            acc[b][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xv[q][b], wf, acc[b][j], 0, 0, 0);
         }
+        if (s + q + 1 >= ns) goto done;
+        load(q, s + q + NBUF);
       }
-    done:;
     }
+  done:;
+  }
 #pragma unroll
-    for (int b = 0; b < MB; ++b) {
-      if (m0 + 16 * b >= cnt) break;
-      __syncthreads();  // the previous rows' sums have been read
+  for (int b = 0; b < MB; ++b) {
+    if (m0 + 16 * b >= cnt) break;
+    __syncthreads();  // the previous rows' sums have been read
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int h = 0; h < 2; ++h)
-          part[wave][4 * g + r][h][l] =
-              f32x4{acc[b][4 * h][r], acc[b][4 * h + 1][r], acc[b][4 * h + 2][r], acc[b][4 * h + 3][r]};
-      __syncthreads();
-      Op::template finish<KW>(p, e, tile, off + m0 + 16 * b, min(16, cnt - m0 - 16 * b), part);
-    }
+      for (int h = 0; h < 2; ++h)
+        part[wave][4 * g + r][h][l] =
+            f32x4{acc[b][4 * h][r], acc[b][4 * h + 1][r], acc[b][4 * h + 2][r], acc[b][4 * h + 3][r]};
+    __syncthreads();
+    Op::template finish<KW>(p, e, tile, off + m0 + 16 * b, min(16, cnt - m0 - 16 * b), part);
   }
 }
 
@@ -141,6 +196,7 @@ __device__ __forceinline__ void expert_rows(const Params& p, int y, int& off, in
 // 0..7) and the matching up columns (8..15)
 struct StreamUp {
   using Params = UpArgs;
+  static constexpr bool EXPERTS = true;
   static __device__ void rows(const Params& p, int y, int& off, int& cnt) { expert_rows(p, y, off, cnt); }
   static __device__ int k0(const Params&, int) { return 0; }
   static __device__ int k(const Params& p, int) { return p.d; }
@@ -185,6 +241,7 @@ struct StreamUp {
 template <int AGG>
 struct StreamDown {
   using Params = DownArgs;
+  static constexpr bool EXPERTS = true;
   static __device__ void rows(const Params& p, int y, int& off, int& cnt) { expert_rows(p, y, off, cnt); }
   static __device__ int k0(const Params&, int) { return 0; }
   static __device__ int k(const Params& p, int) { return p.n; }
@@ -220,28 +277,53 @@ struct StreamDown {
   }
 };
 
-// Row blocks per workgroup (us of up-proj / down-proj, streaming against tiled):
-//   T = 1, d = 1536, n = 256, E = 128, K = 8           mean <= 1   9 / 4.5    26 / 7
-//   T = 64, d = 4096, n = 512, E = 128, K = 8          mean 4      208 / 97   218 / 108
-//   T = 128, d = 768, n = 256, E = 32, K = 4           mean 16     9.2 / 6.1  17 / 7.6
-//   T = 256, d = 4096, n = 512, E = 128, K = 8         mean 16     219 / 108  223 / 110
-//   T = 512, the same                                  mean 32     230 / 118  226 / 112
-//   T = 256, d = 1536, n = 1024, E = 16, K = 2         mean 32     29 / 18    41 / 25
-//   T = 512, d = 1024, n = 256, E = 64, K = 8          mean 64     25 / 18    30 / 12.6
-// Up to about 20 rows the weights bind and streaming is never behind.  Beyond,
-// its four row blocks cost registers and row loads, and it only wins where the
-// tiled GEMM has too few tiles for the CUs (the fifth and sixth lines: 128 and 96
-// tiles up and down; 128 against 256 in the last).
-int stream_row_blocks(int64_t rows, int E, int64_t tiles_per_expert) {
-  const int64_t mean = (rows + E - 1) / E;
-  if (mean <= 10) return 1;
-  if (mean <= 20) return 2;
-  return mean <= 64 && E * tiles_per_expert < 192 ? 4 : 0;
+// Row blocks per workgroup.  (up + down) streaming / tiled, with mb = 1 | mb = 2, for
+// balanced experts and for a router skewed by Zipf exponents 0.5 to 2 (the worst):
+//                                            mean 2       8            12           16
+//   d = 1024, n = 256, E = 64, K = 8         .84|.83      .91|.89      1.12|.92     1.20|.95
+//     skewed                                 .81|.80      1.15|1.01    1.15|1.10    1.16|1.08
+//   d = 1536, n = 256, E = 256, K = 8        .78|.79      .91|.86      .97|.89      1.20|.90
+//     skewed                                 .85|.81      1.08|.97     1.17|.99     1.42|1.11
+//   d = 1024, n = 128, E = 1024, K = 8       .74|.75      .80|.78      .88|.80      1.11|.84
+//     skewed                                 .76|.79      1.24|1.01    1.41|1.08    1.65|1.22
+//   d = 4096, n = 512, E = 128, K = 8        .90|.90      1.03|.95     1.10|.95     1.36|.97
+//     skewed                                 .89|.93      1.10|1.03    1.21|1.07    1.26|1.09
+//   d = 1024, n = 256, E = 16, K = 8         .61|.63      .59|.63      .67|.69      .69|.70
+//     skewed                                 .66|.67      .62|.68      .72|.71      .75|.72
+// An expert with more rows than a group has its weights read again per group, so
+// two row blocks are the better ones from a few rows per expert on, skewed or not
+// (with at most 16 tokens no expert fills a second).  Up to 12 rows per expert
+// streaming is the faster one and a skewed router costs it little; up to 20 it
+// depends on the skew, more so the more tokens a hot expert can have (T = 2048 in
+// the third line: 69 us against 57).  Beyond, and for more tokens, the tiled GEMMs
+// are taken, except where they have too few tiles for the CUs:
+//   d = 1536, n = 1024, E = 16, K = 2, T = 256, mean 32   up 29 / 41   down 18 / 25
+// A rounded routing's experts have no rows or m_tile and more, whatever the mean:
+//   T = 512, d = 1536, n = 256, E = 256, K = 8 (mean 16), rounded up to 256:
+//   forward call 1088 us streaming, 350 tiled; d = 4096, n = 512, up to 128: 2923, 826
+StreamShape stream_shape(const moe_dims& m, int capacity, int m_tile, int64_t tiles_per_expert) {
+  const StreamShape tiled{0, 0};
+  if ((int64_t)m.d * 2 * m.n > INT32_MAX) return tiled;  // 32-bit offsets within an expert's weights
+  const int64_t mean = std::max<int64_t>(((int64_t)m.T * m.K + m.E - 1) / m.E, m_tile);
+  const bool few_tiles = m.E * tiles_per_expert < 192;
+  int mb;
+  if (m.T <= 16 || mean <= 2)
+    mb = 1;
+  else if (mean <= (few_tiles || m.T <= 2048 ? 20 : 12))
+    mb = 2;
+  else if (mean <= 64 && few_tiles)
+    mb = 4;
+  else
+    return tiled;
+  // further groups of at most `capacity` rows over experts of at most T
+  const int64_t rows = 16 * mb, further = std::min(capacity / rows, m.E * ((m.T - 1) / rows));
+  return m.E + further <= 65535 ? StreamShape{mb, (int)further} : tiled;
 }
 
 // Partial router logits of k slice y: part[y][t][e] = sum over the slice of X W_r
 struct StreamRouter {
   using Params = RouterPartArgs;
+  static constexpr bool EXPERTS = false;
   static __device__ void rows(const Params& p, int, int& off, int& cnt) {
     off = 0;
     cnt = p.T;
@@ -285,19 +367,16 @@ static hipError_t run_stream(const typename Op::Params& p, dim3 grid, int mb, in
   return hipGetLastError();
 }
 
-// grid of an expert GEMM: groups of one expert past the eighth are looped over
-static dim3 stream_grid(int tiles, int E, int mb, int T) {
-  return dim3(tiles, E, std::min((T + 16 * mb - 1) / (16 * mb), 8));
-}
+static dim3 stream_grid(int tiles, int E, const StreamShape& t) { return dim3(tiles, E + t.further); }
 
-hipError_t launch_stream_up(const UpArgs& a, int mb, int T, hipStream_t s) {
-  return run_stream<StreamUp>(a, stream_grid(a.n / 64, a.E, mb, T), mb, a.d, s);
+hipError_t launch_stream_up(const UpArgs& a, const StreamShape& t, hipStream_t s) {
+  return run_stream<StreamUp>(a, stream_grid(a.n / 64, a.E, t), t.mb, a.d, s);
 }
-hipError_t launch_stream_down(const DownArgs& a, int strategy, int mb, int T, hipStream_t s) {
-  const dim3 grid = stream_grid(a.d / kStreamCols, a.E, mb, T);
-  if (strategy == MOE_AGG_SCATTER_SUM) return run_stream<StreamDown<1>>(a, grid, mb, a.n, s);
-  if (strategy == MOE_AGG_ATOMIC_F32) return run_stream<StreamDown<2>>(a, grid, mb, a.n, s);
-  return run_stream<StreamDown<0>>(a, grid, mb, a.n, s);
+hipError_t launch_stream_down(const DownArgs& a, int strategy, const StreamShape& t, hipStream_t s) {
+  const dim3 grid = stream_grid(a.d / kStreamCols, a.E, t);
+  if (strategy == MOE_AGG_SCATTER_SUM) return run_stream<StreamDown<1>>(a, grid, t.mb, a.n, s);
+  if (strategy == MOE_AGG_ATOMIC_F32) return run_stream<StreamDown<2>>(a, grid, t.mb, a.n, s);
+  return run_stream<StreamDown<0>>(a, grid, t.mb, a.n, s);
 }
 
 // Row blocks of the router's workgroups: one (16 tokens) while that gives up to

@@ -35,13 +35,19 @@ def test_weight_gradients_of_equal_experts():
 @pytest.mark.parametrize("T,d,n,E,K,zipf", [
     (1, 128, 64, 8, 1, 0.0),      # one row; fewer k steps (n: 2, d: 4) than waves
     (3, 384, 192, 40, 3, 0.0),    # one row block, the last of the k splits uneven
-    (10, 896, 320, 8, 8, 0.0),    # one row block at its largest mean (10 rows an expert), K = E
-    (11, 768, 256, 8, 8, 0.0),    # two row blocks
+    (10, 896, 320, 8, 8, 0.0),    # one row block of 10 rows, K = E
+    (16, 768, 256, 8, 8, 0.0),    # its largest T
+    (17, 768, 256, 8, 8, 0.0),    # two row blocks
+    (11, 768, 256, 8, 8, 0.0),
     (20, 256, 128, 16, 16, 0.0),  # two row blocks at their largest mean (20)
     (21, 256, 128, 16, 16, 0.0),  # four row blocks
     (128, 640, 192, 8, 4, 0.0),   # four at their largest mean (64), rows past one group
     (129, 640, 192, 8, 4, 0.0),   # the tiled GEMMs
     (150, 256, 64, 120, 8, 1.5),  # skewed: empty experts, and experts with many groups of 16 rows
+    (300, 128, 64, 2056, 4, 1.5),  # the same over more experts than one pass of the group search holds
+    (600, 640, 192, 320, 8, 1.5),  # of 32 rows
+    (600, 384, 192, 320, 1, 1.5),  # of 16 rows (mean 2)
+    (140, 640, 192, 24, 8, 3.0),  # of 64 rows
 ])
 @pytest.mark.parametrize("biased", [False, True])
 def test_few_rows_per_expert(T, d, n, E, K, zipf, biased):

@@ -36,3 +36,27 @@ def test_router_gradient_splits_without_dbias(tmp_path):
         launches, = record([{**call, "dbias": dbias}], tmp_path)
         dwr, = [l for l in launches if "OpDWr" in l[0]]
         assert dwr[1] == -(-splits * (33 if dbias else 32) // 8) * 8
+
+
+def test_projections_of_a_rounded_routing(tmp_path):
+    """Experts rounded up to m_tile rows have that many, whatever the mean of the token choice: above the streaming
+    projections' range the tiled ones run."""
+    dims = (512, 1536, 256, 256, 8)  # mean 16
+    forms = [None, (16, "nearest"), (16, "up"), (32, "nearest"), (128, "up"), (256, "up")]
+    calls = [{"call": "fwd", "dims": dims, **({"round": f} if f else {})} for f in forms]
+    stream = [["StreamUp" in "".join(names(l)), "StreamDown" in "".join(names(l))] for l in record(calls, tmp_path)]
+    assert stream == 3 * [[True, True]] + 3 * [[False, False]]
+
+
+@pytest.mark.parametrize("T,E,K,rows", [(1000, 512, 8, 32), (4000, 2048, 4, 32), (4000, 256, 1, 0), (2000, 256, 1, 32),
+                                        (17, 8, 8, 32), (16, 16, 16, 16), (200, 512, 4, 16)])
+def test_streaming_grid_holds_a_hot_experts_groups(tmp_path, T, E, K, rows):
+    """The experts' first groups of `rows` rows and all that a skewed router can add (K hot experts with every token),
+    each with a workgroup of its own; not from 12 rows per expert on where an expert can have many groups (rows 0)."""
+    launches, = record([{"call": "fwd", "dims": (T, 1536, 256, E, K)}], tmp_path)
+    if not rows:
+        assert not any("stream_gemm_kernel" in l[0] for l in launches)
+        return
+    for l in launches[:2]:
+        assert "stream_gemm_kernel" in l[0] and l[3] == 1
+        assert E + K * ((T - 1) // rows) <= l[2] <= E + T * K // rows
