@@ -6,10 +6,12 @@
 // the top-K kernel in Appendix D (equal scores go to the lower expert index).
 // Unlike that kernel, the expert index is not packed into the low mantissa
 // bits: the comparison uses the exact (score, index) pair, so no score is
-// perturbed.  One wave64 handles one token at a time; the K winners are found
-// by K rounds of a wave-wide arg-max over (score desc, index asc).  A
-// workgroup owns 64 consecutive tokens, i.e. one 64-bit word of every
-// expert's membership bitmap, which it assembles in LDS.
+// perturbed.  Three forms: a lane per token (topk_lane_kernel: E <= 256, many
+// tokens), a wave per token over a workgroup of 64 consecutive tokens, i.e. one
+// 64-bit word of every expert's membership bitmap, assembled in LDS
+// (topk_route_kernel: more experts), and a wave per token with the metadata
+// formed from the lists (topk_few_kernel: few tokens).  The waves select their
+// token's K winners by arg-max rounds or over the key bits (wave_topk).
 #include "device_common.h"
 #include "launch.h"
 #include "topk_net.h"
@@ -21,21 +23,30 @@ namespace smoe {
 // of the K positions, by some lane, with w the value over the selected values'
 // sum (added in ascending expert order).
 //
-// EPL <= 16: a select over the bits of the 32-bit keys, most significant first,
-// on ballots.  The candidates with the bit set replace the candidates if they
-// are as many as still wanted, else they are selected and the others stay; it
-// stops once the candidates are exactly as many as wanted, after about half of
-// the bits.  Equal keys at the end go to the lowest experts (lowest j, then
-// lowest lane).  Scalar masks and counts, one vector compare per bit: K rounds
-// of a wave-wide arg-max (six dependent DPP steps each) took 5 us per token
-// with 16 waves on a CU, and the EPL > 16 form below, whose masks would not fit
-// the scalar registers, still does them.
+// Small K: K rounds of a wave-wide arg-max (six dependent DPP steps each).
+// Larger K, EPL <= 16 (beyond, the masks would not fit the scalar registers): a
+// select over the bits of the 32-bit keys, most significant first, on ballots.  The
+// candidates with the bit set replace the candidates if they are as many as still
+// wanted, else they are selected and the others stay; it stops once the candidates
+// are exactly as many as wanted, after about half of the bits.  Equal keys at the
+// end go to the lowest experts (lowest j, then lowest lane).  Scalar masks and
+// counts, one vector compare per bit, whatever K.  us of the top-K launch, rounds /
+// bits:
+//   T = 4096, E = 64     K = 1 6.7 / 7.3    4 7.5 / 7.9    6 8.2 / 8.5    8 9.3 / 8.7    16 12.0 / 9.3
+//   T = 16, E = 64             7.3 / 8.8      9.0 / 8.5      9.7 / 8.6     11.1 / 9.2      14.1 / 10.2
+//   T = 4096, E = 256          8.1 / 11.5     9.9 / 13.0    11.7 / 13.2    13.3 / 13.8     20.1 / 15.0
+//   T = 4096, E = 1024        11.9 / 29.5    20.2 / 32.3    26.0 / 33.2    31.1 / 35.8     52.7 / 41.9
+//   T = 16384, E = 512        19.4 / 47.4    36.6 / 55.3    48.0 / 57.7    58.8 / 61.2    103.5 / 67.1
+template <int EPL>
+constexpr int kBitSelectK = EPL == 1 ? 6 : EPL <= 4 ? 8 : EPL <= 16 ? 9 : 17;
 template <int EPL, class Put>
 __device__ __forceinline__ void wave_topk(const float (&v)[EPL], int E, int K, Put put) {
   static_assert(EPL >= 1 && EPL <= 64, "the taken mask holds one bit per value of a lane");
   const int lane = lane_id();
   float denom = 0.f;
-  if constexpr (EPL <= 16) {
+  bool bits = false;
+  if constexpr (kBitSelectK<EPL> <= 16) bits = K >= kBitSelectK<EPL>;
+  if (bits) {
     uint32_t key[EPL];
     int rank[EPL];
     uint64_t alive[EPL], sel[EPL];

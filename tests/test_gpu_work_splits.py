@@ -125,8 +125,12 @@ def test_router_weights_past_32_bit_offsets():
     assert torch.equal(r.arrays()["logits"][0], Wr[-1].float())
 
 
-@pytest.mark.parametrize("T,E,K", [(16, 8, 8), (17, 72, 5), (70, 136, 8), (33, 264, 16), (90, 520, 7), (20, 1024, 1)])
-def test_few_token_selection_with_ties(T, E, K):
+@pytest.mark.parametrize("T,E,K", [
+    (16, 8, 8), (17, 72, 5), (70, 136, 8), (33, 264, 16), (90, 520, 7), (20, 1024, 1),
+    (16, 64, 5), (40, 64, 6), (40, 136, 7), (33, 264, 8), (16, 1024, 9),  # both selects, on both sides of their rule
+    (4100, 264, 8), (4100, 520, 9), (4100, 1024, 2),                      # past the few-token form
+])
+def test_wave_per_token_selection_with_ties(T, E, K):
     """Given scores with many equal values, zeros of both signs and rows of one
     value: the selection still takes the lowest experts, in the oracle's order."""
     from test_gpu_parity import _torch, check_routing, oracle_routing
