@@ -37,13 +37,33 @@ bool router_topk_fusable(int E, int K);
 hipError_t launch_router_topk(const RouterTopkArgs& a, hipStream_t s);
 
 // Routing of few tokens (T <= kFewTokens, E <= kFewExperts, 32-bit offsets within
-// W_r): the router GEMM's
-// partial logits of `slices` k slices [slices][T][E], then a wave per token for
-// softmax and top-K, then (T > kFewOneGroup) one launch of metadata.
+// W_r): the router GEMM's partial logits of `slices` k slices [slices][T][E], then a
+// wave per token for softmax and top-K, then (T > kFewOneGroup) one launch of
+// metadata, which every workgroup forms from all T K list entries.  us of moe_route,
+// few-token form / other path:
+//                                    T = 2048       4096        6144        8192       16384
+//   d = 1024, E = 64, K = 8          17.7 / 28.7    20.6 / 29.2 29.4 / 29.3 32.4 / 29.6 50 / 31
+//   d = 1536, E = 128, K = 8         21.3 / 38.9    24.4 / 39.4 37 / 40     41 / 41    62 / 42
+//   d = 2048, E = 256, K = 8         27.9 / 64.7    39.5 / 65.7 51 / 68     55 / 69    89 / 73
+//   d = 4096, E = 8, K = 2           23.4 / 38.6    24.9 / 39.5 39 / 40     41 / 40    55 / 41
+//   d = 1536, E = 512, K = 8         40.6 / 101.5   48.8 / 104  69 / 105    73 / 106   130 / 113
+// 4096 is below every crossing; with E >= 256 the form would pay to 8192.
 constexpr int kFewTokens = 4096, kFewExperts = 1024;
 constexpr int kFewOneGroup = 16;  // tokens whose top-K and metadata are one launch
-inline bool route_few(int T, int d, int E) {
-  return T <= kFewTokens && E <= kFewExperts && (int64_t)d * E <= INT32_MAX;
+// counts_only: its metadata counts the top-K entries in LDS, where the other path
+// only sums bitmap words; with few experts and many entries that is the faster one
+// (one_launch: router and top-K fuse there).  us, few-token form / other path:
+//   E = 64, K = 8, d = 128   T = 1024 13.2 / 12.9   2048 14.9 / 13.3   4096 17.5 / 13.5
+//   E = 64, K = 8, d = 768   T = 2048 16.2 / 17.2   3072 17.8 / 17.6   4096 18.9 / 17.4
+//   E = 128, K = 8, d = 128  T = 2048 16.6 / 17.9   3072 18.4 / 18.0   4096 19.6 / 18.4
+//   E = 64, K = 2, d = 128   T = 4096 11.5 / 13.0;  E = 256, K = 8 26.3 / 33.1
+//   scores given, K = 8      E = 8 T = 256 6.6 / 6.3, 4096 11.5 / 6.4;  E = 64 T = 2048 11.5 / 11.4
+inline bool route_few(const moe_dims& m, bool counts_only, bool scores_in, bool one_launch) {
+  if (m.T > kFewTokens || m.E > kFewExperts || (int64_t)m.d * m.E > INT32_MAX) return false;
+  if (!counts_only || m.T <= kFewOneGroup) return true;
+  const int64_t entries = (int64_t)m.T * m.K;
+  if (scores_in) return entries <= 256 * m.E;
+  return !one_launch || m.E > 128 || entries <= 8192 + 18 * (int64_t)m.d + (m.E > 64 ? 16384 : 0);
 }
 struct RouterPartArgs {
   const uint16_t* X; const uint16_t* Wr; float* part; int T, d, E, slice;

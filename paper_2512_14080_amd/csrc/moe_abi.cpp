@@ -386,10 +386,10 @@ int moe_route(moe_dims m, const moe_bf16* X, const moe_bf16* Wr, const float* bi
   const bool counts_only = (flags & MOE_ROUTE_COUNTS_ONLY) != 0;
   r->state = MOE_ROUTING_STATE_EMPTY;  // until the metadata launch is enqueued
   r->reserved = 0;
-  if (smoe::route_few(m.T, m.d, m.E)) {
+  const bool fused = !scores_in && !(flags & MOE_ROUTE_SEPARATE_TOPK) && smoe::router_topk_fusable(m.E, m.K);
+  if (smoe::route_few(m, counts_only, scores_in, fused)) {
     // few tokens: partial logits of the router's k slices in the routing's
     // scratch (one slice: in r->scores, which the softmax then overwrites)
-    const bool fused = !scores_in && !(flags & MOE_ROUTE_SEPARATE_TOPK) && smoe::router_topk_fusable(m.E, m.K);
     float* logits = !scores_in && (flags & MOE_ROUTE_WRITE_LOGITS) ? r->logits : nullptr;
     const int slices = scores_in ? 1 : smoe::router_slices(m.T, m.d, m.E, smoe::round_scratch_bytes(m.T, m.E));
     float* part = slices > 1 ? (float*)((char*)r->scratch + round_lists_offset(m)) : r->scores;
@@ -414,7 +414,7 @@ int moe_route(moe_dims m, const moe_bf16* X, const moe_bf16* Wr, const float* bi
     r->state = counts_only ? MOE_ROUTING_STATE_COUNTS : MOE_ROUTING_STATE_BUILT;
     return MOE_OK;
   }
-  if (!scores_in && !(flags & MOE_ROUTE_SEPARATE_TOPK) && smoe::router_topk_fusable(m.E, m.K)) {
+  if (fused) {
     float* logits = (flags & MOE_ROUTE_WRITE_LOGITS) ? r->logits : nullptr;
     smoe::RouterTopkArgs a{X, Wr, bias, logits, r->scores, scores_t, r->topk_idx, r->topk_w, r->mask,
                            m.T, m.d, m.E, m.K, r->words};

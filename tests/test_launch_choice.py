@@ -60,3 +60,20 @@ def test_streaming_grid_holds_a_hot_experts_groups(tmp_path, T, E, K, rows):
     for l in launches[:2]:
         assert "stream_gemm_kernel" in l[0] and l[3] == 1
         assert E + K * ((T - 1) // rows) <= l[2] <= E + T * K // rows
+
+
+@pytest.mark.parametrize("dims,scores_in,few", [
+    ((1024, 128, 64, 64, 8), False, True), ((2048, 128, 64, 64, 8), False, False), ((2048, 768, 64, 64, 8), False, True),
+    ((4096, 768, 64, 64, 8), False, False), ((4096, 128, 64, 64, 2), False, True), ((4096, 128, 64, 128, 8), False, False),
+    ((4096, 128, 64, 256, 8), False, True), ((4096, 128, 64, 64, 16), False, True), ((256, 128, 64, 8, 8), True, True),
+    ((512, 128, 64, 8, 8), True, False), ((16, 128, 64, 8, 8), True, True), ((17, 128, 64, 8, 8), True, True),
+])
+def test_few_token_routing_for_counts_only(tmp_path, dims, scores_in, few):
+    """Where only the counts are wanted, the few-token form is left where its metadata costs more than the bitmap's;
+    the complete routing of the same sizes keeps it."""
+    flags = B.MOE_ROUTE_SCORES_IN if scores_in else 0
+    full, counts = record([{"call": "route", "dims": dims, "flags": flags | f} for f in (0, B.MOE_ROUTE_COUNTS_ONLY)],
+                          tmp_path)
+    assert any("topk_few" in n for n in names(full))
+    assert any("topk_few" in n for n in names(counts)) == few
+    assert any("expert_scan" in n for n in names(counts)) == (not few)
