@@ -155,7 +155,9 @@ def test_wide_tiles_on_short_loops():
     """Enough experts for the 256 x 256 tiles of every GEMM, with the loops at
     their shortest: down (k = n = 64) and dX~ (k = 2n = 128) on the split LDS
     ring, and weight gradients over experts of 0 to 4 k steps of 64 rows."""
-    check_layer(W.MoEConfig("ring", T=1600, d=768, n=64, E=72, K=2, m_tile=64), seed=36)
+    cfg = W.MoEConfig("ring", T=1600, d=768, n=64, E=72, K=2, m_tile=64)
+    check_layer(cfg, seed=36)
+    check_layer(cfg, seed=36, eb=expert_biases(cfg, 36))
     cfg = W.MoEConfig("kshort", T=1200, d=512, n=256, E=72, K=2, m_tile=64)
     bias = np.concatenate([[-40.0], np.linspace(-5.0, 1.5, cfg.E - 1)]).astype(np.float32)
     for mode in (None, "nearest"):

@@ -1,5 +1,6 @@
 """Which kernels the host path chooses: the rules on sizes, without a GPU."""
 import os
+import re
 
 import pytest
 
@@ -77,3 +78,18 @@ def test_few_token_routing_for_counts_only(tmp_path, dims, scores_in, few):
     assert any("topk_few" in n for n in names(full))
     assert any("topk_few" in n for n in names(counts)) == few
     assert any("expert_scan" in n for n in names(counts)) == (not few)
+
+
+@pytest.mark.parametrize("d,n,plain", [(1536, 256, {"OpUp", "OpDown", "OpDH", "OpDXt"}), (1664, 448, set()),
+                                       (2048, 512, {"OpUp", "OpDH"}), (1024, 1024, {"OpDown", "OpDH", "OpDXt"})])
+def test_whole_tiles_in_row_order(tmp_path, d, n, plain):
+    """256-wide tiles that all lie within the matrix, fewer than eight to a row, take the kernels without column limits
+    and blocked order; an uneven last tile or longer rows the general ones."""
+    fwd, bwd = record([{"call": c, "dims": (32768, d, n, 128, 8), "dbias": True} for c in ("fwd", "bwd")], tmp_path)
+    found = {}
+    for name in names(fwd + bwd):
+        m = re.search(r"(OpUp|OpDown|OpDH|OpDXt)INS_7GemmCfgILi256ELi256E.*?EEE(Li0E)?Lb([01])E", name)
+        if m:
+            found[m.group(1)] = m.group(3) == "1"
+    assert set(found) == {"OpUp", "OpDown", "OpDH", "OpDXt"}
+    assert {k for k, v in found.items() if v} == plain
