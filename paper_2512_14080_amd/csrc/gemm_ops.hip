@@ -123,6 +123,25 @@ hipError_t launch_mtiles(const int32_t* offsets, int E, int32_t* out, hipStream_
   return hipGetLastError();
 }
 
+// Of the mean rows of the token choice: an expert's last m-tile is half full on
+// average.  A rounded expert has one of the two multiples of m_tile around the mean,
+// and none where that is 0, so a rounding to large tiles leaves fewer experts than
+// the token choice's (with E m-tiles expected, T = 643, d = 1792, n = 448, E = 88, K
+// = 3 rounded to 256, about ten experts left: dH in 256 wide tiles 56 us, in 64 26).
+int64_t expected_mtiles(const moe_dims& m, const moe_routing& r) {
+  const int64_t rows = (int64_t)m.T * m.K;
+  const int t = rounding_tile(r);
+  if (t == 0 || rows > 2 * kMTile * (int64_t)m.E) return std::max<int64_t>(m.E, rows / kMTile + m.E / 2);
+  const int64_t lo = rows / m.E / t * t, hi = lo + t;
+  auto tiles = [&](int64_t f) -> double {
+    return t >= 128 ? (f + kMTile - 1) / kMTile : f ? std::max(1., f / (double)kMTile + .5) : 0.;
+  };
+  double up = (rows / (double)m.E - lo) / t;  // share of the experts rounded up
+  if (rounding_mode(r) == MOE_ROUND_UP) up = hi <= m.T;
+  if (rounding_mode(r) == MOE_ROUND_DOWN) up = 0;
+  return std::max<int64_t>(1, (int64_t)(m.E * (tiles(lo) + up * (tiles(hi) - tiles(lo)))));
+}
+
 // ------------------------------------------------------------ k-chunk list
 // The weight gradients reduce over an expert's rows (varlen K).  With skewed
 // routing a few experts own most rows, and their tiles would run for the
@@ -1618,8 +1637,7 @@ constexpr TileTimes kTimesDown{100, 58, 0};     // down and dX~
 constexpr TileTimes kTimesDH{100, 61, 33};
 
 static int n_tiles(int N, int BN) { return (N + BN - 1) / BN; }
-static int tile_width(const TileTimes& times, int64_t rows, int E, int N) {
-  const int64_t mtiles = std::max<int64_t>(E, rows / kMTile + E / 2);  // about; ragged last tiles included
+static int tile_width(const TileTimes& times, int64_t mtiles, int N) {
   const int64_t cus = cu_count();
   int best = 0;
   int64_t least = 0;
@@ -1642,14 +1660,14 @@ static int tile_width(const TileTimes& times, int64_t rows, int E, int N) {
 static bool plain_256(int N) { return N % 256 == 0 && N < 8 * 256; }
 
 hipError_t launch_up(const UpArgs& a, hipStream_t s) {
-  const int N = 2 * a.n, w = tile_width(kTimesUp, a.rows, a.E, N);
+  const int N = 2 * a.n, w = tile_width(kTimesUp, a.mt, N);
   const int grid = pad8(mtiles_bound(a.capacity, a.E, 256) * n_tiles(N, w));
   if (w == 256 && plain_256(N)) return run<OpUp<C256x256w, true>>({a}, grid, s);
   return w == 256 ? run<OpUp<C256x256w>>({a}, grid, s) : run<OpUp<C256x128>>({a}, grid, s);
 }
 
 hipError_t launch_down(const DownArgs& a, hipStream_t s) {
-  const int w = tile_width(kTimesDown, a.rows, a.E, a.d);
+  const int w = tile_width(kTimesDown, a.mt, a.d);
   const int grid = pad8(mtiles_bound(a.capacity, a.E, 256) * n_tiles(a.d, w));
   if (w == 256 && plain_256(a.d)) return run<OpDown<C256x256s, kAggGather, true>>({a}, grid, s);
   return w == 256 ? run<OpDown<C256x256s>>({a}, grid, s) : run<OpDown<C256x128>>({a}, grid, s);
@@ -1669,10 +1687,10 @@ hipError_t launch_down_ablation(const DownArgs& a, int strategy, hipStream_t s) 
   return launch_down(a, s);
 }
 
-int dh_n_tiles(int n, int64_t rows, int E) { return n_tiles(n, tile_width(kTimesDH, rows, E, n)); }
+int dh_n_tiles(int n, int64_t mt) { return n_tiles(n, tile_width(kTimesDH, mt, n)); }
 
 hipError_t launch_dh(const DHArgs& a, hipStream_t s) {
-  const int w = tile_width(kTimesDH, a.rows, a.E, a.n);
+  const int w = tile_width(kTimesDH, a.mt, a.n);
   const int grid = pad8(mtiles_bound(a.capacity, a.E, 256) * n_tiles(a.n, w));
   if (w == 256 && plain_256(a.n)) return run<OpDH<C256x256w, true>>({a}, grid, s);
   switch (w) {
@@ -1683,7 +1701,7 @@ hipError_t launch_dh(const DHArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_dxt(const DXtArgs& a, hipStream_t s) {
-  const int w = tile_width(kTimesDown, a.rows, a.E, a.d);
+  const int w = tile_width(kTimesDown, a.mt, a.d);
   const int grid = pad8(mtiles_bound(a.capacity, a.E, 256) * n_tiles(a.d, w));
   if (w == 256 && plain_256(a.d)) return run<OpDXt<C256x256ws, true>>({a}, grid, s);
   return w == 256 ? run<OpDXt<C256x256ws>>({a}, grid, s) : run<OpDXt<C256x128>>({a}, grid, s);

@@ -80,24 +80,32 @@ hipError_t launch_topk_few(const float* in, int slices, const float* bias, float
                            const moe_routing& r, int T, int E, int K, int do_softmax, bool counts_only, hipStream_t s);
 hipError_t launch_tc_metadata_few(const moe_routing& r, int T, int E, int K, bool counts_only, hipStream_t s);
 
+// What built a routing, as moe_routing.reserved keeps it: 0 for token choice, else
+// the rounding's m_tile and mode.  It guides the choice of kernels.
+inline int rounding_word(int m_tile, int mode) { return m_tile | mode << 16; }
+inline int rounding_tile(const moe_routing& r) { return r.reserved & 0xffff; }
+inline int rounding_mode(const moe_routing& r) { return r.reserved >> 16; }
+
 // The varlen-M m-tile list (mtiles_kernel): built from the expert offsets
 // once per forward / backward call, read by the up, down, dH and dX~ GEMMs.
 constexpr int kMTile = 256;  // rows of an m-tile
 size_t mtiles_bytes(int64_t capacity, int E);
+// about how many m-tiles a routing has
+int64_t expected_mtiles(const moe_dims& m, const moe_routing& r);
 hipError_t launch_mtiles(const int32_t* offsets, int E, int32_t* out, hipStream_t s);
 
-// rows: the routed rows to expect (T K), for the choice of the tiles; capacity
-// bounds them.
+// mt: the m-tiles to expect (expected_mtiles), for the choice of the tiles; capacity
+// bounds the rows.
 struct UpArgs {
   const uint16_t* X; const uint16_t* W1; const int32_t* offsets; const int32_t* row_token;
-  uint16_t* H; uint16_t* A; int d, n, E, capacity; int64_t rows; const int32_t* mtiles;
+  uint16_t* H; uint16_t* A; int d, n, E, capacity; int64_t mt; const int32_t* mtiles;
   const float* b1;  // [E,2n] expert bias added to H, or null
 };
 hipError_t launch_up(const UpArgs& a, hipStream_t s);
 
 struct DownArgs {
   const uint16_t* A; const uint16_t* W2; const int32_t* offsets; uint16_t* Y; int d, n, E, capacity;
-  int64_t rows; const int32_t* mtiles;
+  int64_t mt; const int32_t* mtiles;
   const float* b2;  // [E,d] expert bias added to Y, or null
   // aggregation ablation only: token-major destination row of each row
   // (scatter), or the fp32 output and the row tokens / weights (atomics)
@@ -124,18 +132,18 @@ hipError_t launch_stream_down(const DownArgs& a, int strategy, const StreamShape
 struct DHArgs {
   const uint16_t* dO; const uint16_t* W2; const uint16_t* H; const int32_t* offsets; const int32_t* row_token;
   const float* row_w; uint16_t* dH; uint16_t* Ap; float* dS; float* dS_part; int d, n, E, capacity;
-  int64_t rows; const int32_t* mtiles;
+  int64_t mt; const int32_t* mtiles;
   // <dO_t, b2_e> of the expert-bias dS term as two fp32 halves [T][2E]
   // (columns e and E + e; see launch_bias_split), or null
   const float* bq;
 };
-int dh_n_tiles(int n, int64_t rows, int E);  // dS partials per row
+int dh_n_tiles(int n, int64_t mt);  // dS partials per row
 inline int dh_max_n_tiles(int n) { return (n + 63) / 64; }  // at the narrowest tile
 hipError_t launch_dh(const DHArgs& a, hipStream_t s);
 
 struct DXtArgs {
   const uint16_t* dH; const uint16_t* W1; const int32_t* offsets; uint16_t* dXt; int d, n, E, capacity;
-  int64_t rows; const int32_t* mtiles;
+  int64_t mt; const int32_t* mtiles;
 };
 hipError_t launch_dxt(const DXtArgs& a, hipStream_t s);
 

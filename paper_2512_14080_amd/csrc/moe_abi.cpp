@@ -253,8 +253,8 @@ size_t routing_layout(const moe_dims& m, int64_t cap, int flags, char* base, moe
 struct Projections {
   smoe::StreamShape up, down;  // mb = 0: tiled
   Projections(const moe_dims& m, const moe_routing& r)
-      : up(smoe::stream_shape(m, r.capacity, r.reserved, (2 * m.n + 255) / 256)),
-        down(smoe::stream_shape(m, r.capacity, r.reserved, (m.d + 255) / 256)) {}
+      : up(smoe::stream_shape(m, r.capacity, smoe::rounding_tile(r), (2 * m.n + 255) / 256)),
+        down(smoe::stream_shape(m, r.capacity, smoe::rounding_tile(r), (m.d + 255) / 256)) {}
   hipError_t lists(const int32_t* offsets, int E, int32_t* mtiles, hipStream_t s) const {
     return up.mb && down.mb ? hipSuccess : smoe::launch_mtiles(offsets, E, mtiles, s);
   }
@@ -455,7 +455,7 @@ int moe_round_tokens(moe_dims m, int32_t m_tile, int mode, const float* u, const
   if (tr == tc || tr->mask == tc->mask) return fail(MOE_ERR_INVALID_ARG, "tr must not alias tc");
   hipStream_t stream = (hipStream_t)stream_;
   tr->state = MOE_ROUTING_STATE_EMPTY;
-  tr->reserved = m_tile;
+  tr->reserved = smoe::rounding_word(m_tile, mode);
   smoe::prof_begin(MOE_KC_ROUND, stream);
   bool counted = false;
   uint64_t* list = (uint64_t*)((char*)tr->scratch + round_lists_offset(m));
@@ -499,9 +499,9 @@ int moe_fwd(moe_dims m, const moe_bf16* X, const moe_bf16* W1, const moe_bf16* W
   FwdWs w;
   fwd_layout(m, r->capacity, (char*)ws, &w);
   hipStream_t stream = (hipStream_t)stream_;
-  const int64_t rows = (int64_t)m.T * m.K;
-  const smoe::UpArgs up{X, W1, r->offsets, r->row_token, H, w.A, m.d, m.n, m.E, r->capacity, rows, w.mtiles, b1};
-  const smoe::DownArgs down{w.A, W2, r->offsets, w.Y, m.d, m.n, m.E, r->capacity, rows, w.mtiles, b2};
+  const int64_t mt = smoe::expected_mtiles(m, *r);
+  const smoe::UpArgs up{X, W1, r->offsets, r->row_token, H, w.A, m.d, m.n, m.E, r->capacity, mt, w.mtiles, b1};
+  const smoe::DownArgs down{w.A, W2, r->offsets, w.Y, m.d, m.n, m.E, r->capacity, mt, w.mtiles, b2};
   const Projections proj(m, *r);
   HIP_TRY(proj.lists(r->offsets, m.E, w.mtiles, stream), "m-tile list");
   LAUNCH(MOE_KC_UP, proj.run_up(up, stream), "up-proj");
@@ -554,13 +554,13 @@ int moe_fwd_aggregation_ablation(moe_dims m, const moe_bf16* X, const moe_bf16* 
   FwdWs w;
   abl_layout(m, r->capacity, (char*)ws, &w, &dst, &o32);
   hipStream_t stream = (hipStream_t)stream_;
-  const int64_t rows = (int64_t)m.T * m.K;
+  const int64_t mt = smoe::expected_mtiles(m, *r);
   const Projections proj(m, *r);
   HIP_TRY(proj.lists(r->offsets, m.E, w.mtiles, stream), "m-tile list");
   LAUNCH(MOE_KC_UP,
-         proj.run_up({X, W1, r->offsets, r->row_token, H, w.A, m.d, m.n, m.E, r->capacity, rows, w.mtiles, nullptr}, stream),
+         proj.run_up({X, W1, r->offsets, r->row_token, H, w.A, m.d, m.n, m.E, r->capacity, mt, w.mtiles, nullptr}, stream),
          "up-proj");
-  smoe::DownArgs da{w.A, W2, r->offsets, w.Y, m.d, m.n, m.E, r->capacity, rows, w.mtiles, nullptr};
+  smoe::DownArgs da{w.A, W2, r->offsets, w.Y, m.d, m.n, m.E, r->capacity, mt, w.mtiles, nullptr};
   if (strategy == MOE_AGG_GATHER_SUM) {
     LAUNCH(MOE_KC_DOWN, proj.run_down(da, strategy, stream), "down-proj");
     LAUNCH(MOE_KC_AGG_O, smoe::launch_agg_o(w.Y, *r, O, m.T, m.d, stream), "aggregation");
@@ -621,8 +621,8 @@ int moe_bwd(moe_dims m, const moe_bf16* dO, const moe_bf16* X, const moe_bf16* H
   bwd_layout(m, r->capacity, (char*)ws, &w);
   hipStream_t stream = (hipStream_t)stream_;
   float* dS_out = dS ? dS : w.dS;
-  const int64_t rows = (int64_t)m.T * m.K;
-  const int nnt = smoe::dh_n_tiles(m.n, rows, m.E);
+  const int64_t rows = (int64_t)m.T * m.K, mt = smoe::expected_mtiles(m, *r);
+  const int nnt = smoe::dh_n_tiles(m.n, mt);
   HIP_TRY(smoe::launch_bwd_lists(r->offsets, m.T, rows, m.E, m.d, m.n, w.mtiles, w.klist2, w.klist1, Wr, Wr ? w.WrT : nullptr,
                                  stream),
           "tile lists and W_r transpose");
@@ -633,7 +633,7 @@ int moe_bwd(moe_dims m, const moe_bf16* dO, const moe_bf16* X, const moe_bf16* H
   }
   LAUNCH(MOE_KC_DH,
          smoe::launch_dh({dO, W2, H, r->offsets, r->row_token, r->row_w, w.dH, w.Ap, dS_out, w.dS_part, m.d, m.n, m.E,
-                          r->capacity, rows, w.mtiles, b2 ? w.bq : nullptr},
+                          r->capacity, mt, w.mtiles, b2 ? w.bq : nullptr},
                          stream),
          "dH");
   // dS in parts (one per N tile of dH): a few are summed where they are read,
@@ -642,7 +642,7 @@ int moe_bwd(moe_dims m, const moe_bf16* dO, const moe_bf16* X, const moe_bf16* H
   if (nnt > 1 && !ds_in_parts)
     HIP_TRY(smoe::launch_reduce_rowparts(w.dS_part, dS_out, r->capacity, nnt, stream), "dS reduce");
   LAUNCH(MOE_KC_DW2, smoe::launch_dw2({w.Ap, dO, r->offsets, r->row_token, dW2, m.T, rows, m.d, m.n, m.E, w.klist2, w.dw2_part}, stream), "dW2");
-  LAUNCH(MOE_KC_DXT, smoe::launch_dxt({w.dH, W1, r->offsets, w.dXt, m.d, m.n, m.E, r->capacity, rows, w.mtiles}, stream),
+  LAUNCH(MOE_KC_DXT, smoe::launch_dxt({w.dH, W1, r->offsets, w.dXt, m.d, m.n, m.E, r->capacity, mt, w.mtiles}, stream),
          "dX~");
   LAUNCH(MOE_KC_DW1, smoe::launch_dw1({X, w.dH, r->offsets, r->row_token, dW1, m.T, rows, m.d, m.n, m.E, w.klist1, w.dw1_part}, stream), "dW1");
   LAUNCH(MOE_KC_AGG_DX,

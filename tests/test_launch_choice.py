@@ -93,3 +93,17 @@ def test_whole_tiles_in_row_order(tmp_path, d, n, plain):
             found[m.group(1)] = m.group(3) == "1"
     assert set(found) == {"OpUp", "OpDown", "OpDH", "OpDXt"}
     assert {k for k, v in found.items() if v} == plain
+
+
+@pytest.mark.parametrize("dims,form,width", [
+    ((643, 1792, 448, 88, 3), None, 256), ((643, 1792, 448, 88, 3), (256, "nearest"), 64),  # about eight experts left
+    ((3084, 4096, 512, 128, 8), None, 64), ((3084, 4096, 512, 128, 8), (128, "up"), 256),  # one m-tile each
+    ((512, 1536, 256, 128, 4), (256, "up"), 128), ((512, 1536, 256, 128, 4), (256, "down"), 64),
+    ((32768, 1536, 256, 128, 8), None, 256), ((32768, 1536, 256, 128, 8), (128, "nearest"), 256),
+])
+def test_tile_width_follows_the_rounding(tmp_path, dims, form, width):
+    """dH's tiles by the m-tiles that the rounding leaves, not by those of the token choice."""
+    call = {"call": "bwd", "dims": dims, "dbias": True, **({"round": form} if form else {})}
+    launches, = record([call], tmp_path)
+    dh, = [n for n in names(launches) if "OpDH" in n]
+    assert f"GemmCfgILi256ELi{width}E" in dh
