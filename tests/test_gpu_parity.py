@@ -158,14 +158,17 @@ def test_k_equals_e_and_k_one():
     check_layer(W.MoEConfig("k1", T=300, d=128, n=64, E=8, K=1, m_tile=16), seed=4)
 
 
-def test_wave_per_token_topk_shapes():
-    """E > 256 takes the wave-per-token top-K (here with K = 3 and K = 12);
-    K in (8, 16] at E <= 256 takes the lane-per-token kernel's 16-slot form
-    (K = 10, and K = E = 16).  The routing and the layer still match."""
-    check_layer(W.MoEConfig("e264", T=300, d=128, n=64, E=264, K=3, m_tile=16), seed=13)
-    check_layer(W.MoEConfig("e264k12", T=300, d=128, n=64, E=264, K=12, m_tile=16), seed=16, round_mode="nearest")
-    check_layer(W.MoEConfig("k10", T=300, d=128, n=64, E=16, K=10, m_tile=16), seed=14, round_mode="nearest")
-    check_layer(W.MoEConfig("k16", T=300, d=128, n=64, E=16, K=16, m_tile=16), seed=17)
+@pytest.mark.parametrize("T", [4200, 300])
+def test_wave_per_token_topk_shapes(T):
+    """With more than 4096 tokens E > 256 takes the wave-per-token top-K over
+    64-token words (here with K = 3, arg-max rounds, and K = 12, the select over
+    the key bits); K in (8, 16] at E <= 256 takes the lane-per-token kernel's
+    16-slot form (K = 10, and K = E = 16).  With fewer all take the few-token
+    form.  The routing and the layer still match."""
+    check_layer(W.MoEConfig("e264", T=T, d=128, n=64, E=264, K=3, m_tile=16), seed=13)
+    check_layer(W.MoEConfig("e264k12", T=T, d=128, n=64, E=264, K=12, m_tile=16), seed=16, round_mode="nearest")
+    check_layer(W.MoEConfig("k10", T=T, d=128, n=64, E=16, K=10, m_tile=16), seed=14, round_mode="nearest")
+    check_layer(W.MoEConfig("k16", T=T, d=128, n=64, E=16, K=16, m_tile=16), seed=17)
 
 
 def test_weight_gradients_over_row_chunks():
@@ -321,7 +324,11 @@ def test_rounding_selection_tiles(T, m_tile, quantised):
         check_routing(layer, R, idx, rdir)
 
 
-def test_routing_with_nonfinite_scores():
+@pytest.mark.parametrize("T,E,K", [(4400, 64, 6),   # lane per token, four waves to a word
+                                   (4400, 24, 3), (4400, 72, 7), (4400, 40, 12),  # one wave (E an odd multiple of 8)
+                                   (4400, 264, 4), (4400, 264, 10),               # wave per token, both selects
+                                   (700, 64, 6), (700, 264, 10), (16, 64, 6)])    # few tokens
+def test_routing_with_nonfinite_scores(T, E, K):
     """Scores holding NaN and +-Inf (a diverged router, or caller-supplied
     scores) still give every token K distinct experts in [0, E), consistent
     counts/offsets/rows, and a rounded routing within capacity; the layer then
@@ -329,7 +336,7 @@ def test_routing_with_nonfinite_scores():
     which is the float order wherever both operands are numbers."""
     torch = _torch()
     from paper_2512_14080_amd.layer import DeviceLayer
-    cfg = W.MoEConfig("nonfinite", T=700, d=128, n=128, E=64, K=6, m_tile=64)
+    cfg = W.MoEConfig("nonfinite", T=T, d=128, n=128, E=E, K=K, m_tile=64)
     inp = W.make_inputs(cfg, 12)
     _, S = oracle_scores(inp)
     rng = np.random.default_rng(5)
@@ -365,13 +372,15 @@ def test_routing_with_nonfinite_scores():
 
 # Shapes at the limits the ABI accepts (E <= 4096, K <= 16) and the
 # wave-per-token top-K instantiations behind them: values per lane EPL =
-# ceil(E / 64) of 4 (E = 256), 16 (E = 1024), 64 (E = 2056 and 4096: lane
-# values 32 .. 63 exercise the upper half of the selection mask).
-@pytest.mark.parametrize("E,K", [(256, 16), (1024, 8), (2056, 16), (4096, 16)])
-def test_wide_expert_counts_route(E, K):
+# ceil(E / 64) of 8 (E = 512), 16 (E = 1024), 32 and 64 (E = 2048, 2056 and 4096:
+# lane values 32 .. 63 exercise the upper half of the selection mask; any T).  Up
+# to 4096 tokens E <= 1024 takes the few-token form, E = 256 beyond the lane-per-token kernel.
+@pytest.mark.parametrize("T,E,K", [(4200, 256, 16), (4200, 512, 5), (4200, 1024, 8), (4200, 1024, 16), (700, 256, 16),
+                                   (700, 1024, 8), (700, 2048, 3), (700, 2056, 16), (700, 4096, 16)])
+def test_wide_expert_counts_route(T, E, K):
     torch = _torch()
     from paper_2512_14080_amd.layer import DeviceLayer
-    cfg = W.MoEConfig(f"e{E}k{K}", T=700, d=128, n=64, E=E, K=K, m_tile=16)
+    cfg = W.MoEConfig(f"e{E}k{K}", T=T, d=128, n=64, E=E, K=K, m_tile=16)
     inp = W.make_inputs(cfg, 21)
     _, S = oracle_scores(inp)
     for mode in (None, "nearest"):

@@ -1,5 +1,9 @@
 """The router GEMM with softmax and top-K fused into its epilogue (E a multiple
-of 8, E <= 256, K <= 8), against the two-launch path and the oracle.
+of 8, E <= 256, K <= 8, more than 4096 tokens), against the two-launch path and the
+oracle, and the few-token form (up to 4096 tokens), whose kernels are the same with
+and without MOE_ROUTE_SEPARATE_TOPK, so that there only the oracle and the rerun
+compare.  Which kernels each shape runs is checked without a GPU
+(test_launch_choice).
 
 Three routings of the same inputs, through the C ABI:
   fused     moe_route (the default where the shapes fuse);
@@ -85,25 +89,36 @@ def check(cfg, seed, T=None, bias=None):
     return o
 
 
-@pytest.mark.parametrize("cfg,T", [
-    (W.CONFIGS["tiny"], None),                                               # E = 8, K = 2 (128 x 64 tiles)
-    (W.MoEConfig("e16", T=3000, d=512, n=64, E=16, K=4, m_tile=128), None),  # ragged last tile
-    (W.MoEConfig("e64", T=700, d=256, n=64, E=64, K=8, m_tile=128), None),
-    (W.MoEConfig("e128", T=1000, d=384, n=64, E=128, K=8, m_tile=128), None),
-    (W.MoEConfig("e8k1", T=130, d=128, n=64, E=8, K=1, m_tile=16), None),
-    (W.MoEConfig("e128t1", T=1, d=128, n=64, E=128, K=8, m_tile=128), None),
-    (W.MoEConfig("e104k5", T=250, d=256, n=64, E=104, K=5, m_tile=16), None),  # 24 idle columns
-    (W.MoEConfig("e256", T=1000, d=256, n=64, E=256, K=8, m_tile=128), None),   # 128 x 256 tiles, two row blocks
-    (W.MoEConfig("e200k6", T=700, d=128, n=64, E=200, K=6, m_tile=64), None),  # 56 idle columns
-])
-def test_fused_router_topk(cfg, T):
-    check(cfg, seed=31, T=T)
+def _cfg(E, K, T, d, m_tile=128):
+    return W.MoEConfig(f"e{E}k{K}t{T}", T=T, d=d, n=64, E=E, K=K, m_tile=m_tile)
 
 
-def test_fused_router_topk_with_bias_and_ties():
+FEW = [W.CONFIGS["tiny"], _cfg(16, 4, 3000, 512), _cfg(64, 8, 700, 256), _cfg(128, 8, 1000, 384), _cfg(8, 1, 130, 128),
+       _cfg(128, 8, 1, 128), _cfg(104, 5, 250, 256), _cfg(256, 8, 1000, 256), _cfg(200, 6, 700, 128)]
+FUSED = [
+    _cfg(8, 2, 4160, 512),     # 128 x 64 tiles, 56 idle columns
+    _cfg(16, 4, 4500, 512),    # ragged last tile
+    _cfg(64, 8, 4097, 256),    # one row in the last tile
+    _cfg(128, 8, 4200, 384),
+    _cfg(8, 1, 4226, 128),
+    _cfg(40, 3, 4300, 128),    # 24 idle columns of 64
+    _cfg(104, 5, 4346, 256),   # 24 idle columns of 128
+    _cfg(256, 8, 4600, 256),   # 128 x 256 tiles, two row blocks
+    _cfg(200, 6, 4700, 128),   # 56 idle columns
+    _cfg(136, 7, 4224, 128),   # 120 idle columns, whole tiles of rows
+]
+
+
+@pytest.mark.parametrize("cfg", FUSED + FEW, ids=lambda c: c.name)
+def test_fused_router_topk(cfg):
+    check(cfg, seed=31)
+
+
+@pytest.mark.parametrize("T", [4500, 900])
+def test_fused_router_topk_with_bias_and_ties(T):
     """A router bias, and the Zipf-skewed bias of the sparse workloads: a hot
     expert chosen by every token and many near-equal scores."""
-    cfg = W.MoEConfig("e96", T=900, d=256, n=64, E=96, K=6, m_tile=64, zipf_s=1.1)
+    cfg = W.MoEConfig("e96", T=T, d=256, n=64, E=96, K=6, m_tile=64, zipf_s=1.1)
     check(cfg, seed=32)
     bias = np.zeros(cfg.E, np.float32)
     bias[5] = 60.0
@@ -129,13 +144,14 @@ def test_fused_router_topk_other_full_sizes(name):
     check(W.CONFIGS[name], seed=0)
 
 
-def test_fused_router_topk_nonfinite_logits():
+@pytest.mark.parametrize("E,K,T", [(128, 8, 4600), (40, 3, 4600), (200, 7, 4600), (128, 8, 600)])
+def test_fused_router_topk_nonfinite_logits(E, K, T):
     """X rows holding NaN, +-Inf or values whose logits overflow give NaN and
     infinite logits.  Every token still gets K distinct experts in [0, E)
     (the exact (score, expert) order is total, NaN included), and the selection,
     weights and bitmap equal those of the top-K kernel run on the fused
     path's own scores."""
-    cfg = W.MoEConfig("e128nf", T=600, d=256, n=64, E=128, K=8, m_tile=128)
+    cfg = W.MoEConfig("nf", T=T, d=256, n=64, E=E, K=K, m_tile=128)
     nan, pinf, ninf = np.uint16(0x7FC0), np.uint16(0x7F80), np.uint16(0xFF80)
 
     def edit(X):
@@ -143,7 +159,7 @@ def test_fused_router_topk_nonfinite_logits():
         X[10, 0] = pinf                # +-Inf logits (and NaN where they cancel)
         X[11, 5] = ninf
         X[20, :] = np.uint16(0x7E00)   # about 4e37 everywhere: logits overflow
-        X[599, 1] = nan                # the ragged last tile
+        X[T - 1, 1] = nan              # the ragged last tile
     inp, o = routings(cfg, 35, edit_x=edit)
     f, r = o["fused"], o["rerun"]
     idx = f["topk_idx"]

@@ -61,11 +61,14 @@ def test_few_rows_per_expert(T, d, n, E, K, zipf, biased):
 
 @pytest.mark.parametrize("T,d,E,K,mode", [
     (1, 128, 8, 1, None),        # one token: one workgroup for top-K and metadata; four k steps
-    (64, 1536, 128, 8, None),    # the last word of the one-workgroup form; several k slices
-    (65, 384, 40, 3, None),      # the first T past it: a lone token in the second word
+    (16, 256, 72, 3, None),      # the last T of the one-workgroup form
+    (17, 256, 72, 3, None),      # the first past it
+    (16, 256, 72, 3, "up"),      # the one-workgroup form for counts and transposed scores, rows left by the rounding
+    (64, 1536, 128, 8, None),    # one whole word; several k slices
+    (65, 384, 40, 3, None),      # a lone token in the second word
     (300, 4096, 200, 16, None),  # K > 8, E off the 64-lane groups
     (1000, 256, 264, 12, "nearest"),
-    (63, 256, 24, 5, "nearest"),  # rounding on the one-workgroup form (counts only)
+    (63, 256, 24, 5, "nearest"),  # rounding on one word, its last token missing
     (4096, 128, 64, 8, None),    # the last T of the few-token form
     (4097, 128, 64, 8, None),    # the first T past it
     (200, 128, 1024, 2, "up"),   # the largest E of the form, transposed scores beyond 64 KB of LDS
@@ -82,7 +85,7 @@ def test_few_token_routing(T, d, E, K, mode):
     torch = _torch()
     from paper_2512_14080_amd import binding as B
     from paper_2512_14080_amd.layer import DeviceLayer
-    cfg = W.MoEConfig("route", T=T, d=d, n=64, E=E, K=K, m_tile=16, zipf_s=0.5)
+    cfg = W.MoEConfig("route", T=T, d=d, n=64, E=E, K=K, m_tile=8 if T == 16 else 16, zipf_s=0.5)
     inp = W.make_inputs(cfg, 34)
     layers = []
     for scores in (None, "given"):
@@ -129,8 +132,9 @@ def test_router_weights_past_32_bit_offsets():
     (16, 8, 8), (17, 72, 5), (70, 136, 8), (33, 264, 16), (90, 520, 7), (20, 1024, 1),
     (16, 64, 5), (40, 64, 6), (40, 136, 7), (33, 264, 8), (16, 1024, 9),  # both selects, on both sides of their rule
     (4100, 264, 8), (4100, 520, 9), (4100, 1024, 2),                      # past the few-token form
+    (4100, 24, 3), (4100, 72, 7), (4100, 40, 12), (4100, 128, 8), (4100, 64, 16),  # lane per token, one wave and four
 ])
-def test_wave_per_token_selection_with_ties(T, E, K):
+def test_selection_with_ties(T, E, K):
     """Given scores with many equal values, zeros of both signs and rows of one
     value: the selection still takes the lowest experts, in the oracle's order."""
     from test_gpu_parity import _torch, check_routing, oracle_routing

@@ -107,3 +107,26 @@ def test_tile_width_follows_the_rounding(tmp_path, dims, form, width):
     launches, = record([call], tmp_path)
     dh, = [n for n in names(launches) if "OpDH" in n]
     assert f"GemmCfgILi256ELi{width}E" in dh
+
+
+def test_kernels_of_the_fused_router_tests(tmp_path):
+    """The shapes that test_gpu_router_topk names fused run the fused router (and with MOE_ROUTE_SEPARATE_TOPK the
+    router GEMM and the lane-per-token kernel); its few-token ones the few-token kernels, with either flag."""
+    from test_gpu_router_topk import FEW, FUSED
+    shapes = [(c.T, c.d, c.n, c.E, c.K) for c in FUSED + FEW]
+    got = record([{"call": "route", "dims": s, "flags": f} for s in shapes for f in (0, B.MOE_ROUTE_SEPARATE_TOPK)],
+                 tmp_path)
+    for i, s in enumerate(shapes):
+        one, two = names(got[2 * i]), names(got[2 * i + 1])
+        if i < len(FUSED):
+            assert "OpRouterTopk" in one[0] and "OpRouterI" in two[0] and "topk_lane" in two[1], s
+        else:
+            assert one == two and "StreamRouter" in one[0] and "topk_few" in one[1], s
+
+
+def test_kernels_of_the_wide_selections(tmp_path):
+    """E > 256 with more than 4096 tokens, and E > 1024 with any number: the wave-per-token kernel over 64-token words."""
+    shapes = [(4200, 264, 3), (4200, 1024, 8), (700, 2056, 16), (700, 4096, 16), (4200, 16, 10), (4200, 24, 3)]
+    for s, l in zip(shapes, record([{"call": "route", "dims": (T, 128, 64, E, K), "flags": B.MOE_ROUTE_SCORES_IN}
+                                    for T, E, K in shapes], tmp_path)):
+        assert ("topk_route" if s[1] > 256 else "topk_lane") in names(l)[0], s
