@@ -1783,22 +1783,19 @@ hipError_t launch_bwd_lists(const int32_t* offsets, int T, int64_t rows, int E, 
 }
 
 // the GEMM over the k-chunk list (its split experts are summed by
-// launch_bwd_final_reduce)
-template <template <class> class Op, class Args>
+// launch_bwd_final_reduce); MIN_M: the least M there is (n 64, d 128)
+template <template <class> class Op, int MIN_M, class Args>
 static hipError_t run_dw(const Args& a, int M, int N, hipStream_t s) {
   const DwTile t = dw_tile(M, N, a.E, a.rows);
   const int grid = pad8((a.E + dw_slabs(a.T, (int64_t)M * N)) * n_tiles(M, t.bm) * n_tiles(N, t.bn));
-  if (t.bn == 256) {
-    if (t.bm == 256) return run<Op<W256x256>>({a}, grid, s);
-    if (t.bm == 128) return run<Op<W128x256>>({a}, grid, s);
-    return run<Op<W64x256>>({a}, grid, s);
-  }
-  if (t.bm == 128) return run<Op<W128x128>>({a}, grid, s);
-  return run<Op<W64x128>>({a}, grid, s);
+  if constexpr (MIN_M == 64)
+    if (t.bm == 64) return t.bn == 256 ? run<Op<W64x256>>({a}, grid, s) : run<Op<W64x128>>({a}, grid, s);
+  if (t.bm == 256) return run<Op<W256x256>>({a}, grid, s);
+  return t.bn == 256 ? run<Op<W128x256>>({a}, grid, s) : run<Op<W128x128>>({a}, grid, s);
 }
 
-hipError_t launch_dw2(const DW2Args& a, hipStream_t s) { return run_dw<OpDW2>(a, a.n, a.d, s); }
-hipError_t launch_dw1(const DW1Args& a, hipStream_t s) { return run_dw<OpDW1>(a, a.d, 2 * a.n, s); }
+hipError_t launch_dw2(const DW2Args& a, hipStream_t s) { return run_dw<OpDW2, 64>(a, a.n, a.d, s); }
+hipError_t launch_dw1(const DW1Args& a, hipStream_t s) { return run_dw<OpDW1, 128>(a, a.d, 2 * a.n, s); }
 
 static DwGrid dw_reduce_grid(int T, int64_t MN) {
   const int slabs = dw_slabs(T, MN);

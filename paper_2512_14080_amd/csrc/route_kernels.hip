@@ -152,22 +152,13 @@ __device__ __forceinline__ void wave_topk(const float (&v)[EPL], int E, int K, P
 constexpr int kTopkWaves = 16;
 
 // Workgroup = 64 tokens (one membership word).  `in` and `scores` may alias
-// (logits overwritten in place by the scores).  With STASH every output of the
-// workgroup's 64 tokens is staged in LDS and written at the end: the scores
-// (token-major and transposed, scores_t[e][t] in 64-token runs) and the top-K
-// lists.  With no global store pending while the token loop runs, the wait
-// for the next token's row (requested one token ahead) covers only loads.
-constexpr int kStashPitch = 65;  // floats per expert row of the stash (bank-conflict-free both ways)
-template <int EPL, bool STASH>
+// (logits overwritten in place by the scores).
+template <int EPL>
 __global__ __launch_bounds__(1024) void topk_route_kernel(const float* in, float* scores, float* __restrict__ scores_t,
                                                          int32_t* __restrict__ topk_idx, float* __restrict__ topk_w,
                                                          uint64_t* __restrict__ mask, int T, int E, int K, int W,
                                                          int do_softmax) {
-  extern __shared__ __attribute__((aligned(16))) char dyn[];
-  unsigned long long* mword = (unsigned long long*)dyn;                  // [E]
-  float* st = (float*)(dyn + ((E * 8 + 15) & ~15));                       // STASH: [E][kStashPitch]
-  int* sidx = (int*)(st + (STASH ? E * kStashPitch : 0));                 // STASH: [64][K]
-  float* sw = (float*)(sidx + (STASH ? 64 * K : 0));                      // STASH: [64][K]
+  extern __shared__ unsigned long long mword[];  // [E]
   const int w = blockIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = lane_id();
@@ -208,52 +199,25 @@ __global__ __launch_bounds__(1024) void topk_route_kernel(const float* in, float
         const int e = lane + 64 * j;
         if (e < E) {
           v[j] = v[j] / s;
-          if (!STASH) scores[(size_t)t * E + e] = v[j];
+          scores[(size_t)t * E + e] = v[j];
         }
       }
     }
-    if (STASH || scores_t) {
+    if (scores_t) {
 #pragma unroll
       for (int j = 0; j < EPL; ++j) {
         const int e = lane + 64 * j;
-        if (e < E) {
-          if (STASH)
-            st[e * kStashPitch + i] = v[j];
-          else
-            scores_t[(size_t)e * T + t] = v[j];
-        }
+        if (e < E) scores_t[(size_t)e * T + t] = v[j];
       }
     }
     wave_topk<EPL>(v, E, K, [&](int k, int e, float wt) {
-      if (STASH) {
-        sidx[i * K + k] = e;
-        sw[i * K + k] = wt;
-      } else {
-        topk_idx[(size_t)t * K + k] = e;
-        topk_w[(size_t)t * K + k] = wt;
-      }
+      topk_idx[(size_t)t * K + k] = e;
+      topk_w[(size_t)t * K + k] = wt;
       atomicOr(&mword[e], 1ull << i);
     });
   }
   __syncthreads();
   for (int e = threadIdx.x; e < E; e += kTopkWaves * 64) mask[(size_t)e * W + w] = mword[e];
-  if (STASH) {
-    const int nt = min(64, T - w * 64);  // tokens of this workgroup
-    if (do_softmax)
-      for (int idx = threadIdx.x; idx < nt * E; idx += kTopkWaves * 64) {
-        const int i = idx / E, e = idx % E;
-        scores[(size_t)(w * 64 + i) * E + e] = st[e * kStashPitch + i];
-      }
-    if (scores_t)
-      for (int idx = threadIdx.x; idx < E * 64; idx += kTopkWaves * 64) {
-        const int e = idx >> 6, i = idx & 63;
-        if (i < nt) scores_t[(size_t)e * T + w * 64 + i] = st[e * kStashPitch + i];
-      }
-    for (int idx = threadIdx.x; idx < nt * K; idx += kTopkWaves * 64) {
-      topk_idx[(size_t)w * 64 * K + idx] = sidx[idx];
-      topk_w[(size_t)w * 64 * K + idx] = sw[idx];
-    }
-  }
 }
 
 // Lane-per-token selection (K <= KM <= 16; E a multiple of 4 * NW, E <= 256).
@@ -1018,13 +982,9 @@ __global__ __launch_bounds__(64 * kPlaceWaves) void token_place_kernel(
 
 // ---------------------------------------------------------------- launchers
 
-static size_t topk_lds_bytes(int E, int K, bool stash) {
-  return ((E * 8 + 15) & ~15) + (stash ? (size_t)E * kStashPitch * 4 + 64 * (size_t)K * 8 : 0);
-}
-
 hipError_t launch_topk_route(const float* in, float* scores, float* scores_t, int32_t* topk_idx, float* topk_w,
                              uint64_t* mask, int T, int E, int K, int W, int do_softmax, hipStream_t s) {
-  if (E % 4 == 0 && E <= 256 && K <= 16 && K <= E) {
+  if (E <= 256) {
     // LDS beyond the default 64 KB of dynamic LDS is granted per kernel
 #define SMOE_TOPK_LANE(KM, NW)                                                                                    \
   do {                                                                                                            \
@@ -1052,22 +1012,12 @@ hipError_t launch_topk_route(const float* in, float* scores, float* scores_t, in
     return hipGetLastError();
   }
   const dim3 grid(W), block(kTopkWaves * 64);
-  const int epl = (E + 63) / 64;
-  // the stash must fit the default 64 KB of dynamic LDS
-  const bool stash = topk_lds_bytes(E, K, true) <= 65536;
 #define SMOE_TOPK(N)                                                                                               \
-  if (epl <= N) {                                                                                                  \
-    if (stash)                                                                                                     \
-      topk_route_kernel<N, true><<<grid, block, topk_lds_bytes(E, K, true), s>>>(in, scores, scores_t, topk_idx,      \
-                                                                               topk_w, mask, T, E, K, W, do_softmax); \
-    else                                                                                                           \
-      topk_route_kernel<N, false><<<grid, block, topk_lds_bytes(E, K, false), s>>>(in, scores, scores_t, topk_idx,    \
-                                                                                 topk_w, mask, T, E, K, W, do_softmax); \
+  if (E <= 64 * N) {                                                                                               \
+    topk_route_kernel<N><<<grid, block, (size_t)E * 8, s>>>(in, scores, scores_t, topk_idx, topk_w, mask, T, E, K, \
+                                                            W, do_softmax);                                        \
     return hipGetLastError();                                                                                      \
   }
-  SMOE_TOPK(1)
-  SMOE_TOPK(2)
-  SMOE_TOPK(4)
   SMOE_TOPK(8)
   SMOE_TOPK(16)
   SMOE_TOPK(32)
@@ -1078,7 +1028,6 @@ hipError_t launch_topk_route(const float* in, float* scores, float* scores_t, in
 
 hipError_t launch_topk_few(const float* in, int slices, const float* bias, float* logits, float* scores_t,
                            const moe_routing& r, int T, int E, int K, int do_softmax, bool counts_only, hipStream_t s) {
-  if (T > kFewTokens || E > kFewExperts) return hipErrorInvalidValue;
   const bool meta = T <= kFewOneGroup;
   const dim3 grid((T + kFewWaves - 1) / kFewWaves), block(64 * kFewWaves);
   // META: E * 12 + 16 K * 8 <= 14 KB; else the transposed scores: E * 68 <= 68 KB
@@ -1109,7 +1058,6 @@ hipError_t launch_topk_few(const float* in, int slices, const float* bias, float
 }
 
 hipError_t launch_tc_metadata_few(const moe_routing& r, int T, int E, int K, bool counts_only, hipStream_t s) {
-  if (T > kFewTokens || E > kFewExperts) return hipErrorInvalidValue;
   const size_t lds = (size_t)E * 16 + 64 * K * 8;  // <= 24 KB
   tc_metadata_few_kernel<<<dim3(r.words), dim3(1024), lds, s>>>(r, T, E, K, counts_only);
   return hipGetLastError();
@@ -1120,7 +1068,6 @@ hipError_t launch_tc_metadata(const moe_routing& r, int T, int E, int K, bool co
   expert_scan_kernel<<<dim3(E), dim3(256), 0, s>>>(r.mask, r.mask_prefix, r.counts, W,
                                                    counts_only ? nullptr : r.status);
   if (counts_only) return hipGetLastError();
-  if (E > 4096) return hipErrorInvalidValue;  // the first rows take 16 KB of LDS
   tc_place_kernel<<<dim3((T + 255) / 256), dim3(256), (size_t)E * 4, s>>>(
       r.topk_idx, r.topk_w, r.mask, r.mask_prefix, r.counts, r.offsets, r.tok_offsets, r.tok_count, r.tok_rows,
       r.row_token, r.row_expert, r.row_w, T, E, K, W, r.status);
