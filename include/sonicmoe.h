@@ -91,7 +91,8 @@ typedef struct {
   int32_t *tok_count;    /* [T]   experts of each token                        */
   float *tok_denom;      /* [T]   sum of the token's selected scores           */
   int32_t *round_dir;    /* [E]   -1 dropped / 0 kept / +1 padded (rounding)   */
-  int32_t *scratch;      /* internal: scans and the rounding select's lists    */
+  int32_t *scratch;      /* internal: scans, the rounding select's lists, the
+                            router's partial logits of few tokens             */
   int32_t *status;       /* [1]   device word: 0 once the metadata kernels have
                             run on a consistent selection; otherwise the OR of
                             MOE_STATUS_* bits, and the rows are not valid
@@ -142,8 +143,9 @@ enum {
                                    and r->state becomes MOE_ROUTING_STATE_COUNTS,
                                    which moe_fwd and moe_bwd refuse          */
   MOE_ROUTE_SEPARATE_TOPK = 16  /* run the router GEMM and softmax/top-K as two
-                                   launches even where they fuse (the logits
-                                   then pass through r->logits or r->scores) */
+                                   launches even where they fuse (with more
+                                   than 4096 tokens the logits then pass
+                                   through r->logits or r->scores)           */
 };
 
 /*
@@ -162,11 +164,13 @@ enum {
  * r->status is cleared by the metadata kernels.
  * With T > 4096, E <= 256 and K <= 8 the softmax and top-K run in the
  * router GEMM's epilogue (one launch; the logits are written only with
- * MOE_ROUTE_WRITE_LOGITS).  With T <= 4096 and E <= 1024 the router GEMM's
- * partial sums pass through r->scratch or r->scores, with or without
- * MOE_ROUTE_SEPARATE_TOPK.  Its scores may differ from the two-launch path's
+ * MOE_ROUTE_WRITE_LOGITS).  Its scores may differ from the two-launch path's
  * in the last bits (the order of the softmax sum); selection, mask and weights
  * are those the two-launch path derives from the scores it writes.
+ * With T <= 4096 and E <= 1024 (d E < 2^31) other kernels run, built for few
+ * tokens: the router GEMM's partial sums pass through r->scratch or r->scores.
+ * MOE_ROUTE_SEPARATE_TOPK only changes the timing classes there.  Calls with
+ * MOE_ROUTE_COUNTS_ONLY take them for small T K only.
  * Scores are compared through the order-preserving image of their fp32 bit
  * pattern, which is the float order for numbers (+0 = -0) and extends it to
  * NaN (sign clear: above +Inf; sign set: below -Inf), so non-finite scores
@@ -326,7 +330,8 @@ enum {
   MOE_KC_ROUTER_GEMM = 0, MOE_KC_TOPK, MOE_KC_META, MOE_KC_ROUND,
   MOE_KC_UP, MOE_KC_DOWN, MOE_KC_AGG_O,
   MOE_KC_DH, MOE_KC_DW2, MOE_KC_DXT, MOE_KC_DW1, MOE_KC_AGG_DX, MOE_KC_DWR,
-  MOE_KC_ROUTER_TOPK, /* the router GEMM with fused softmax/top-K */
+  MOE_KC_ROUTER_TOPK, /* the router GEMM with fused softmax/top-K; for few tokens
+                         (see moe_route) two launches, counted as one */
   MOE_KC_COUNT
 };
 int moe_prof_select(int kernel_class);

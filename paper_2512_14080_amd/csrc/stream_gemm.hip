@@ -345,11 +345,13 @@ struct StreamRouter {
   }
 };
 
-// waves and loads in flight of the row blocks: the widest split of k that
-// keeps two or more steps per wave, within the registers (no spills); a short k
-// (the down-projection of a narrow expert) has two waves with a step or two each,
-// (T = 65, d = 1664, n = 64, E = 312, K = 8: down 26 us with eight waves,
-// six of them idle, 13 with two)
+// Waves and steps of loads in flight of the row blocks, within the registers (no
+// spills): up to eight waves share the k / 32 steps.  From k = 768 on every wave has
+// three or more; k = 256 is one step for each of eight waves, below 256 some of them
+// have none, and a second buffer then re-reads the first step (cached, unused).  A
+// short k (the down-projection of a narrow expert) has two waves with a step or two
+// each (T = 65, d = 1664, n = 64, E = 312, K = 8: down 26 us with eight waves, six of
+// them idle, 13 with two).
 template <class Op>
 static hipError_t run_stream(const typename Op::Params& p, dim3 grid, int mb, int k, hipStream_t s) {
   if (mb == 1 && k >= 768)
