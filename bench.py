@@ -195,14 +195,13 @@ MI355X_XCDS = 8             # GRBM_GUI_ACTIVE sums the busy cycles of the eight 
 FLOP_PER_MFMA_MOP = 512     # SQ_INSTS_VALU_MFMA_MOPS_* count in units of 512 FLOPs
 
 
-def mfma_report(pmc_dir, config="7b"):
+def mfma_report(pmc_dir):
     """Markdown summary of the matrix-core work and utilisation of each GEMM class from one rocprofv3 --pmc
     run of MFMA_COUNTERS: bf16 MFMA FLOPs per launch (512 per counted MOP), the achieved rate over the
     dispatch's own timestamps against the 2.5 PFLOP/s dense peak, the clock the dispatch ran at (busy cycles
     per XCD over its duration) and the share of SIMD cycles the MFMA pipe was busy."""
     import csv
     import glob
-    from paper_2512_14080_amd import workloads as W
     files = glob.glob(os.path.join(pmc_dir, "**", "*counter_collection.csv"), recursive=True)
     if not files:
         raise FileNotFoundError(f"no counter_collection.csv under {pmc_dir}")
@@ -221,18 +220,16 @@ def mfma_report(pmc_dir, config="7b"):
         cls = next((cl for frag, cl in KERNEL_CLASS_OF if frag in name), None)
         if cls is not None and c.get("SQ_INSTS_VALU_MFMA_MOPS_BF16", 0) > 0:
             by_cls.setdefault(cls, []).append((dur, c))
-    c = W.CONFIGS[config]
-    sel = "" if config == "7b" else f" --config {config}"
-    run = f"python3 bench.py{sel} --steps 2 --warmup 1 --no-cpu-baseline"
+    run = "python3 bench.py --steps 2 --warmup 1 --no-cpu-baseline"
     lines = [
-        f"# MFMA work and utilisation per GEMM launch: {config.upper()} layer step (T={c.T}, d={c.d}, n={c.n}, "
-        f"E={c.E}, K={c.K}), token rounding M_tile={c.m_tile} nearest",
+        "# MFMA work and utilisation per GEMM launch: 7B layer step (T=32768, d=1536, n=256, E=128, K=8), token "
+        "rounding M_tile=128 nearest",
         "",
         "Commands (repository root, one MI355X):",
         "",
         "```",
         f"rocprofv3 --pmc {' '.join(MFMA_COUNTERS)} --output-format csv -d {pmc_dir} -o run -- {run}",
-        f"python3 bench.py{sel} --mfma-report {pmc_dir}",
+        f"python3 bench.py --mfma-report {pmc_dir}",
         "```",
         "",
         f"Per launch, averaged over the dispatches of the run: bf16 MFMA FLOPs = {FLOP_PER_MFMA_MOP} x "
@@ -690,7 +687,7 @@ def main():
         print(stats_report(*args.stats_report), end="")
         return
     if args.mfma_report:
-        print(mfma_report(args.mfma_report, args.config), end="")
+        print(mfma_report(args.mfma_report), end="")
         return
     if args.gpus != 1:
         print(f"bench.py measures one GPU only (got --gpus {args.gpus}): the layer is built and measured on a "
